@@ -235,7 +235,7 @@ Dims dims_of(const tlmpm_scene_desc* d)
 }
 
 struct Offsets {
-    size_t X, u, v, H, code, code_prev, D, perm, E, m, V0, cell_start, active, cnt0, cnt1, sc0, sc1, p2g, rs, p2g_x,
+    size_t X, u, v, H, code, code_prev, D, perm, E, m, V0, cell_start, active, binfo, bkey, cnt0, cnt1, sc0, sc1, p2g, rs, p2g_x,
         rs_x, xp2g, xrs, aabb_x, xlist, xin, xg, hist,
         aabb, wpart, Fdot, Gp, wacc, Jmat, Jrig, brig, bmixed, ccode, ckeys, gmeta, gperm, bround, tools, tinfo, ctr, bact, status, dirty, bdirty, pcell, cand_idx, coff, cmask, cstatic, bcand, hbin, hmax, uanc, uanc_x, uref, bor, umm,
         bcount, bids, crec, htab, hnext, ph_n, ph_q, ph_u,
@@ -329,6 +329,8 @@ Offsets plan(const tlmpm_scene_desc* d, long long n_active)
     o.V0 = d->vol0 ? L.take(N * f) : 0;
     o.cell_start = L.take(((size_t)g.n_bricks * TL_CELLS + 1) * 4);
     o.active = L.take((size_t)g.n_bricks * 4);
+    o.binfo = L.take((size_t)n_active * sizeof(int4));
+    o.bkey = L.take((size_t)g.n_bricks * 4);
     o.cnt0 = L.take((size_t)g.NN);
     o.cnt1 = L.take((size_t)g.NN);
     const size_t scap = slot_cap(d);
@@ -621,6 +623,8 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     D.cell_start = (int*)(base + o.cell_start);
     D.active = (int*)(base + o.active);
     D.n_active = (int)active.size();
+    D.binfo = (int4*)(base + o.binfo);
+    D.bkey = (uint32_t*)(base + o.bkey);
     D.cnt[0] = (uint8_t*)(base + o.cnt0);
     D.cnt[1] = (uint8_t*)(base + o.cnt1);
     D.scode[0] = (uint32_t*)(base + o.sc0);
@@ -711,7 +715,7 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     std::vector<float> h(3 * (size_t)N);
     auto up3 = [&](float* dst, const float* src) -> hipError_t {
         for (long long q = 0; q < N; q++)
-            for (int a = 0; a < 3; a++) h[a * N + q] = src ? src[3 * (size_t)perm[q] + a] : 0.0f;
+            for (int a = 0; a < 3; a++) h[3 * (size_t)q + a] = src ? src[3 * (size_t)perm[q] + a] : 0.0f;
         hipError_t e = hipMemcpyAsync(dst, h.data(), 3 * N * sizeof(float), hipMemcpyHostToDevice, sc->st);
         if (e == hipSuccess) e = hipStreamSynchronize(sc->st); // h is reused
         return e;
@@ -748,6 +752,14 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     if (!active.empty() &&
         (e = hipMemcpyAsync(D.active, active.data(), active.size() * 4, hipMemcpyHostToDevice, sc->st)) != hipSuccess)
         return bail(e, "upload bricks");
+    std::vector<int4> binfo(active.size());
+    for (size_t b = 0; b < active.size(); b++) {
+        const int id = active[b];
+        binfo[b] = make_int4(id, id % g.cbx, (id / g.cbx) % g.cby, id / (g.cbx * g.cby));
+    }
+    if (!active.empty() && (e = hipMemcpyAsync(D.binfo, binfo.data(), binfo.size() * sizeof(int4), hipMemcpyHostToDevice,
+                                               sc->st)) != hipSuccess)
+        return bail(e, "upload bricks");
     if ((e = hipMemcpyAsync(D.bact, bact.data(), bact.size() * 4, hipMemcpyHostToDevice, sc->st)) != hipSuccess)
         return bail(e, "upload brick index");
     std::vector<int> qround, qmap;
@@ -781,6 +793,10 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     // contact-history stamp 1 (stored stamps of 0 read as the previous substep's
     // empty history), no F update pending
     if ((e = tl_launch_fill_i32(D.ctr, 1, 1, sc->st)) != hipSuccess) return bail(e, "counters");
+    // cells of bricks without particles (the summaries below cover the others): a zero
+    // would read as a cell of code 0 and give the nodes next to it a slot of that code
+    if ((e = tl_launch_fill_i32((int*)D.ccode, g.n_bricks * TL_CELLS, (int)TL_CC_EMPTY, sc->st)) != hipSuccess)
+        return bail(e, "cell summaries");
     const TlLaunch L = single_launch(sc);
     if ((e = tl_launch_mixed(&L, 1)) != hipSuccess) return bail(e, "cell summaries");
     if ((e = tl_launch_slots(&L, 0, 0, 1)) != hipSuccess) return bail(e, "slot table");
@@ -1342,7 +1358,8 @@ extern "C" tlmpm_status tlmpm_read_state(tlmpm_scene* sc, uint32_t mask, void* c
             float* o = (float*)dst;
             for (long long q = 0; q < N; q++)
                 for (int a = 0; a < comps; a++) {
-                    float val = buf[(size_t)a * N + q];
+                    // (vectors [N][3]; matrices by rows [3][N][3])
+                    float val = buf[comps == 1 ? (size_t)q : 3 * ((size_t)(a / 3) * N + q) + a % 3];
                     if (bit == TLMPM_FIELD_F && (a == 0 || a == 4 || a == 8)) val += 1.0f;
                     o[(size_t)perm[q] * comps + a] = val;
                 }
@@ -1414,7 +1431,7 @@ extern "C" tlmpm_status tlmpm_write_state(tlmpm_scene* sc, uint32_t mask, const 
             for (int a = 0; a < comps; a++) {
                 float val = f[(size_t)perm[q] * comps + a];
                 if (bit == TLMPM_FIELD_F && (a == 0 || a == 4 || a == 8)) val -= 1.0f;
-                buf[(size_t)a * N + q] = val;
+                buf[comps == 1 ? (size_t)q : 3 * ((size_t)(a / 3) * N + q) + a % 3] = val;
             }
         if (N) HIPCHK(hipMemcpyAsync(dstp, buf.data(), (size_t)comps * N * 4, hipMemcpyHostToDevice, sc->st));
         HIPCHK(hipStreamSynchronize(sc->st));

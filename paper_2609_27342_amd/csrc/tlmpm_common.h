@@ -2,7 +2,7 @@
 //
 // Layout in HBM (one scene, all carved from the caller's workspace):
 //   particles, sorted by (brick, cell parity class, cell, input order), SoA float:
-//     X[3][N] reference positions, u[3][N] = x - X, v[3][N], H[9][N] = F - I
+//     X[N][3] reference positions, u[N][3] = x - X, v[N][3], H[3][N][3] = F - I by rows
 //   code[N]      u32: side mask s1 (bits 0-14: digit == 1), s2 (bits 15-29: digit == 2),
 //                bit 30: code_prev[p] holds the code the pending F update must use,
 //                bit 31: material-contact candidate
@@ -109,10 +109,10 @@ struct SceneK {
 
 // device pointers of a scene
 struct SceneD {
-    float* X;      // [3][N]
-    float* u;      // [3][N]
-    float* v;      // [3][N]
-    float* H;      // [9][N]
+    float* X;      // [N][3]
+    float* u;      // [N][3]
+    float* v;      // [N][3]
+    float* H;      // [3][N][3], row r of F - I at H[r]
     uint32_t* code;
     uint32_t* code_prev;
     float* D;
@@ -122,6 +122,8 @@ struct SceneD {
     float* V0;     // [N] or null
     int* cell_start;   // [n_bricks*64 + 1]
     int* active;       // active brick ids
+    int4* binfo;       // [active brick] brick id and its brick coordinates x, y, z
+    uint32_t* bkey;    // [bricks] the one slot key of a brick's particles, or TL_CC_MIXED
     int n_active;
     uint8_t* cnt[2];
     uint32_t* scode[2];
@@ -139,11 +141,11 @@ struct SceneD {
     float* hist;   // rigid contact history [TL_MAX_TOOLS+1][4][N]: u_t xyz, stamp
     float* aabb;   // [n_bricks][8]: min xyz, max xyz, max |v|, 0
     double* wpart; // [TL_MAX_TOOLS * 6][n_active] per-brick wrench sums of the call so far
-    float* Fdot;   // [9][N] rate of F of its last update (viscous scenes), else null
-    float* Gp;     // [9][N] F_p^{-1} - I (plastic scenes), else null
+    float* Fdot;   // [3][N][3] rate of F of its last update (viscous scenes), else null
+    float* Gp;     // [3][N][3] F_p^{-1} - I (plastic scenes), else null
     double* wacc;  // [TL_MAX_TOOLS][6]
-    float* Jmat;   // [3][N] material contact impulse (candidates only)
-    float* Jrig;   // [3][N] floor and tool impulse (bricks with brig set)
+    float* Jmat;   // [N][3] material contact impulse (candidates only)
+    float* Jrig;   // [N][3] floor and tool impulse (bricks with brig set)
     int* brig;     // [bricks] the brick was within reach of a rigid body this substep
     int* bmixed;   // [bricks] a cell of the brick holds two side codes
     uint32_t* ccode; // [bricks * 64] (sorted cell order) the one slot key of a cell, or TL_CC_*

@@ -153,7 +153,7 @@ DEV void anchor_exact(const SceneK& S, const SceneD& D, int bi, int brick, int b
     float r[6] = {1e30f, 1e30f, 1e30f, -1e30f, -1e30f, -1e30f};
     for (int p = beg + threadIdx.x; p < end; p += blockDim.x)
         for (int a = 0; a < 3; a++) {
-            const float ua = D.u[a * N + p];
+            const float ua = D.u[at3(p, a)];
             r[a] = fminf(r[a], ua);
             r[3 + a] = fmaxf(r[3 + a], ua);
         }
@@ -327,9 +327,9 @@ DEV uint32_t bin_hash(int i, int j, int k, uint32_t mask)
 
 DEV void cur_pos(const SceneK& S, const SceneD& D, long long p, float x[3])
 {
-    x[0] = D.X[p] + D.u[p];
-    x[1] = D.X[S.N + p] + D.u[S.N + p];
-    x[2] = D.X[2 * S.N + p] + D.u[2 * S.N + p];
+    x[0] = D.X[at3(p, 0)] + D.u[at3(p, 0)];
+    x[1] = D.X[at3(p, 1)] + D.u[at3(p, 1)];
+    x[2] = D.X[at3(p, 2)] + D.u[at3(p, 2)];
 }
 
 // Candidate record: {id, code, reference cell x | y << 16, cell z}, {x, m}, {v, R}
@@ -345,7 +345,7 @@ DEV void make_rec(const SceneK& S, const SceneD& D, int p, const float x[3], flo
     r[0] = make_float4(__int_as_float(p), __uint_as_float(D.code[p]), __int_as_float(c[0] | (c[1] << 16)),
                        __int_as_float(c[2]));
     r[1] = make_float4(x[0], x[1], x[2], m);
-    r[2] = make_float4(D.v[p], D.v[S.N + p], D.v[2 * S.N + p], 0.5f * S.s_R * cbrtf(V0));
+    r[2] = make_float4(D.v[at3(p, 0)], D.v[at3(p, 1)], D.v[at3(p, 2)], 0.5f * S.s_R * cbrtf(V0));
 }
 
 // Flag in the fourth word of a candidate record (beside the cell's z, 16 bits): the
@@ -868,9 +868,9 @@ DEV void pairs_body(const SceneK& S, const SceneD& D, int bi)
         if (has && l == 0) {
             const int nn = s_nnew[sub];
             D.ph_n[(long long)hnew * N + p] = (stamp << 8) | (nn < TL_PCAP ? nn : TL_PCAP);
-            D.Jmat[p] = Jt[0];
-            D.Jmat[N + p] = Jt[1];
-            D.Jmat[2 * N + p] = Jt[2];
+            D.Jmat[at3(p, 0)] = Jt[0];
+            D.Jmat[at3(p, 1)] = Jt[1];
+            D.Jmat[at3(p, 2)] = Jt[2];
         }
     }
 }

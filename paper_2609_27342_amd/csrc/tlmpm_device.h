@@ -11,6 +11,13 @@
 
 #define DEV __device__ __forceinline__
 
+// ------------------------------------------------------------------ particle arrays
+// Component a of particle p in an array of [N][3] floats, and component a = 3 r + c of a
+// 3x3 matrix kept as three such arrays, one per row r: a lane's row is one 12-byte access
+// and a wave's rows are contiguous.
+DEV size_t at3(long long p, int a) { return 3 * (size_t)p + a; }
+DEV size_t at9(long long N, long long p, int a) { return 3 * ((size_t)(a / 3) * (size_t)N + (size_t)p) + a % 3; }
+
 // ---------------------------------------------------------------------------- codes
 // A side code is held as two 15-bit masks: s1 has bit k set when digit k is 1, s2
 // when it is 2 (Eq. 7 in another basis).  Two codes conflict iff some cut has side

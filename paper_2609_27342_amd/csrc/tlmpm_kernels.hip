@@ -14,14 +14,23 @@
 //   2. an 8-lane butterfly reduce-scatter leaves in lane (i, k) the sum of cell i's
 //      particles for corner k (the j bit 2 stage swaps rows with
 //      v_permlane16_swap, the other two add across the quad with DPP);
-//   3. the 8 waves add their per-node sums into LDS one class after another;
+//   3. every lane writes its sum to its place in LDS, and the quad of lanes that owns a
+//      node adds the 8 places that touch it (one cell of each class), class by class;
 //   4. the box sums are written as this brick's partial; a node's total is the sum
 //      of the partials of the (up to 8) bricks around it, formed in fixed order by
 //      the kernel that consumes it.
+// (Step 3 with the waves adding into one LDS box in turn took 9 barriers a round instead
+// of 2 and a slot lookup per lane, corner and component.)
 //
 // Each node holds one slot (logical grid, Sec. III-D) per side code present in its
 // 8 incident cells, in ascending code order; coupling (Eq. 8) is done per node when
-// a box is finalized.
+// a box is finalized, by the node's quad, a component per lane.
+//
+// What bounds P2G and G2P is the chain of dependent phases in a workgroup (brick record,
+// cell index and partial gather, coupling, particle stage, sums) and their instruction
+// count, at three workgroups per CU (80 registers, 43 to 53 KB of LDS).  The registers
+// hold only because a round recomputes its lane geometry (`late`): hoisted out of the
+// round loop it spills 20 and more words a lane.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -33,6 +42,9 @@
 #include "tlmpm_reach.h"
 #include "tlmpm_device.h"
 
+
+// A value that is the same in every lane, kept in a scalar register
+DEV float scalar(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
 
 DEV int box_index(int X, int Y, int Z) { return (Z * 5 + Y) * 5 + X; }
 
@@ -46,75 +58,89 @@ DEV long long box_gid(const SceneK& S, int bx, int by, int bz, int X, int Y, int
 }
 
 // ------------------------------------------------------------------- box slot table
+// Slots of the 125 box nodes, packed: node bn holds slots [base, base + count), their
+// codes ascending; one word base | count << 16 per node.
 struct BoxTab {
-    int cnt[TL_BOXN];
-    int base[TL_BOXN + 1];
-    long long gid[TL_BOXN];
+    int meta[TL_BOXN];
     uint32_t code[TL_BOX_SLOTS];
-    unsigned char node_of[TL_BOX_SLOTS];
 };
 
-// Phase 1: slot counts of the 125 box nodes (threads < 125, no barrier).
-DEV void box_counts(const SceneK& S, const uint8_t* cnt, int bx, int by, int bz, BoxTab& T)
+// A node's packed word and what a lane knows of its own node
+DEV int tab_base(int meta) { return meta & 0xFFFF; }
+DEV int tab_count(int meta) { return meta >> 16; }
+
+// LDS words written by lanes of this wave are read by other lanes of it from here on
+// (a wave's LDS operations run in order; this only keeps the compiler from moving them)
+DEV void wave_lds_fence()
 {
-    const int tid = threadIdx.x;
-    if (tid < TL_BOXN) {
-        int X = tid % 5, Y = (tid / 5) % 5, Z = tid / 25;
-        long long g = box_gid(S, bx, by, bz, X, Y, Z);
-        T.gid[tid] = g;
-        T.cnt[tid] = g >= 0 ? (int)cnt[g] : 0;
-    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
-// Phase 2 (after a barrier): exclusive scan of the counts by wave `wave`.
-DEV void box_scan(BoxTab& T, int* s_total, int wave)
+// Inclusive scan over the 64 lanes by DPP row shifts and row broadcasts
+DEV int wave_scan(int x)
 {
-    const int tid = threadIdx.x;
-    if ((tid >> 6) != wave) return;
-    const int l = tid & 63;
-    int a = 2 * l, b = 2 * l + 1;
-    int va = a < TL_BOXN ? T.cnt[a] : 0;
-    int vb = b < TL_BOXN ? T.cnt[b] : 0;
-    int sum = va + vb, incl = sum;
-    for (int o = 1; o < 64; o <<= 1) {
-        int t = __shfl_up(incl, o, 64);
-        if (l >= o) incl += t;
-    }
-    int excl = incl - sum;
-    if (a < TL_BOXN) T.base[a] = excl;
-    if (b < TL_BOXN) T.base[b] = excl + va;
-    if (l == 63) {
-        T.base[TL_BOXN] = incl;
-        *s_total = incl;
-    }
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false); // row_shr 1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false); // row_bcast 15 to rows 1, 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false); // row_bcast 31 to rows 2, 3
+    return x;
 }
 
-// Phase 3 (after a barrier, threads < 125): codes of this thread's node.
-// The same in two steps, so that the code loads are in flight together with the
-// loads that follow (the partial gather): the first two codes of node bn into
-// registers, then into the table (further codes loaded there).
-DEV void codes_pre(const SceneK& S, const uint32_t* scode, const BoxTab& T, int bn, uint32_t pre[2])
+// The counts of box nodes 2 l and 2 l + 1 in lane l (every wave loads all of them).
+struct BoxCounts {
+    int a, b;
+    DEV void load(const SceneK& S, const uint8_t* cnt, int bx, int by, int bz)
+    {
+        const int l = threadIdx.x & 63;
+        a = node_count(S, cnt, bx, by, bz, 2 * l);
+        b = node_count(S, cnt, bx, by, bz, 2 * l + 1);
+    }
+    static DEV int node_count(const SceneK& S, const uint8_t* cnt, int bx, int by, int bz, int n)
+    {
+        if (n >= TL_BOXN) return 0;
+        const long long g = box_gid(S, bx, by, bz, n % 5, (n / 5) % 5, n / 25);
+        return g >= 0 ? (int)cnt[g] : 0;
+    }
+    // Packed words of all nodes: wave 0 writes them to T (read after the next barrier);
+    // returns the total (every wave alike) and in `own` the word of node bn (no barrier:
+    // every wave scans for itself).
+    DEV int scan(BoxTab& T, int bn, int& own) const
+    {
+        const int l = threadIdx.x & 63;
+        const int incl = wave_scan(a + b), base = incl - a - b;
+        if (threadIdx.x < 64) {
+            if (2 * l < TL_BOXN) T.meta[2 * l] = base | (a << 16);
+            if (2 * l + 1 < TL_BOXN) T.meta[2 * l + 1] = (base + a) | (b << 16);
+        }
+        const int pair = __shfl(base | (a << 16) | (b << 24), bn >> 1, 64);
+        const int pb = pair & 0xFFFF, pa = (pair >> 16) & 0xFF, pc = (pair >> 24) & 0xFF;
+        own = (bn & 1) ? (pb + pa) | (pc << 16) : pb | (pa << 16);
+        return __builtin_amdgcn_readlane(incl, 63);
+    }
+};
+
+// Codes of the slots of node bn, loaded by the quad that owns it: lane u takes slots u,
+// u + 4, ...; the first one is loaded ahead (pre) so that it is in flight with the
+// partial gather.
+DEV uint32_t codes_pre(const SceneK& S, const uint32_t* scode, int meta, long long gid, int u)
 {
-    const int c = T.cnt[bn];
-    const long long g = T.gid[bn];
-    pre[0] = c > 0 ? scode[g] : 0u;
-    pre[1] = c > 1 ? scode[S.NN + g] : 0u;
+    return u < tab_count(meta) ? scode[(long long)u * S.NN + gid] : 0u;
 }
 
-DEV void codes_put(const SceneK& S, const uint32_t* scode, BoxTab& T, int bn, const uint32_t pre[2])
+DEV void codes_put(const SceneK& S, const uint32_t* scode, BoxTab& T, int meta, long long gid, int u, uint32_t pre)
 {
-    const int c = T.cnt[bn], b0 = T.base[bn];
-    const long long g = T.gid[bn];
-    for (int s = 0; s < c; s++) {
-        T.code[b0 + s] = s == 0 ? pre[0] : s == 1 ? pre[1] : scode[(long long)s * S.NN + g];
-        T.node_of[b0 + s] = (unsigned char)bn;
-    }
+    const int c = tab_count(meta), b0 = tab_base(meta);
+    if (u < c) T.code[b0 + u] = pre;
+    for (int s = u + 4; s < c; s += 4) T.code[b0 + s] = scode[(long long)s * S.NN + gid];
 }
 
 DEV int find_slot(const BoxTab& T, int bn, uint32_t key)
 {
-    int c = T.cnt[bn], b0 = T.base[bn];
-    if (c == 1) return T.code[b0] == key ? b0 : -1;
+    const int m = T.meta[bn], c = tab_count(m), b0 = tab_base(m);
     for (int s = 0; s < c; s++)
         if (T.code[b0 + s] == key) return b0 + s;
     return -1;
@@ -129,114 +155,98 @@ struct QPad {
     static constexpr int value = (Q + 3) & ~3;
 };
 
-// Active indices of the 27 bricks around (bx, by, bz) (-1: none), by threads
-// [TL_BOXN, TL_BOXN + 27) of the block; read after the next barrier.
-DEV void load_neighbours(const SceneK& S, const SceneD& D, int bx, int by, int bz, int* nb)
-{
-    const int t = (int)threadIdx.x - TL_BOXN;
-    if (t < 0 || t >= 27) return;
-    const int x = bx + t % 3 - 1, y = by + (t / 3) % 3 - 1, z = bz + t / 9 - 1;
-    nb[t] = (x < 0 || y < 0 || z < 0 || x >= S.cbx || y >= S.cby || z >= S.cbz)
-                ? -1
-                : D.bact[((long long)z * S.cby + y) * S.cbx + x];
-}
-
-// Sums of all slots of box node bn over the bricks that contributed to it, written
-// to dst[slot * Q + c], formed by the 4 threads u = 0..3 of a quad (lanes 4 bn ..
-// 4 bn + 3): contributor d is the brick at home - (d & 1, d >> 1 & 1, d >> 2 & 1),
-// which holds the node at box position (l + 4 * offset); thread u loads contributors u
-// and u + 4 (each its first partial plus, where xflag is set, the partial of its later
-// same-code rounds), the quad adds its 4 sums ((0 + 1) + (2 + 3)) and thread 0
-// writes them.  The order is fixed: results are bitwise reproducible.
-template <int Q>
-DEV void gather_node4(const SceneK& S, const int* nb, const float* __restrict__ part, const float* __restrict__ xpart,
-                      const int* __restrict__ xflag, const BoxTab& T, int bn, int u, float* dst)
-{
-    constexpr int QP = QPad<Q>::value;
-    const int c = T.cnt[bn], b0 = T.base[bn];
-    const int X = bn % 5, Y = (bn / 5) % 5, Z = bn / 25;
-    const int lx = X & 3, ly = Y & 3, lz = Z & 3;
-    unsigned cbase[2] = {0u, 0u};
-    unsigned valid = 0, extra = 0;
+// The two contributors of box node bn that lane u of its quad loads: contributor d is
+// the brick at home - (d & 1, d >> 1 & 1, d >> 2 & 1), which holds the node at box
+// position (l + 4 * offset); lane u takes d = u and u + 4.  nb: the active indices of the
+// 27 bricks around in lanes 0..26; every lane of the wave calls this.
+struct Contrib {
+    int ai[2];       // active index, -1: none
+    unsigned rec[2]; // record of slot 0 (in nodes)
+    DEV void set(const SceneK& S, int nb, int bn, int u)
+    {
+        const int X = bn % 5, Y = (bn / 5) % 5, Z = bn / 25;
+        const int lx = X & 3, ly = Y & 3, lz = Z & 3;
+        const int dx = u & 1, dy = u >> 1;
 #pragma unroll
-    for (int e = 0; e < 2; e++) {
-        const int d = u + 4 * e;
-        const int dx = d & 1, dy = (d >> 1) & 1, dz = (d >> 2) & 1;
-        if ((dx && lx) || (dy && ly) || (dz && lz)) continue;
-        const int ai = nb[((Z >> 2) - dz + 1) * 9 + ((Y >> 2) - dy + 1) * 3 + ((X >> 2) - dx + 1)];
-        if (ai < 0) continue;
-        const int pn = (lx + 4 * dx) + 5 * (ly + 4 * dy) + 25 * (lz + 4 * dz);
-        cbase[e] = (unsigned)ai * (unsigned)(S.scap * TL_BOXN) + (unsigned)pn;
-        valid |= 1u << e;
-        if (xflag && xflag[ai]) extra |= 1u << e;
+        for (int dz = 0; dz < 2; dz++) {
+            const int at = ((Z >> 2) - dz + 1) * 9 + ((Y >> 2) - dy + 1) * 3 + ((X >> 2) - dx + 1);
+            const int i = __shfl(nb, at, 64);
+            ai[dz] = (bn < TL_BOXN && !((dx && lx) || (dy && ly) || (dz && lz))) ? i : -1;
+            const int pn = (lx + 4 * dx) + 5 * (ly + 4 * dy) + 25 * (lz + 4 * dz);
+            rec[dz] = (unsigned)i * (unsigned)(S.scap * TL_BOXN) + (unsigned)pn;
+        }
     }
-    for (int s = 0; s < c; s++) {
-        float acc[QP];
-#pragma unroll
-        for (int q = 0; q < QP; q++) acc[q] = 0.0f;
+};
+
+// One slot's two loads of a lane and their sum over the quad: (own pair), then lanes
+// ^ 1, then ^ 2.  The order is fixed: results are bitwise reproducible.  Every lane of
+// the quad gets the sum.
+template <int QP>
+struct Gather {
+    float4 v[2][QP / 4];
+    DEV void load(const float* __restrict__ part, const Contrib& C, int s, bool on)
+    {
 #pragma unroll
         for (int e = 0; e < 2; e++) {
-            if (!(valid & (1u << e))) continue;
-            const size_t rec = (size_t)(cbase[e] + (unsigned)(s * TL_BOXN)) * QP;
-            const float4* pp = (const float4*)(part + rec);
-            float4 v4[QP / 4];
 #pragma unroll
-            for (int q4 = 0; q4 < QP / 4; q4++) v4[q4] = pp[q4];
-            if (extra & (1u << e)) {
-                const float4* xp = (const float4*)(xpart + rec);
+            for (int q = 0; q < QP / 4; q++) v[e][q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (on && C.ai[e] >= 0) {
+                const float4* pp = (const float4*)(part + (size_t)(C.rec[e] + (unsigned)(s * TL_BOXN)) * QP);
 #pragma unroll
-                for (int q4 = 0; q4 < QP / 4; q4++) {
-                    const float4 x4 = xp[q4];
-                    v4[q4].x += x4.x;
-                    v4[q4].y += x4.y;
-                    v4[q4].z += x4.z;
-                    v4[q4].w += x4.w;
-                }
-            }
-#pragma unroll
-            for (int q4 = 0; q4 < QP / 4; q4++) {
-                acc[4 * q4 + 0] += v4[q4].x;
-                acc[4 * q4 + 1] += v4[q4].y;
-                acc[4 * q4 + 2] += v4[q4].z;
-                acc[4 * q4 + 3] += v4[q4].w;
+                for (int q = 0; q < QP / 4; q++) v[e][q] = pp[q];
             }
         }
+    }
+    // a split brick's second partial, added to its first
+    DEV void add(const float* __restrict__ xpart, const int* __restrict__ xflag, const Contrib& C, int s)
+    {
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+            if (C.ai[e] < 0 || !xflag[C.ai[e]]) continue;
+            const float4* xp = (const float4*)(xpart + (size_t)(C.rec[e] + (unsigned)(s * TL_BOXN)) * QP);
+#pragma unroll
+            for (int q = 0; q < QP / 4; q++) {
+                const float4 x4 = xp[q];
+                v[e][q].x += x4.x;
+                v[e][q].y += x4.y;
+                v[e][q].z += x4.z;
+                v[e][q].w += x4.w;
+            }
+        }
+    }
+    template <int Q>
+    DEV void sum(float (&acc)[Q]) const
+    {
 #pragma unroll
         for (int q = 0; q < Q; q++) {
+            const float4 a = v[0][q / 4], b = v[1][q / 4];
+            acc[q] = (q % 4 == 0) ? a.x + b.x : (q % 4 == 1) ? a.y + b.y : (q % 4 == 2) ? a.z + b.z : a.w + b.w;
             acc[q] += lane_xor<1>(acc[q]);
             acc[q] += lane_xor<2>(acc[q]);
         }
-        if (u == 0)
-#pragma unroll
-            for (int q = 0; q < Q; q++) dst[(b0 + s) * Q + q] = acc[q];
     }
-}
+};
 
-// Compatibility coupling of one 3-vector field at a node with slots [b0, b0+c)
-// (Eq. 8): f_a += (1/M) sum_{b != a, compatible} (m_a f_b - m_b f_a), M = sum of
-// all slot masses; fields read from src (stride Q, offset off) and written to dst
-// (stride 3), all pre-exchange values.
-template <int Q>
-DEV void couple_node(const BoxTab& T, int b0, int c, const float* src, int off, float* dst)
+// Compatibility coupling of component `off` of a node with slots [b0, b0 + c) (Eq. 8):
+// f_a += (1/M) sum_{b != a, compatible} (m_a f_b - m_b f_a), M = sum of all slot masses;
+// src[slot * Q] the masses, src[slot * Q + off] the field, all pre-exchange values.
+// Calls put(slot, m, f_bar).
+template <int Q, class Put>
+DEV void couple_component(const BoxTab& T, int b0, int c, const float* src, int off, Put&& put)
 {
-    if (c == 1) {
-        for (int j = 0; j < 3; j++) dst[b0 * 3 + j] = src[b0 * Q + off + j];
-        return;
-    }
     float M = 0.0f;
     for (int a = 0; a < c; a++) M += src[(b0 + a) * Q];
-    float invM = M > 0.0f ? 1.0f / M : 0.0f;
+    const float invM = M > 0.0f ? 1.0f / M : 0.0f;
     for (int a = 0; a < c; a++) {
-        uint32_t ca = T.code[b0 + a];
-        float ma = src[(b0 + a) * Q];
-        float fa[3] = {src[(b0 + a) * Q + off], src[(b0 + a) * Q + off + 1], src[(b0 + a) * Q + off + 2]};
-        float acc[3] = {0.0f, 0.0f, 0.0f};
+        const uint32_t ca = T.code[b0 + a];
+        const float ma = src[(b0 + a) * Q], fa = src[(b0 + a) * Q + off];
+        float acc = 0.0f;
         for (int b = 0; b < c; b++) {
             if (b == a || codes_conflict(ca, T.code[b0 + b])) continue;
-            float mb = src[(b0 + b) * Q];
-            for (int j = 0; j < 3; j++) acc[j] += ma * src[(b0 + b) * Q + off + j] - mb * fa[j];
+            const float mb = src[(b0 + b) * Q];
+            acc += ma * src[(b0 + b) * Q + off] - mb * fa;
         }
-        for (int j = 0; j < 3; j++) dst[(b0 + a) * 3 + j] = fa[j] + acc[j] * invM;
+        put(b0 + a, ma, fa + acc * invM);
     }
 }
 
@@ -247,10 +257,10 @@ struct Lane {
     int beg, count;    // particles of the cell
 };
 
-DEV Lane lane_of(const SceneD& D, int brick)
+// Place of thread tid in its brick
+DEV Lane lane_at(int tid)
 {
     Lane L;
-    int tid = threadIdx.x;
     L.w = tid >> 6;
     L.lane = tid & 63;
     L.i = ((L.lane >> 2) & 3) | ((L.lane >> 3) & 4); // lane bits 2, 3, 5
@@ -258,16 +268,30 @@ DEV Lane lane_of(const SceneD& D, int brick)
     L.cxl = 2 * (L.i & 1) + (L.w & 1);
     L.cyl = 2 * ((L.i >> 1) & 1) + ((L.w >> 1) & 1);
     L.czl = 2 * ((L.i >> 2) & 1) + ((L.w >> 2) & 1);
+    L.beg = L.count = 0;
+    return L;
+}
+
+DEV void lane_cell(const SceneD& D, int brick, Lane& L)
+{
     const int* cs = D.cell_start + (long long)brick * TL_CELLS + L.w * 8 + L.i;
     L.beg = cs[0];
     L.count = cs[1] - cs[0];
-    return L;
+}
+
+// The same value, computed from no earlier than here: keeps what is derived from it (the
+// addresses of a round's loads, stores and LDS places) out of the registers of the code
+// before, where it would be spilled
+DEV int late(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
 }
 
 // Particle of this lane in round r.  Bricks whose cells each hold one code take
 // particle 8 r + j of the lane's cell; bricks with a mixed cell take particle j of
 // the cell's r-th same-code group (group table built when the codes change).
-DEV bool lane_particle(const SceneD& D, int bi, bool grouped, const Lane& L, int r, long long& p)
+DEV bool lane_particle(const SceneD& D, int bi, bool grouped, const Lane& L, int r, int& p)
 {
     if (!grouped) {
         const int jj = 8 * r + L.j;
@@ -376,64 +400,6 @@ DEV void reduce_scatter8(Gen&& gen, float (&res)[Q], int j)
             const float keep = b0 ? c2[1][q] : c2[0][q];
             res[q] = keep + lane_xor<1>(send);
         }
-    }
-}
-
-// Adds a wave's per-node sums to the LDS box accumulator, one parity class after
-// another (fixed order).  The QA + QB components come from two generators (two
-// butterflies keep fewer partial sums live).  Every 8-lane group holds particles
-// of one code (bricks with a mixed cell are processed in same-code groups).
-// Component q of the generated values is stored at (q + ROT) mod Q of a slot.
-template <int QA, int QB, bool REL, int ROT = 0, class GA, class GB>
-DEV void accumulate_classes(const Lane& L, bool valid, uint32_t key, GA&& ga, GB&& gb, const BoxTab& T, float* acc,
-                            int* status)
-{
-    constexpr int Q = QA + QB;
-    const int leader = L.lane & ~0x13; // j = 0 of the lane's cell
-    const uint32_t lkey = __shfl(key, leader, 64);
-    const bool gvalid = __shfl((int)valid, leader, 64) != 0;
-    if (__any(valid && key != lkey) && L.lane == 0) atomicOr(status, TL_ST_LOOKUP);
-    float res[Q];
-    {
-        float ra[QA];
-        reduce_scatter8<QA, REL>(ga, ra, L.j);
-#pragma unroll
-        for (int q = 0; q < QA; q++) res[q] = ra[q];
-        if constexpr (QB > 0) {
-            float rb[QB];
-            reduce_scatter8<QB, REL>(gb, rb, L.j);
-#pragma unroll
-            for (int q = 0; q < QB; q++) res[QA + q] = rb[q];
-        }
-    }
-    const int bn = box_index(L.cxl + (L.j & 1), L.cyl + ((L.j >> 1) & 1), L.czl + ((L.j >> 2) & 1));
-    for (int phase = 0; phase < 8; phase++) {
-        lds_barrier();
-        if (L.w != phase || !gvalid) continue;
-        int sl = find_slot(T, bn, lkey);
-        if (sl < 0)
-            atomicOr(status, TL_ST_LOOKUP);
-        else
-#pragma unroll
-            for (int q = 0; q < Q; q++) acc[sl * Q + (q + ROT) % Q] += res[q];
-    }
-    lds_barrier();
-}
-
-// Writes the box accumulator as this brick's partial (layout of gather_node4).
-template <int Q>
-DEV void write_partials(const SceneK& S, float* __restrict__ part, int bi, const BoxTab& T, int total, const float* acc)
-{
-    constexpr int QP = QPad<Q>::value;
-    for (int q = threadIdx.x; q < total; q += blockDim.x) {
-        int bn = T.node_of[q];
-        int s = q - T.base[bn];
-        float4* pp = (float4*)(part + (((long long)bi * S.scap + s) * TL_BOXN + bn) * QP);
-        float v[QP];
-#pragma unroll
-        for (int c = 0; c < QP; c++) v[c] = c < Q ? acc[q * Q + c] : 0.0f;
-#pragma unroll
-        for (int q4 = 0; q4 < QP / 4; q4++) pp[q4] = make_float4(v[4 * q4], v[4 * q4 + 1], v[4 * q4 + 2], v[4 * q4 + 3]);
     }
 }
 
@@ -632,8 +598,8 @@ DEV void rigid_body(const SceneK& S, const SceneD& D, int bi)
             float Jc[3] = {0.0f, 0.0f, 0.0f};
             if (valid) {
                 for (int a = 0; a < 3; a++) {
-                    x[a] = (double)D.X[a * N + p] + (double)D.u[a * N + p];
-                    v[a] = D.v[a * N + p];
+                    x[a] = (double)D.X[at3(p, a)] + (double)D.u[at3(p, a)];
+                    v[a] = D.v[at3(p, a)];
                 }
                 m = S.m_uniform ? S.m0 : D.m[p];
                 V0 = S.v_uniform ? S.V0 : D.V0[p];
@@ -656,9 +622,9 @@ DEV void rigid_body(const SceneK& S, const SceneD& D, int bi)
                 }
             }
             if (valid) {
-                D.Jrig[p] = Jc[0];
-                D.Jrig[N + p] = Jc[1];
-                D.Jrig[2 * N + p] = Jc[2];
+                D.Jrig[at3(p, 0)] = Jc[0];
+                D.Jrig[at3(p, 1)] = Jc[1];
+                D.Jrig[at3(p, 2)] = Jc[2];
                 if (Dp != Ds) D.D[p] = Dp;
             }
         }
@@ -669,6 +635,443 @@ DEV void rigid_body(const SceneK& S, const SceneD& D, int bi)
             float acc = 0.0f;
             for (int w = 0; w < 4; w++) acc += s_wr[w][tid];
             D.wpart[(long long)tid * D.n_active + bi] += (double)acc;
+        }
+    }
+}
+
+// ------------------------------------------------------- particle stage of P2G
+// F update from the gradient Lg of the remapped velocities (MUSL), stored with the
+// finite check; a particle whose code changed in this substep's label pass used its
+// previous code for it and drops that mark.
+DEV void store_F(const SceneD& D, long long N, long long p, float dt, const float* Lg, float* H, uint32_t& code)
+{
+    bool fin = true;
+    for (int a = 0; a < 9; a++) {
+        H[a] += dt * Lg[a];
+        D.H[at9(N, p, a)] = H[a];
+        fin = fin && isfinite(H[a]);
+    }
+    if (!fin) atomicOr(D.status, TL_ST_NONFINITE);
+    if (code & TL_PREV_BIT) {
+        code &= ~TL_PREV_BIT;
+        D.code[p] = code;
+    }
+}
+
+// MAT 1: plastic projection after an F update, and the rate of F for the viscosity
+// (kept for the substeps whose P2G has no pending update: the first, or after a
+// state read)
+template <int MAT>
+DEV void plastic_rate(const SceneK& S, const SceneD& D, long long N, long long p, bool updated, const float* H,
+                      float* Lg, float* Gp)
+{
+    if constexpr (MAT == 1) {
+        // plasticity: F_p^{-1} = I + Gp; projection after each F update
+        if (S.ystress > 0.0f) {
+#pragma unroll
+            for (int a = 0; a < 9; a++) Gp[a] = D.Gp[at9(N, p, a)];
+            if (updated) {
+                float K[9]; // F_e - I = H + Gp + H Gp
+#pragma unroll
+                for (int i = 0; i < 3; i++)
+#pragma unroll
+                    for (int j = 0; j < 3; j++) {
+                        float k = H[3 * i + j] + Gp[3 * i + j];
+#pragma unroll
+                        for (int m = 0; m < 3; m++) k += H[3 * i + m] * Gp[3 * m + j];
+                        K[3 * i + j] = k;
+                    }
+                const float Ey = S.e_uniform ? S.E0 : D.E[p];
+                if (vm_project(Ey, S.nu, S.ystress, K, Gp))
+#pragma unroll
+                    for (int a = 0; a < 9; a++) D.Gp[at9(N, p, a)] = Gp[a];
+            }
+        }
+        if (S.visc > 0.0f) {
+            if (updated) {
+#pragma unroll
+                for (int a = 0; a < 9; a++) D.Fdot[at9(N, p, a)] = Lg[a];
+            } else {
+#pragma unroll
+                for (int a = 0; a < 9; a++) Lg[a] = D.Fdot[at9(N, p, a)];
+            }
+        }
+    }
+}
+
+// First Piola-Kirchhoff stress of a particle (zero with the status bit set where J <= 0
+// or the state is not finite)
+template <int MAT>
+DEV void particle_stress(const SceneK& S, const SceneD& D, float E, const float* H, const float* Lg, const float* Gp,
+                         float* Pk)
+{
+    bool ok;
+    if constexpr (MAT == 1) {
+        if (S.ystress > 0.0f) {
+            // P = P_fcr(F_e) F_p^{-T}, F_e - I = H + Gp + H Gp, F_p^{-1} = I + Gp
+            float K[9], Pe[9];
+#pragma unroll
+            for (int i = 0; i < 3; i++)
+#pragma unroll
+                for (int j = 0; j < 3; j++) {
+                    float k = H[3 * i + j] + Gp[3 * i + j];
+#pragma unroll
+                    for (int m = 0; m < 3; m++) k += H[3 * i + m] * Gp[3 * m + j];
+                    K[3 * i + j] = k;
+                }
+            ok = fixed_corotated(E, S.nu, K, Pe);
+#pragma unroll
+            for (int i = 0; i < 3; i++)
+#pragma unroll
+                for (int j = 0; j < 3; j++) {
+                    float a = Pe[3 * i + j];
+#pragma unroll
+                    for (int m = 0; m < 3; m++) a += Pe[3 * i + m] * Gp[3 * j + m];
+                    Pk[3 * i + j] = a;
+                }
+        } else {
+            ok = S.material == 1 ? fixed_corotated(E, S.nu, H, Pk) : neo_hookean(E, S.nu, H, Pk);
+        }
+    } else {
+        ok = neo_hookean(E, S.nu, H, Pk);
+    }
+    if (ok && MAT == 1 && S.visc > 0.0f) add_viscous(S.visc, H, Lg, Pk);
+    if (!ok) {
+        atomicOr(D.status, TL_ST_NONFINITE);
+        for (int a = 0; a < 9; a++) Pk[a] = 0.0f;
+    }
+}
+
+// What a particle adds to the 8 corners of its cell: w (m, m v) and A grad N + w ext
+// with A = -dt V0 P (Eq. 2); a zero weight contributes nothing (reading R7).
+struct Scatter {
+    float t[3], A[9], ext[3], vel[3], m, inv_dx;
+    bool valid;
+    // (absolute corners: the CornerW order needs more registers here than the selects
+    // it saves, the impulses also need per-lane gradient signs)
+    DEV void mp(int k, float* o) const // mass and momentum
+    {
+        float wx, wy, wz;
+        corner_weights(t, k, wx, wy, wz);
+        float wm = wx * wy * wz * m;
+        o[0] = wm;
+        o[1] = wm * vel[0];
+        o[2] = wm * vel[1];
+        o[3] = wm * vel[2];
+    }
+    DEV void dp(int k, float* o) const // internal, external and contact impulse
+    {
+        float wx, wy, wz;
+        corner_weights(t, k, wx, wy, wz);
+        float w = wx * wy * wz;
+        float g0 = ((k & 1) ? inv_dx : -inv_dx) * wy * wz;
+        float g1 = ((k & 2) ? inv_dx : -inv_dx) * wx * wz;
+        float g2 = ((k & 4) ? inv_dx : -inv_dx) * wx * wy;
+        bool on = valid && w != 0.0f;
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            float f = A[3 * a] * g0 + A[3 * a + 1] * g1 + A[3 * a + 2] * g2 + w * ext[a];
+            o[a] = on ? f : 0.0f;
+        }
+    }
+};
+
+// Stress and external impulses of the lane's particle, ready to scatter
+template <int MAT>
+DEV void scatter_setup(const SceneK& S, const SceneD& D, long long N, long long p, bool valid, bool rig, uint32_t code,
+                       const float* H, const float* Lg, const float* Gp, const float* t, Scatter& C)
+{
+    const float dt = S.dt;
+    float m = 0.0f, V0 = 0.0f;
+    C.valid = valid;
+    C.inv_dx = S.inv_dx;
+    for (int a = 0; a < 3; a++) {
+        C.t[a] = t[a];
+        C.vel[a] = C.ext[a] = 0.0f;
+    }
+    if (valid) {
+        // (loaded here, not with the rest: in flight during the stress)
+        float jr[3] = {0.0f, 0.0f, 0.0f}, jm[3] = {0.0f, 0.0f, 0.0f};
+        for (int a = 0; a < 3; a++) C.vel[a] = D.v[at3(p, a)];
+        m = S.m_uniform ? S.m0 : D.m[p];
+        V0 = S.v_uniform ? S.V0 : D.V0[p];
+        const float E = S.e_uniform ? S.E0 : D.E[p];
+        if (rig) // floor and tool impulses of this substep (k_rigid)
+            for (int a = 0; a < 3; a++) jr[a] = D.Jrig[at3(p, a)];
+        if (S.material_contact && (code & TL_CAND_BIT))
+            for (int a = 0; a < 3; a++) jm[a] = D.Jmat[at3(p, a)];
+        particle_stress<MAT>(S, D, E, H, Lg, Gp, C.A);
+        C.ext[0] = (jr[0] + jm[0]) + dt * m * S.gx;
+        C.ext[1] = (jr[1] + jm[1]) + dt * m * S.gy;
+        C.ext[2] = (jr[2] + jm[2]) + dt * m * S.gz;
+    } else {
+        for (int a = 0; a < 9; a++) C.A[a] = 0.0f;
+    }
+    const float sA = -dt * V0;
+#pragma unroll
+    for (int a = 0; a < 9; a++) C.A[a] *= sA;
+    C.m = valid ? m : 0.0f;
+}
+
+// --------------------------------------------------------------- one-code bricks
+// Most bricks lie away from every cut: all particles of the 27 bricks around them hold
+// one side code.  The nodes of such a brick's box then hold one slot each, number 0, in
+// every table, so P2G and G2P need no slot tables there: a box value is indexed by its
+// node, the coupling is the identity, and the sum of a node over the 8 parity classes
+// reads 8 known places (one cell of each class touches a node) instead of taking the
+// classes one after another.  The sums keep the order of the general path, so a
+// brick's results are bitwise the same on either path.  Box of 14.2M particles with three
+// cuts (about a quarter of the bricks near one): P2G 746 -> 570 us, G2P 598 -> 422 us; a
+// block of 4 bricks, where one workgroup's chain is all: 13.0 -> 8.6 and 11.7 -> 7.1 us.
+
+// Whether brick (bx, by, bz) is such a brick; every wave decides by itself from the
+// same words, without a barrier.  nb: in lanes 0..26 the active index of the brick at
+// offset (l % 3 - 1, l / 3 % 3 - 1, l / 9 - 1), -1 if it holds no particle.  STAMP: also
+// require that no label pass changed the codes of these bricks since the last G2P
+// (`changed` false: the pending re-scatter sums then have the same slots).
+template <bool STAMP>
+DEV bool one_code(const SceneK& S, const SceneD& D, int bx, int by, int bz, int& nb, bool& changed)
+{
+    const int l = threadIdx.x & 63;
+    nb = -1;
+    uint32_t key = 0u;
+    bool ch = false;
+    if (l < 27) {
+        const int x = bx + l % 3 - 1, y = by + (l / 3) % 3 - 1, z = bz + l / 9 - 1;
+        if (x >= 0 && y >= 0 && z >= 0 && x < S.cbx && y < S.cby && z < S.cbz) {
+            const int b = (z * S.cby + y) * S.cbx + x;
+            nb = D.bact[b];
+            key = D.bkey[b];
+            if (STAMP) ch = D.bdirty[b] == D.ctr[0];
+        }
+    }
+    changed = STAMP && __any(nb >= 0 && ch);
+    const uint32_t own = __builtin_amdgcn_readlane(key, 13);
+    return own != TL_CC_MIXED && !changed && __all(nb < 0 || key == own);
+}
+
+#define TL_ONE_PLACES (TL_WG + 1) // a wave's 64 (cell, corner) sums for 8 classes, and a zero
+
+// Where node bn finds its sum of class w = (px, py, pz): of the two cells that touch it
+// along an axis one has parity p; place = wave p bits << 6 | lane bits of the cell's i
+// and the corner's j (lane layout of Lane).  Classes without a cell of the brick there
+// read the zero at place TL_WG.
+struct NodePlaces {
+    int x[2], y[2], z[2];
+    DEV void set(int bn)
+    {
+        const int X = bn % 5, Y = (bn / 5) % 5, Z = bn / 25;
+#pragma unroll
+        for (int p = 0; p < 2; p++) {
+            const int cx = (X ^ p) & 1, cy = (Y ^ p) & 1, cz = (Z ^ p) & 1; // corner bits
+            const int ax = X - cx, ay = Y - cy, az = Z - cz;                // cells
+            x[p] = (ax < 0 || ax > 3) ? TL_WG : ((ax >> 1) << 2) | cx | (p << 6);
+            y[p] = (ay < 0 || ay > 3) ? TL_WG : ((ay >> 1) << 3) | (cy << 1) | (p << 7);
+            z[p] = (az < 0 || az > 3) ? TL_WG : ((az >> 1) << 5) | (cz << 4) | (p << 8);
+        }
+    }
+    DEV int operator()(int w) const
+    {
+        const int s = x[w & 1] + y[(w >> 1) & 1] + z[w >> 2];
+        return s < TL_WG ? s : TL_WG;
+    }
+};
+
+// Rounds of 8 particles per cell that the cells of this wave need; the largest of the
+// block's waves (after the barrier that follows put) is the brick's.
+DEV void put_rounds(const Lane& L, int* s_rw)
+{
+    int r = 0;
+    while (__any(L.count > 8 * r)) r++;
+    if (L.lane == 0) s_rw[L.w] = r;
+}
+
+DEV int get_rounds(const int* s_rw)
+{
+    int r = s_rw[0];
+#pragma unroll
+    for (int w = 1; w < 8; w++) r = max(r, s_rw[w]);
+    return r;
+}
+
+// P2G of a one-code brick.  s_v: the box's remapped velocities (float4 per node); s_part:
+// TL_ONE_PLACES places of 8 floats.
+template <int MAT, bool SPLIT>
+DEV void p2g_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int nb, KA_Args A, bool fp, float* s_v,
+                 float* s_part, int* s_rw)
+{
+    const int tid = threadIdx.x, bn = tid >> 2, u = tid & 3;
+    const long long N = S.N;
+    const float dt = S.dt;
+    Contrib con;
+    con.set(S, nb, bn, u);
+    Gather<4> G;
+    if (fp) G.load(D.rs, con, 0, true);
+    Lane L = lane_at(tid);
+    lane_cell(D, info.x, L);
+    const bool rig = A.do_p2g && (S.floor_on || D.tinfo[1]) && D.brig[info.x] != 0;
+    int p = L.beg;
+    bool valid = lane_particle(D, bi, false, L, 0, p);
+    float t[3] = {0.0f, 0.0f, 0.0f}, H[9];
+    uint32_t code = 0;
+    auto load_particle = [&]() {
+        const float Xp[3] = {D.X[at3(p, 0)], D.X[at3(p, 1)], D.X[at3(p, 2)]};
+        code = D.code[p];
+#pragma unroll
+        for (int a = 0; a < 9; a++) H[a] = D.H[at9(N, p, a)];
+        frac_of(S, Xp, info.y * TL_B + L.cxl, info.z * TL_B + L.cyl, info.w * TL_B + L.czl, t);
+    };
+    if (valid) load_particle();
+    put_rounds(L, s_rw);
+    if (tid < 8) s_part[TL_WG * 8 + tid] = 0.0f;
+    if (fp) { // node velocities v~ = p~ / m (Eq. 8 with one slot: no exchange)
+        float acc[4];
+        G.sum(acc);
+        const float im = acc[0] > 0.0f ? 1.0f / acc[0] : 0.0f;
+        const float pu = u == 0 ? acc[1] : u == 1 ? acc[2] : acc[3];
+        if (bn < TL_BOXN) s_v[tid] = pu * im;
+    }
+    lds_barrier();
+    const int rounds = get_rounds(s_rw);
+    float sum[2] = {0.0f, 0.0f};
+    for (int r = 0; r < rounds; r++) {
+        const int tl = late(tid);
+        L = lane_at(tl);
+        if (r > 0) {
+            lane_cell(D, info.x, L);
+            valid = lane_particle(D, bi, false, L, r, p);
+            if (valid) load_particle();
+        }
+        if (!valid) t[0] = t[1] = t[2] = 0.0f;
+        float Lg[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}; // dF/dt of the update
+        float Gp[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+        const float4* vb = (const float4*)s_v + box_index(L.cxl, L.cyl, L.czl);
+        if (valid) {
+            if (fp) {
+#pragma unroll
+                for (int k = 0; k < 8; k++) {
+                    float wx, wy, wz;
+                    corner_weights(t, k, wx, wy, wz);
+                    const bool on = wx * wy * wz != 0.0f; // reading R7
+                    const float4 v4 = vb[(k & 1) + 5 * ((k >> 1) & 1) + 25 * (k >> 2)];
+                    float g0 = ((k & 1) ? S.inv_dx : -S.inv_dx) * wy * wz;
+                    float g1 = ((k & 2) ? S.inv_dx : -S.inv_dx) * wx * wz;
+                    float g2 = ((k & 4) ? S.inv_dx : -S.inv_dx) * wx * wy;
+                    if (!on) g0 = g1 = g2 = 0.0f;
+                    const float va[3] = {v4.x, v4.y, v4.z};
+#pragma unroll
+                    for (int a = 0; a < 3; a++) {
+                        Lg[3 * a + 0] += va[a] * g0;
+                        Lg[3 * a + 1] += va[a] * g1;
+                        Lg[3 * a + 2] += va[a] * g2;
+                    }
+                }
+                store_F(D, N, p, dt, Lg, H, code);
+            }
+            plastic_rate<MAT>(S, D, N, p, fp, H, Lg, Gp);
+        }
+        if (!A.do_p2g) continue;
+        Scatter C;
+        scatter_setup<MAT>(S, D, N, p, valid, rig, code, H, Lg, Gp, t, C);
+        float dp[3], mp[4];
+        reduce_scatter8<3, false>([&](int k, float* o) { C.dp(k, o); }, dp, L.j);
+        reduce_scatter8<4, false>([&](int k, float* o) { C.mp(k, o); }, mp, L.j);
+        if (r > 0) lds_barrier(); // the places of the last round have been read
+        float4* pl = (float4*)(s_part + tl * 8);
+        pl[0] = make_float4(mp[0], mp[1], mp[2], mp[3]);
+        pl[1] = make_float4(dp[0], dp[1], dp[2], 0.0f);
+        lds_barrier();
+        NodePlaces np;
+        np.set(late(tid) >> 2);
+        if (bn < TL_BOXN)
+#pragma unroll
+            for (int w = 0; w < 8; w++) {
+                const float2 c = *(const float2*)(s_part + np(w) * 8 + 2 * u);
+                sum[0] += c.x;
+                sum[1] += c.y;
+            }
+    }
+    if (!A.do_p2g) return;
+    if (SPLIT && tid == 0) D.xp2g[bi] = 0;
+    if (bn < TL_BOXN) *(float2*)(D.p2g + (size_t)bi * (unsigned)(S.scap * TL_BOXN * 8) + 2 * tid) = make_float2(sum[0], sum[1]);
+}
+
+// ------------------------------------------------- rounds of bricks with several codes
+#define TL_NO_SLOT 0xFFFFu
+
+// The slots of the 8 corners of a lane's cell, from the wave's places of s_slot (the
+// lane of corner j found the slot of its own corner): corner k at bits 16 (k & 3) of
+// word k >> 2.
+struct CellSlots {
+    unsigned long long w[2];
+    DEV void read(const uint16_t* s_slot, int tid)
+    {
+        const int b = tid & ~0x13; // j = 0 of the lane's cell
+        w[0] = *(const unsigned long long*)(s_slot + b);
+        w[1] = *(const unsigned long long*)(s_slot + b + 16);
+    }
+    DEV int operator()(int k) const { return (int)((w[k >> 2] >> (16 * (k & 3))) & 0xFFFFu); }
+};
+
+// Every 8-lane group of a round holds particles of one code (bricks with a mixed cell are
+// processed in same-code groups): lane j looks the slot of corner j of its cell up, once
+// for the whole group, and writes it to its place.  A group without particles, or a
+// failed lookup, has none.  The launches of a mid-size scene last as long as these bricks
+// do: 183k particles on a cut, P2G 29.2 -> 24.0 us, G2P 26.5 -> 21.4 us.
+DEV void find_corner_slot(const SceneD& D, const BoxTab& T, const Lane& L, int tid, bool valid, uint32_t key,
+                          uint16_t* s_slot)
+{
+    const int leader = L.lane & ~0x13; // j = 0 of the lane's cell
+    const uint32_t lkey = __shfl(key, leader, 64);
+    const bool gvalid = __shfl((int)valid, leader, 64) != 0;
+    if (__any(valid && key != lkey) && L.lane == 0) atomicOr(D.status, TL_ST_LOOKUP);
+    int sl = TL_NO_SLOT;
+    if (gvalid) {
+        const int bn = box_index(L.cxl + (L.j & 1), L.cyl + ((L.j >> 1) & 1), L.czl + ((L.j >> 2) & 1));
+        const int f = find_slot(T, bn, lkey);
+        if (f < 0)
+            atomicOr(D.status, TL_ST_LOOKUP);
+        else
+            sl = f;
+    }
+    s_slot[tid] = (uint16_t)sl;
+}
+
+// Adds a round's places to the sums of the slots of a node's owner lane (components C u
+// .. C u + C - 1): per slot the 8 classes in order after the sums of the rounds before.
+// Sums of earlier rounds wait in s_acc (Q components per slot); the last round's go to
+// the brick's partial [slot][box node][4 C].
+template <int C, int Q>
+DEV void add_places(const NodePlaces& np, int meta, int bn, int u, const float* s_part, const uint16_t* s_slot,
+                    float* s_acc, bool first, bool last, float* __restrict__ part)
+{
+    float v[8][C];
+    int sl[8];
+#pragma unroll
+    for (int w = 0; w < 8; w++) {
+        const int at = np(w);
+        sl[w] = s_slot[at];
+#pragma unroll
+        for (int q = 0; q < C; q++) v[w][q] = s_part[at * 4 * C + C * u + q];
+    }
+    const int c = tab_count(meta), b0 = tab_base(meta);
+    for (int s = 0; s < c; s++) {
+        float sum[C];
+        float* wait = s_acc + (b0 + s) * Q + C * u;
+#pragma unroll
+        for (int q = 0; q < C; q++) sum[q] = (first || C * u + q >= Q) ? 0.0f : wait[q];
+#pragma unroll
+        for (int w = 0; w < 8; w++)
+#pragma unroll
+            for (int q = 0; q < C; q++) sum[q] += sl[w] == b0 + s ? v[w][q] : 0.0f;
+        if (last) {
+            float* out = part + ((size_t)s * TL_BOXN + bn) * 4 * C + C * u;
+#pragma unroll
+            for (int q = 0; q < C; q++) out[q] = sum[q];
+        } else {
+#pragma unroll
+            for (int q = 0; q < C; q++)
+                if (C * u + q < Q) wait[q] = sum[q];
         }
     }
 }
@@ -684,281 +1087,210 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
 {
     __shared__ BoxTab Tc;
     __shared__ BoxTab Tr;
-    __shared__ float s_vt[TL_BOX_SLOTS * 3];
-    __shared__ float s_rsum[TL_BOX_SLOTS * 4];
-    __shared__ float s_acc[TL_BOX_SLOTS * 7];
-    __shared__ int s_total_r, s_total_c;
-    __shared__ int s_nb[27];
-    __shared__ int s_rounds;
+    __shared__ __align__(16) float s_vt[(TL_BOX_SLOTS + 1) * 4];  // v~ of the slots, and a zero
+    __shared__ __align__(16) float s_part[TL_ONE_PLACES * 8];      // first the node sums of the re-scatter
+    __shared__ __align__(16) float s_acc[TL_BOX_SLOTS * 7];
+    __shared__ __align__(8) uint16_t s_cs[TL_ONE_PLACES + 7], s_cr[TL_ONE_PLACES + 7];
+    __shared__ int s_rw[8];
+    float* const s_rsum = s_part;
+    static_assert(TL_ONE_PLACES * 8 >= TL_BOX_SLOTS * 4, "node sums in the places");
 
     const int nround = SPLIT ? D.bround[bi] : 0; // rounds of a brick with a mixed cell, else 0
     if (SPLIT && part == 1 && nround <= 1) return;
-    const int brick = D.active[bi];
+    const int4 info = D.binfo[bi];
+    const int brick = info.x, bx = info.y, by = info.z, bz = info.w;
+    const bool fp = D.ctr[1] != 0; // F update of the last substep pending
+    int nbv;
+    bool changed;
+    if (one_code<true>(S, D, bx, by, bz, nbv, changed)) {
+        p2g_one<MAT, SPLIT>(S, D, bi, info, nbv, A, fp, s_vt, s_part, s_rw);
+        return;
+    }
     const bool grouped = D.bmixed[brick] != 0; // a cell holds two codes: same-code groups
     // (all mixed bricks split, or none: the decision does not depend on list order)
     const bool split = SPLIT && grouped && nround > 1 && S.xcap > 0 && D.ctr[3] <= S.xcap;
     const int r0 = part; // first round of this workgroup
-    const int bx = brick % S.cbx, by = (brick / S.cbx) % S.cby, bz = brick / (S.cbx * S.cby);
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, bn = tid >> 2, u = tid & 3;
     const long long N = S.N;
     const float dt = S.dt;
-    const bool fp = D.ctr[1] != 0;                              // F update of the last substep pending
-    const bool use_r = fp;                                            // finalize v~ (tables rs)
-    const bool use_c = A.do_p2g && ((A.tabs_differ && fp) || !fp); // separate P2G tables
+    const bool use_r = fp; // finalize v~ (tables rs)
+    // separate P2G tables, where a label pass changed the codes around (the two buffers
+    // agree elsewhere)
+    const bool use_c = A.do_p2g && ((A.tabs_differ && fp && changed) || !fp);
     const bool xg_rs = SPLIT && D.xg[0] != 0; // the last G2P split bricks: their second re-scatter sums
 
-    // ---- phase 1: cell index, box counts, brick-vs-tool tests, round-0 particle loads
-    Lane L = lane_of(D, brick);
-    if (use_r) box_counts(S, D.cnt[A.rsb], bx, by, bz, Tr);
-    if (use_r) load_neighbours(S, D, bx, by, bz, s_nb);
-    if (use_c) box_counts(S, D.cnt[A.cur], bx, by, bz, Tc);
-    if (tid == 0) s_rounds = 0;
+    // ---- phase 1: counts, cell index, codes and partials of the own node, particle loads
+    BoxCounts nr, nc;
+    if (use_r) nr.load(S, D.cnt[A.rsb], bx, by, bz);
+    if (use_c) nc.load(S, D.cnt[A.cur], bx, by, bz);
+    Lane L = lane_at(tid);
+    lane_cell(D, brick, L);
     // floor/tool impulses were computed for this brick by k_rigid
     const bool rig = A.do_p2g && (S.floor_on || D.tinfo[1]) && D.brig[brick] != 0;
-    const int gxc = bx * TL_B + L.cxl, gyc = by * TL_B + L.cyl, gzc = bz * TL_B + L.czl;
-    long long p = L.beg;
+    int p = L.beg;
     bool valid = lane_particle(D, bi, grouped, L, r0, p);
-    float Xp[3] = {0.0f, 0.0f, 0.0f}, H[9], vel[3] = {0.0f, 0.0f, 0.0f};
+    float t[3] = {0.0f, 0.0f, 0.0f}, H[9];
     uint32_t code = 0;
     auto load_particle = [&]() {
-        Xp[0] = D.X[p];
-        Xp[1] = D.X[N + p];
-        Xp[2] = D.X[2 * N + p];
+        const float Xp[3] = {D.X[at3(p, 0)], D.X[at3(p, 1)], D.X[at3(p, 2)]};
         code = D.code[p];
 #pragma unroll
-        for (int a = 0; a < 9; a++) H[a] = D.H[a * N + p];
-        if (A.do_p2g)
-            for (int a = 0; a < 3; a++) vel[a] = D.v[a * N + p];
+        for (int a = 0; a < 9; a++) H[a] = D.H[at9(N, p, a)];
+        frac_of(S, Xp, info.y * TL_B + L.cxl, info.z * TL_B + L.cyl, info.w * TL_B + L.czl, t);
     };
-    if (valid) load_particle();
-    lds_barrier();
-    if (grouped) {
-        if (tid == 0) s_rounds = D.bround[bi];
-    } else if (L.j == 0) {
-        atomicMax(&s_rounds, (L.count + 7) >> 3);
-    }
-    if (use_r) box_scan(Tr, &s_total_r, 0);
-    if (use_c) box_scan(Tc, &s_total_c, 1);
-    lds_barrier();
-    const int total_r = use_r ? s_total_r : 0;
-    const int total_c = use_c ? s_total_c : total_r;
+    int mr = 0, mc = 0;
+    const int total_r = use_r ? nr.scan(Tr, bn, mr) : 0;
+    const int total_c = use_c ? nc.scan(Tc, bn, mc) : total_r;
     if (total_r > TL_BOX_SLOTS || total_c > TL_BOX_SLOTS) {
         if (tid == 0) atomicOr(D.status, TL_ST_BOX);
         return;
     }
-    // ---- phase 3: per box node: codes, re-scatter sums, coupling, v~ (Eq. 8, MUSL)
-    // (4 threads per node: the quad of lanes 4 bn .. 4 bn + 3)
-    if ((tid >> 2) < TL_BOXN) {
-        const int bn = tid >> 2, u = tid & 3;
-        uint32_t pre_r[2], pre_c[2];
-        if (u == 0 && use_r) codes_pre(S, D.scode[A.rsb], Tr, bn, pre_r);
-        if (u == 0 && use_c) codes_pre(S, D.scode[A.cur], Tc, bn, pre_c);
-        if (use_r) {
-            const int c = Tr.cnt[bn], b0 = Tr.base[bn];
-            if (c > 0) gather_node4<4>(S, s_nb, D.rs, D.rs_x, xg_rs ? D.xrs : nullptr, Tr, bn, u, s_rsum);
-            if (u == 0) codes_put(S, D.scode[A.rsb], Tr, bn, pre_r);
-            if (u == 0 && c > 0) {
-                couple_node<4>(Tr, b0, c, s_rsum, 1, s_vt);
-                for (int a = 0; a < c; a++) {
-                    float m = s_rsum[(b0 + a) * 4];
-                    float im = m > 0.0f ? 1.0f / m : 0.0f;
-                    for (int jj = 0; jj < 3; jj++) s_vt[(b0 + a) * 3 + jj] *= im;
-                }
+    if (bn >= TL_BOXN) mr = mc = 0;
+    const long long gid = bn < TL_BOXN ? box_gid(S, bx, by, bz, bn % 5, (bn / 5) % 5, bn / 25) : -1;
+    Contrib C;
+    C.set(S, nbv, bn, u);
+    const int cr = tab_count(mr), br = tab_base(mr);
+    Gather<4> g0, g1;
+    uint32_t pre_r = 0, pre_c = 0;
+    if (use_r) {
+        pre_r = codes_pre(S, D.scode[A.rsb], mr, gid, u);
+        g0.load(D.rs, C, 0, cr > 0);
+        g1.load(D.rs, C, 1, cr > 1);
+    }
+    if (use_c) pre_c = codes_pre(S, D.scode[A.cur], mc, gid, u);
+    if (valid) load_particle();
+    put_rounds(L, s_rw);
+    if (tid < 8) s_part[TL_WG * 8 + tid] = 0.0f;
+    if (tid < 4) s_vt[TL_BOX_SLOTS * 4 + tid] = 0.0f;
+    if (tid == 0) s_cs[TL_WG] = TL_NO_SLOT;
+    // ---- phase 2: re-scatter sums of the own node, coupling, v~ (Eq. 8, MUSL)
+    if (use_r) {
+        codes_put(S, D.scode[A.rsb], Tr, mr, gid, u, pre_r);
+        for (int s = 0; s < cr; s += 2) {
+            if (s > 0) {
+                g0.load(D.rs, C, s, true);
+                g1.load(D.rs, C, s + 1, s + 1 < cr);
+            }
+            if (xg_rs) {
+                g0.add(D.rs_x, D.xrs, C, s);
+                if (s + 1 < cr) g1.add(D.rs_x, D.xrs, C, s + 1);
+            }
+            float a0[4], a1[4];
+            g0.sum(a0);
+            g1.sum(a1);
+            if (cr == 1) { // one slot: no exchange
+                const float im = a0[0] > 0.0f ? 1.0f / a0[0] : 0.0f;
+                s_vt[br * 4 + u] = (u == 0 ? a0[1] : u == 1 ? a0[2] : a0[3]) * im;
+            } else {
+                s_rsum[(br + s) * 4 + u] = u == 0 ? a0[0] : u == 1 ? a0[1] : u == 2 ? a0[2] : a0[3];
+                if (s + 1 < cr) s_rsum[(br + s + 1) * 4 + u] = u == 0 ? a1[0] : u == 1 ? a1[1] : u == 2 ? a1[2] : a1[3];
             }
         }
-        if (u == 0 && use_c) codes_put(S, D.scode[A.cur], Tc, bn, pre_c);
+        wave_lds_fence();
+        if (cr > 1 && u < 3)
+            couple_component<4>(Tr, br, cr, s_rsum, 1 + u, [&](int sl, float m, float f) {
+                const float im = m > 0.0f ? 1.0f / m : 0.0f;
+                s_vt[sl * 4 + u] = f * im;
+            });
     }
-    if (A.do_p2g)
-        for (int q = tid; q < total_c * 7; q += TL_WG) s_acc[q] = 0.0f;
+    if (use_c) codes_put(S, D.scode[A.cur], Tc, mc, gid, u, pre_c);
     lds_barrier();
     const BoxTab& T = use_c ? Tc : Tr;
-    const int rounds = (split && part == 0) ? 1 : s_rounds;
+    const int mt = use_c ? mc : mr;
+    const int rounds = (split && part == 0) ? 1 : grouped ? D.bround[bi] : get_rounds(s_rw);
+    const float4* const vt = (const float4*)s_vt;
 
     for (int r = r0; r < rounds; r++) {
+        const int tl = late(tid);
+        L = lane_at(tl);
         if (r > r0) {
+            lane_cell(D, brick, L);
             valid = lane_particle(D, bi, grouped, L, r, p);
             if (valid) load_particle();
         }
-        float t[3] = {0.0f, 0.0f, 0.0f};
-        uint32_t key = 0;
-        if (valid) {
-            frac_of(S, Xp, gxc, gyc, gzc, t);
-            key = slot_key(S, code);
-        }
+        if (!valid) t[0] = t[1] = t[2] = 0.0f;
+        const uint32_t key = valid ? slot_key(S, code) : 0u;
+        if (r > r0) lds_barrier(); // the places of the last round have been read
+        if (A.do_p2g) find_corner_slot(D, T, L, tl, valid, key, s_cs);
         // ---- deformation-gradient update from the remapped velocities (MUSL)
         float Lg[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}; // dF/dt of the update
-        if (use_r && valid) {
-            uint32_t kprev = (code & TL_PREV_BIT) ? slot_key(S, D.code_prev[p]) : key;
-            for (int k = 0; k < 8; k++) {
-                float wx, wy, wz;
-                corner_weights(t, k, wx, wy, wz);
-                if (wx * wy * wz == 0.0f) continue;
-                int bn = box_index(L.cxl + (k & 1), L.cyl + ((k >> 1) & 1), L.czl + ((k >> 2) & 1));
-                int sl = find_slot(Tr, bn, kprev);
-                if (sl < 0) {
-                    atomicOr(D.status, TL_ST_LOOKUP);
-                    continue;
-                }
-                float g0 = ((k & 1) ? S.inv_dx : -S.inv_dx) * wy * wz;
-                float g1 = ((k & 2) ? S.inv_dx : -S.inv_dx) * wx * wz;
-                float g2 = ((k & 4) ? S.inv_dx : -S.inv_dx) * wx * wy;
-                for (int a = 0; a < 3; a++) {
-                    float va = s_vt[sl * 3 + a];
-                    Lg[3 * a + 0] += va * g0;
-                    Lg[3 * a + 1] += va * g1;
-                    Lg[3 * a + 2] += va * g2;
-                }
-            }
-            bool fin = true;
-            for (int a = 0; a < 9; a++) {
-                H[a] += dt * Lg[a];
-                D.H[a * N + p] = H[a];
-                fin = fin && isfinite(H[a]);
-            }
-            if (!fin) atomicOr(D.status, TL_ST_NONFINITE);
-            if (code & TL_PREV_BIT) {
-                code &= ~TL_PREV_BIT;
-                D.code[p] = code;
-            }
-        }
-        // plasticity: F_p^{-1} = I + Gp; projection after each F update
         float Gp[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        if constexpr (MAT == 1) {
-            if (S.ystress > 0.0f && valid) {
-#pragma unroll
-                for (int a = 0; a < 9; a++) Gp[a] = D.Gp[a * N + p];
-                if (use_r) {
-                    float K[9]; // F_e - I = H + Gp + H Gp
-#pragma unroll
-                    for (int i = 0; i < 3; i++)
-#pragma unroll
-                        for (int j = 0; j < 3; j++) {
-                            float k = H[3 * i + j] + Gp[3 * i + j];
-#pragma unroll
-                            for (int m = 0; m < 3; m++) k += H[3 * i + m] * Gp[3 * m + j];
-                            K[3 * i + j] = k;
+        if (use_r) {
+            // particles labelled in this substep's pass use their previous code; their
+            // wave looks every corner up by itself
+            const bool fresh = __any(valid && (code & TL_PREV_BIT) != 0u);
+            const bool same = !use_c && A.do_p2g;
+            if (!fresh && !same) find_corner_slot(D, Tr, L, tl, valid, key, s_cr);
+            wave_lds_fence();
+            CellSlots cs;
+            cs.read(same ? s_cs : s_cr, tl);
+            if (fresh && valid) {
+                const uint32_t kprev = (code & TL_PREV_BIT) ? slot_key(S, D.code_prev[p]) : key;
+                auto half = [&](int h) {
+                    unsigned long long x = 0;
+#pragma unroll 1
+                    for (int k = 4 * h + 3; k >= 4 * h; k--) {
+                        float wx, wy, wz;
+                        corner_weights(t, k, wx, wy, wz);
+                        int sl = TL_NO_SLOT;
+                        if (wx * wy * wz != 0.0f) {
+                            const int f = find_slot(
+                                Tr, box_index(L.cxl + (k & 1), L.cyl + ((k >> 1) & 1), L.czl + (k >> 2)), kprev);
+                            if (f < 0)
+                                atomicOr(D.status, TL_ST_LOOKUP);
+                            else
+                                sl = f;
                         }
-                    const float Ey = S.e_uniform ? S.E0 : D.E[p];
-                    if (vm_project(Ey, S.nu, S.ystress, K, Gp))
+                        x = (x << 16) | (unsigned)sl;
+                    }
+                    return x;
+                };
+                cs.w[0] = half(0);
+                cs.w[1] = half(1);
+            }
+            if (valid) {
 #pragma unroll
-                        for (int a = 0; a < 9; a++) D.Gp[a * N + p] = Gp[a];
+                for (int k = 0; k < 8; k++) {
+                    float wx, wy, wz;
+                    corner_weights(t, k, wx, wy, wz);
+                    const bool on = wx * wy * wz != 0.0f; // reading R7
+                    const int sl = cs(k);
+                    const float4 v4 = vt[sl < TL_BOX_SLOTS ? sl : TL_BOX_SLOTS];
+                    float h0 = ((k & 1) ? S.inv_dx : -S.inv_dx) * wy * wz;
+                    float h1 = ((k & 2) ? S.inv_dx : -S.inv_dx) * wx * wz;
+                    float h2 = ((k & 4) ? S.inv_dx : -S.inv_dx) * wx * wy;
+                    if (!on) h0 = h1 = h2 = 0.0f;
+                    const float va[3] = {v4.x, v4.y, v4.z};
+#pragma unroll
+                    for (int a = 0; a < 3; a++) {
+                        Lg[3 * a + 0] += va[a] * h0;
+                        Lg[3 * a + 1] += va[a] * h1;
+                        Lg[3 * a + 2] += va[a] * h2;
+                    }
                 }
+                store_F(D, N, p, dt, Lg, H, code);
             }
         }
-        if constexpr (MAT == 1) {
-            // viscosity uses the rate of the last F update: kept for the substeps
-            // whose P2G has no pending update (the first, or after a state read)
-            if (S.visc > 0.0f && valid) {
-                if (use_r) {
-#pragma unroll
-                    for (int a = 0; a < 9; a++) D.Fdot[a * N + p] = Lg[a];
-                } else {
-#pragma unroll
-                    for (int a = 0; a < 9; a++) Lg[a] = D.Fdot[a * N + p];
-                }
-            }
-        }
+        if (valid) plastic_rate<MAT>(S, D, N, p, use_r, H, Lg, Gp);
         if (!A.do_p2g) continue;
-        // ---- stress and external/contact impulses
-        float m = 0.0f, V0 = 0.0f, E = 0.0f;
-        float Pk[9];
-        float Jc[3] = {0.0f, 0.0f, 0.0f};
-        if (valid) {
-            m = S.m_uniform ? S.m0 : D.m[p];
-            V0 = S.v_uniform ? S.V0 : D.V0[p];
-            E = S.e_uniform ? S.E0 : D.E[p];
-            bool ok;
-            if constexpr (MAT == 1) {
-                if (S.ystress > 0.0f) {
-                    // P = P_fcr(F_e) F_p^{-T}, F_e - I = H + Gp + H Gp, F_p^{-1} = I + Gp
-                    float K[9], Pe[9];
-#pragma unroll
-                    for (int i = 0; i < 3; i++)
-#pragma unroll
-                        for (int j = 0; j < 3; j++) {
-                            float k = H[3 * i + j] + Gp[3 * i + j];
-#pragma unroll
-                            for (int m = 0; m < 3; m++) k += H[3 * i + m] * Gp[3 * m + j];
-                            K[3 * i + j] = k;
-                        }
-                    ok = fixed_corotated(E, S.nu, K, Pe);
-#pragma unroll
-                    for (int i = 0; i < 3; i++)
-#pragma unroll
-                        for (int j = 0; j < 3; j++) {
-                            float a = Pe[3 * i + j];
-#pragma unroll
-                            for (int m = 0; m < 3; m++) a += Pe[3 * i + m] * Gp[3 * j + m];
-                            Pk[3 * i + j] = a;
-                        }
-                } else {
-                    ok = S.material == 1 ? fixed_corotated(E, S.nu, H, Pk) : neo_hookean(E, S.nu, H, Pk);
-                }
-            } else {
-                ok = neo_hookean(E, S.nu, H, Pk);
-            }
-            if (ok && MAT == 1 && S.visc > 0.0f) add_viscous(S.visc, H, Lg, Pk);
-            if (!ok) {
-                atomicOr(D.status, TL_ST_NONFINITE);
-                for (int a = 0; a < 9; a++) Pk[a] = 0.0f;
-            }
-        } else {
-            for (int a = 0; a < 9; a++) Pk[a] = 0.0f;
-        }
-        float ext[3] = {0.0f, 0.0f, 0.0f};
-        if (valid) {
-            if (rig) { // floor and tool impulses of this substep (k_rigid)
-                Jc[0] += D.Jrig[p];
-                Jc[1] += D.Jrig[N + p];
-                Jc[2] += D.Jrig[2 * N + p];
-            }
-            if (S.material_contact && (code & TL_CAND_BIT)) {
-                Jc[0] += D.Jmat[p];
-                Jc[1] += D.Jmat[N + p];
-                Jc[2] += D.Jmat[2 * N + p];
-            }
-            ext[0] = Jc[0] + dt * m * S.gx;
-            ext[1] = Jc[1] + dt * m * S.gy;
-            ext[2] = Jc[2] + dt * m * S.gz;
-        }
-        // A = -dt V0 P;  dp_k = A grad N_k + w_k ext  (Eq. 2); a zero weight contributes
-        // nothing (reading R7)
-        const float sA = -dt * V0;
-#pragma unroll
-        for (int a = 0; a < 9; a++) Pk[a] *= sA;
-        const float mm = valid ? m : 0.0f;
-        // absolute corners (the CornerW order needs more registers here than the
-        // selects it saves: the impulse generator also needs per-lane gradient signs)
-        auto gen_mp = [&](int k, float* o) { // mass and momentum
-            float wx, wy, wz;
-            corner_weights(t, k, wx, wy, wz);
-            float wm = wx * wy * wz * mm;
-            o[0] = wm;
-            o[1] = wm * vel[0];
-            o[2] = wm * vel[1];
-            o[3] = wm * vel[2];
-        };
-        auto gen_dp = [&](int k, float* o) { // internal, external and contact impulse
-            float wx, wy, wz;
-            corner_weights(t, k, wx, wy, wz);
-            float w = wx * wy * wz;
-            float g0 = ((k & 1) ? S.inv_dx : -S.inv_dx) * wy * wz;
-            float g1 = ((k & 2) ? S.inv_dx : -S.inv_dx) * wx * wz;
-            float g2 = ((k & 4) ? S.inv_dx : -S.inv_dx) * wx * wy;
-            bool on = valid && w != 0.0f;
-#pragma unroll
-            for (int a = 0; a < 3; a++) {
-                float f = Pk[3 * a] * g0 + Pk[3 * a + 1] * g1 + Pk[3 * a + 2] * g2 + w * ext[a];
-                o[a] = on ? f : 0.0f;
-            }
-        };
-        // impulses first: their butterfly then runs while fewer values are live;
-        // stored as (m, m v, dp) like the other order
-        accumulate_classes<3, 4, false, 4>(L, valid, key, gen_dp, gen_mp, T, s_acc, D.status);
+        Scatter W;
+        scatter_setup<MAT>(S, D, N, p, valid, rig, code, H, Lg, Gp, t, W);
+        // impulses first: their butterfly then runs while fewer values are live
+        float dp[3], mp[4];
+        reduce_scatter8<3, false>([&](int k, float* o) { W.dp(k, o); }, dp, L.j);
+        reduce_scatter8<4, false>([&](int k, float* o) { W.mp(k, o); }, mp, L.j);
+        float4* pl = (float4*)(s_part + tl * 8);
+        pl[0] = make_float4(mp[0], mp[1], mp[2], mp[3]);
+        pl[1] = make_float4(dp[0], dp[1], dp[2], 0.0f);
+        lds_barrier();
+        NodePlaces np;
+        np.set(late(tid) >> 2);
+        if (bn < TL_BOXN)
+            add_places<2, 7>(np, mt, bn, u, s_part, s_cs, s_acc, r == r0, r + 1 == rounds,
+                          (part ? D.p2g_x : D.p2g) + (size_t)bi * (unsigned)(S.scap * TL_BOXN * 8));
     }
     if (!A.do_p2g) return;
     if (SPLIT && part == 0 && tid == 0) D.xp2g[bi] = split ? 1 : 0;
-    write_partials<7>(S, part ? D.p2g_x : D.p2g, bi, T, total_c, s_acc);
 }
 
 // --------------------------------------------------------------------------- K_B
@@ -966,171 +1298,33 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
 // P2G partials (sum over contributing bricks, coupling Eq. 8, velocities Eq. 9),
 // PIC/FLIP G2P of v and x (Eq. 17), then the MUSL re-scatter of m_p v_p^{n+1} into
 // this brick's partials.  Also records the brick's current AABB and speed bound.
-template <bool SPLIT>
-DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
+
+// PIC/FLIP update of the lane's particle from the interpolated increments av and ax;
+// joins x^{n+1}, the speed and |u^{n+1} - a| into bb.
+DEV void move_particle(const SceneK& S, const SceneD& D, long long N, long long p, const float* Xp, const float* v,
+                       const float* u, const float* av, const float* ax, const float* ap, float* vn1, float* bb)
 {
-    __shared__ BoxTab T;
-    __shared__ float s_sum[TL_BOX_SLOTS * 7];
-    __shared__ float s_grid[TL_BOX_SLOTS * 6];
-    __shared__ float s_acc[TL_BOX_SLOTS * 4];
-    __shared__ int s_total;
-    __shared__ int s_nb[27];
-    __shared__ int s_rounds;
-    __shared__ float s_bb[8][8];
-
-    const int nround = SPLIT ? D.bround[bi] : 0; // rounds of a brick with a mixed cell, else 0
-    if (SPLIT && part == 1 && nround <= 1) return; // (split bricks as in the P2G)
-    const int brick = D.active[bi];
-    if (bi == 0 && part == 0 && threadIdx.x == 0) {
-        // end of the substep for this scene: next history stamp, F update pending
-        // (no other kernel of the substep reads these after this point); whether this
-        // G2P splits its mixed bricks (read by the next P2G and box tests)
-        D.ctr[0] += 1;
-        D.ctr[1] = 1;
-        D.ctr[2] += 1;
-        if (SPLIT) D.xg[0] = (S.xcap > 0 && D.ctr[3] > 0 && D.ctr[3] <= S.xcap) ? 1 : 0;
-    }
-    const bool grouped = D.bmixed[brick] != 0; // a cell holds two codes: same-code groups
-    // this substep's P2G split its mixed bricks (a scene without split workgroups never)
-    const bool xsplit = SPLIT && S.xcap > 0 && D.ctr[3] > 0 && D.ctr[3] <= S.xcap;
-    const bool split = grouped && nround > 1 && xsplit;
-    const int r0 = part;
-    const int bx = brick % S.cbx, by = (brick / S.cbx) % S.cby, bz = brick / (S.cbx * S.cby);
-    const int tid = threadIdx.x;
-    const long long N = S.N;
     const float dt = S.dt, beta = S.beta;
-    // displacement anchor of this workgroup's particles (pair-search skip), kept for
-    // bricks with contact candidates (only candidates can be partners): the centre of
-    // the brick's box after the last G2P minus the centre of its particles' reference
-    // box.  A split brick's second workgroup reads the first one's record, which that
-    // one may rewrite in this launch; either value is a valid anchor, since the spread
-    // is measured against the anchor taken.
-    const bool track = S.pair_skip && D.bcand[bi] > 0;
-    float ap[3] = {0.0f, 0.0f, 0.0f};
-    if (track) g2p_anchor(D, D.aabb + (long long)brick * 8, brick, ap);
+    for (int a = 0; a < 3; a++) {
+        vn1[a] = beta * v[a] + av[a];
+        float un = u[a] + dt * ax[a];
+        D.v[at3(p, a)] = vn1[a];
+        D.u[at3(p, a)] = un;
+        float xa = Xp[a] + un;
+        bb[a] = fminf(bb[a], xa);
+        bb[3 + a] = fmaxf(bb[3 + a], xa);
+        bb[7] = fmaxf(bb[7], fabsf(un - ap[a]));
+    }
+    bb[6] = fmaxf(bb[6], sqrtf(vn1[0] * vn1[0] + vn1[1] * vn1[1] + vn1[2] * vn1[2]));
+}
 
-    // ---- phase 1: cell index, box counts, round-0 particle loads
-    Lane L = lane_of(D, brick);
-    box_counts(S, D.cnt[cur], bx, by, bz, T);
-    load_neighbours(S, D, bx, by, bz, s_nb);
-    if (tid == 0) s_rounds = 0;
-    const int gxc = bx * TL_B + L.cxl, gyc = by * TL_B + L.cyl, gzc = bz * TL_B + L.czl;
-    long long p = L.beg;
-    bool valid = lane_particle(D, bi, grouped, L, r0, p);
-    float Xp[3] = {0.0f, 0.0f, 0.0f}, v[3] = {0.0f, 0.0f, 0.0f}, u[3] = {0.0f, 0.0f, 0.0f};
-    uint32_t code = 0;
-    auto load_particle = [&]() {
-        for (int a = 0; a < 3; a++) {
-            Xp[a] = D.X[a * N + p];
-            v[a] = D.v[a * N + p];
-            u[a] = D.u[a * N + p];
-        }
-        code = D.code[p];
-    };
-    if (valid) load_particle();
-    lds_barrier();
-    if (grouped) {
-        if (tid == 0) s_rounds = D.bround[bi];
-    } else if (L.j == 0) {
-        atomicMax(&s_rounds, (L.count + 7) >> 3);
-    }
-    box_scan(T, &s_total, 0);
-    lds_barrier();
-    const int total = s_total;
-    if (total > TL_BOX_SLOTS) {
-        if (tid == 0) atomicOr(D.status, TL_ST_BOX);
-        return;
-    }
-    // ---- phase 3: per box node: codes, P2G sums, coupling (Eq. 8), v^n and dv (Eq. 9)
-    if ((tid >> 2) < TL_BOXN) {
-        const int bn = tid >> 2, u = tid & 3;
-        uint32_t pre[2];
-        if (u == 0) codes_pre(S, D.scode[cur], T, bn, pre);
-        const int c = T.cnt[bn], b0 = T.base[bn];
-        if (c > 0) gather_node4<7>(S, s_nb, D.p2g, D.p2g_x, xsplit ? D.xp2g : nullptr, T, bn, u, s_sum);
-        if (u == 0) codes_put(S, D.scode[cur], T, bn, pre);
-        if (u == 0 && c > 0) {
-            float* gvn = s_grid;
-            float* gdv = s_grid + TL_BOX_SLOTS * 3;
-            couple_node<7>(T, b0, c, s_sum, 1, gvn);
-            couple_node<7>(T, b0, c, s_sum, 4, gdv);
-            for (int a = 0; a < c; a++) {
-                float m = s_sum[(b0 + a) * 7];
-                float im = m > 0.0f ? 1.0f / m : 0.0f;
-                for (int jj = 0; jj < 3; jj++) {
-                    gvn[(b0 + a) * 3 + jj] *= im;
-                    gdv[(b0 + a) * 3 + jj] *= im;
-                }
-            }
-        }
-    }
-    for (int q = tid; q < total * 4; q += TL_WG) s_acc[q] = 0.0f;
-    lds_barrier();
-    const int rounds = (split && part == 0) ? 1 : s_rounds;
-    // box of x^{n+1}, speed bound, and the largest |u^{n+1} - a| about the anchor a
-    // (for the pair-search skip)
-    float bb[8] = {1e30f, 1e30f, 1e30f, -1e30f, -1e30f, -1e30f, 0.0f, 0.0f};
-    const float* gv = s_grid;
-    const float* gdv = s_grid + TL_BOX_SLOTS * 3;
-    for (int r = r0; r < rounds; r++) {
-        if (r > r0) {
-            valid = lane_particle(D, bi, grouped, L, r, p);
-            if (valid) load_particle();
-        }
-        float t[3] = {0.0f, 0.0f, 0.0f};
-        uint32_t key = 0;
-        float m = 0.0f, vn1[3] = {0.0f, 0.0f, 0.0f};
-        if (valid) {
-            frac_of(S, Xp, gxc, gyc, gzc, t);
-            key = slot_key(S, code);
-            float av[3] = {0.0f, 0.0f, 0.0f}, ax[3] = {0.0f, 0.0f, 0.0f};
-            for (int k = 0; k < 8; k++) {
-                float wx, wy, wz;
-                corner_weights(t, k, wx, wy, wz);
-                float w = wx * wy * wz;
-                if (w == 0.0f) continue;
-                int bn = box_index(L.cxl + (k & 1), L.cyl + ((k >> 1) & 1), L.czl + ((k >> 2) & 1));
-                int sl = find_slot(T, bn, key);
-                if (sl < 0) {
-                    atomicOr(D.status, TL_ST_LOOKUP);
-                    continue;
-                }
-                for (int a = 0; a < 3; a++) {
-                    float vn = gv[sl * 3 + a], dv = gdv[sl * 3 + a];
-                    av[a] += w * ((1.0f - beta) * vn + dv);
-                    ax[a] += w * (vn + dv);
-                }
-            }
-            for (int a = 0; a < 3; a++) {
-                vn1[a] = beta * v[a] + av[a];
-                float un = u[a] + dt * ax[a];
-                D.v[a * N + p] = vn1[a];
-                D.u[a * N + p] = un;
-                float xa = Xp[a] + un;
-                bb[a] = fminf(bb[a], xa);
-                bb[3 + a] = fmaxf(bb[3 + a], xa);
-                bb[7] = fmaxf(bb[7], fabsf(un - ap[a]));
-            }
-            bb[6] = fmaxf(bb[6], sqrtf(vn1[0] * vn1[0] + vn1[1] * vn1[1] + vn1[2] * vn1[2]));
-            m = S.m_uniform ? S.m0 : D.m[p];
-        }
-        const float mm = valid ? m : 0.0f;
-        const CornerW cw = corner_table(t, L.j);
-        auto gen = [&](int r, float* o) {
-            const float wx = cw.wx[r & 1], wy = cw.wy[(r >> 1) & 1], wz = cw.wz[r >> 2];
-            float w = wx * wy * wz * mm;
-            o[0] = w;
-            o[1] = w * vn1[0];
-            o[2] = w * vn1[1];
-            o[3] = w * vn1[2];
-        };
-        accumulate_classes<4, 0, true>(L, valid, key, gen, gen, T, s_acc, D.status);
-    }
-    if (SPLIT && part == 0 && tid == 0) D.xrs[bi] = split ? 1 : 0;
-    write_partials<4>(S, part ? D.rs_x : D.rs, bi, T, total, s_acc);
-    // brick AABB of x^{n+1} and speed bound (used to skip distant contact work); a
-    // split brick's second workgroup keeps the box of its particles apart
-    // (brick_aabb joins the two)
+// Brick AABB of x^{n+1} and speed bound (used to skip distant contact work), from each
+// lane's bb; a split brick's second workgroup keeps the box of its particles apart
+// (brick_aabb joins the two).  With track also the displacement anchor.
+DEV void put_box(const SceneK& S, const SceneD& D, int bi, int brick, int part, bool track, const float* ap,
+                 const float* bb, float (*s_bb)[8])
+{
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
 #pragma unroll
     for (int q = 0; q < 8; q++) {
         if (q == 7 && !track) break;
@@ -1140,7 +1334,7 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
         mm(lane_xor<2>(val));
         mm(lane_xor<4>(val));
         for (int o = 8; o <= 32; o <<= 1) mm(__shfl_xor(val, o, 64));
-        if (L.lane == 0) s_bb[L.w][q] = val;
+        if (lane == 0) s_bb[w][q] = val;
     }
     lds_barrier();
     if (tid < 7) {
@@ -1158,6 +1352,313 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
     }
 }
 
+// G2P of a one-code brick.  s_g: per box node (1 - beta) v^n + dv and v^n + dv (two
+// float4); s_part: TL_ONE_PLACES places of 4 floats.
+template <bool SPLIT>
+DEV void g2p_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int nb, bool track, const float* ap,
+                 float* s_g, float* s_part, int* s_rw, float (*s_bb)[8])
+{
+    const int tid = threadIdx.x, bn = tid >> 2, u4 = tid & 3;
+    const long long N = S.N;
+    const float beta = S.beta;
+    Contrib con;
+    con.set(S, nb, bn, u4);
+    Gather<8> G;
+    G.load(D.p2g, con, 0, true);
+    Lane L = lane_at(tid);
+    lane_cell(D, info.x, L);
+    int p = L.beg;
+    bool valid = lane_particle(D, bi, false, L, 0, p);
+    float Xp[3] = {0.0f, 0.0f, 0.0f}, v[3] = {0.0f, 0.0f, 0.0f}, u[3] = {0.0f, 0.0f, 0.0f};
+    auto load_particle = [&]() {
+        for (int a = 0; a < 3; a++) {
+            Xp[a] = D.X[at3(p, a)];
+            v[a] = D.v[at3(p, a)];
+            u[a] = D.u[at3(p, a)];
+        }
+    };
+    if (valid) load_particle();
+    put_rounds(L, s_rw);
+    if (tid < 4) s_part[TL_WG * 4 + tid] = 0.0f;
+    { // node velocities and increments (Eq. 9; Eq. 8 with one slot: no exchange)
+        float acc[7];
+        G.sum(acc);
+        const float im = acc[0] > 0.0f ? 1.0f / acc[0] : 0.0f;
+        const float pu = u4 == 0 ? acc[1] : u4 == 1 ? acc[2] : acc[3];
+        const float du = u4 == 0 ? acc[4] : u4 == 1 ? acc[5] : acc[6];
+        const float vn = pu * im, dv = du * im;
+        if (bn < TL_BOXN) {
+            s_g[bn * 8 + u4] = (1.0f - beta) * vn + dv;
+            s_g[bn * 8 + 4 + u4] = vn + dv;
+        }
+    }
+    lds_barrier();
+    const int rounds = get_rounds(s_rw);
+    float sum = 0.0f;
+    // box of x^{n+1}, speed bound, and the largest |u^{n+1} - a| about the anchor a
+    // (for the pair-search skip)
+    float bb[8] = {1e30f, 1e30f, 1e30f, -1e30f, -1e30f, -1e30f, 0.0f, 0.0f};
+    for (int r = 0; r < rounds; r++) {
+        const int tl = late(tid);
+        L = lane_at(tl);
+        if (r > 0) {
+            lane_cell(D, info.x, L);
+            valid = lane_particle(D, bi, false, L, r, p);
+            if (valid) load_particle();
+        }
+        float t[3] = {0.0f, 0.0f, 0.0f};
+        float m = 0.0f, vn1[3] = {0.0f, 0.0f, 0.0f};
+        if (valid) {
+            frac_of(S, Xp, info.y * TL_B + L.cxl, info.z * TL_B + L.cyl, info.w * TL_B + L.czl, t);
+            const float4* gb = (const float4*)s_g + 2 * box_index(L.cxl, L.cyl, L.czl);
+            float av[3] = {0.0f, 0.0f, 0.0f}, ax[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < 8; k++) { // (a zero weight adds zero: node values are finite or unused)
+                float wx, wy, wz;
+                corner_weights(t, k, wx, wy, wz);
+                const float w = wx * wy * wz;
+                const int o = 2 * ((k & 1) + 5 * ((k >> 1) & 1) + 25 * (k >> 2));
+                const float4 fv = gb[o], fx = gb[o + 1];
+                av[0] += w * fv.x;
+                av[1] += w * fv.y;
+                av[2] += w * fv.z;
+                ax[0] += w * fx.x;
+                ax[1] += w * fx.y;
+                ax[2] += w * fx.z;
+            }
+            move_particle(S, D, N, p, Xp, v, u, av, ax, ap, vn1, bb);
+            m = S.m_uniform ? S.m0 : D.m[p];
+        }
+        const float mm = valid ? m : 0.0f;
+        const CornerW cw = corner_table(t, L.j);
+        float res[4];
+        reduce_scatter8<4, true>(
+            [&](int q, float* o) {
+                const float wx = cw.wx[q & 1], wy = cw.wy[(q >> 1) & 1], wz = cw.wz[q >> 2];
+                float w = wx * wy * wz * mm;
+                o[0] = w;
+                o[1] = w * vn1[0];
+                o[2] = w * vn1[1];
+                o[3] = w * vn1[2];
+            },
+            res, L.j);
+        if (r > 0) lds_barrier(); // the places of the last round have been read
+        *(float4*)(s_part + tl * 4) = make_float4(res[0], res[1], res[2], res[3]);
+        lds_barrier();
+        NodePlaces np;
+        np.set(late(tid) >> 2);
+        if (bn < TL_BOXN)
+#pragma unroll
+            for (int w = 0; w < 8; w++) sum += s_part[np(w) * 4 + u4];
+    }
+    if (SPLIT && tid == 0) D.xrs[bi] = 0;
+    if (bn < TL_BOXN) D.rs[(size_t)bi * (unsigned)(S.scap * TL_BOXN * 4) + tid] = sum;
+    put_box(S, D, bi, info.x, 0, track, ap, bb, s_bb);
+}
+
+template <bool SPLIT>
+DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
+{
+    __shared__ BoxTab T;
+    __shared__ __align__(16) float s_grid[(TL_BOX_SLOTS + 1) * 8]; // per slot (1 - beta) v^n + dv, v^n + dv; a zero
+    __shared__ __align__(16) float s_work[TL_ONE_PLACES * 4 + TL_BOX_SLOTS * 4];
+    __shared__ __align__(8) uint16_t s_cs[TL_ONE_PLACES + 7];
+    __shared__ int s_rw[8];
+    __shared__ float s_bb[8][8];
+    float* const s_sum = s_work;                      // the node sums of nodes with several slots, then
+    float* const s_part = s_work;                     // the places of a round and
+    float* const s_acc = s_work + TL_ONE_PLACES * 4; // the sums of earlier rounds
+    static_assert(TL_ONE_PLACES * 4 + TL_BOX_SLOTS * 4 >= TL_BOX_SLOTS * 7, "node sums in the places");
+
+    const int nround = SPLIT ? D.bround[bi] : 0; // rounds of a brick with a mixed cell, else 0
+    if (SPLIT && part == 1 && nround <= 1) return; // (split bricks as in the P2G)
+    const int4 info = D.binfo[bi];
+    const int brick = info.x, bx = info.y, by = info.z, bz = info.w;
+    if (bi == 0 && part == 0 && threadIdx.x == 0) {
+        // end of the substep for this scene: next history stamp, F update pending
+        // (no other kernel of the substep reads these after this point); whether this
+        // G2P splits its mixed bricks (read by the next P2G and box tests)
+        D.ctr[0] += 1;
+        D.ctr[1] = 1;
+        D.ctr[2] += 1;
+        if (SPLIT) D.xg[0] = (S.xcap > 0 && D.ctr[3] > 0 && D.ctr[3] <= S.xcap) ? 1 : 0;
+    }
+    // displacement anchor of this workgroup's particles (pair-search skip), kept for
+    // bricks with contact candidates (only candidates can be partners): the centre of
+    // the brick's box after the last G2P minus the centre of its particles' reference
+    // box.  A split brick's second workgroup reads the first one's record, which that
+    // one may rewrite in this launch; either value is a valid anchor, since the spread
+    // is measured against the anchor taken.
+    const bool track = S.pair_skip && D.bcand[bi] > 0;
+    float ap[3] = {0.0f, 0.0f, 0.0f};
+    if (track) {
+        g2p_anchor(D, D.aabb + (long long)brick * 8, brick, ap);
+        for (int a = 0; a < 3; a++) ap[a] = scalar(ap[a]);
+    }
+    int nbv;
+    bool changed;
+    if (one_code<false>(S, D, bx, by, bz, nbv, changed)) {
+        g2p_one<SPLIT>(S, D, bi, info, nbv, track, ap, s_grid, s_part, s_rw, s_bb);
+        return;
+    }
+    const bool grouped = D.bmixed[brick] != 0; // a cell holds two codes: same-code groups
+    // this substep's P2G split its mixed bricks (a scene without split workgroups never)
+    const bool xsplit = SPLIT && S.xcap > 0 && D.ctr[3] > 0 && D.ctr[3] <= S.xcap;
+    const bool split = grouped && nround > 1 && xsplit;
+    const int r0 = part;
+    const int tid = threadIdx.x, bn = tid >> 2, u4 = tid & 3;
+    const long long N = S.N;
+    const float beta = S.beta;
+
+    // ---- phase 1: counts, cell index, codes and partials of the own node, particle loads
+    BoxCounts nc;
+    nc.load(S, D.cnt[cur], bx, by, bz);
+    Lane L = lane_at(tid);
+    lane_cell(D, brick, L);
+    int p = L.beg;
+    bool valid = lane_particle(D, bi, grouped, L, r0, p);
+    float Xp[3] = {0.0f, 0.0f, 0.0f}, v[3] = {0.0f, 0.0f, 0.0f}, u[3] = {0.0f, 0.0f, 0.0f};
+    uint32_t code = 0;
+    auto load_particle = [&]() {
+        for (int a = 0; a < 3; a++) {
+            Xp[a] = D.X[at3(p, a)];
+            v[a] = D.v[at3(p, a)];
+            u[a] = D.u[at3(p, a)];
+        }
+        code = D.code[p];
+    };
+    int mt = 0;
+    const int total = nc.scan(T, bn, mt);
+    if (total > TL_BOX_SLOTS) {
+        if (tid == 0) atomicOr(D.status, TL_ST_BOX);
+        return;
+    }
+    if (bn >= TL_BOXN) mt = 0;
+    const int c = tab_count(mt), b0 = tab_base(mt);
+    const long long gid = bn < TL_BOXN ? box_gid(S, bx, by, bz, bn % 5, (bn / 5) % 5, bn / 25) : -1;
+    Contrib C;
+    C.set(S, nbv, bn, u4);
+    const uint32_t pre = codes_pre(S, D.scode[cur], mt, gid, u4);
+    Gather<8> g0, g1;
+    g0.load(D.p2g, C, 0, c > 0);
+    g1.load(D.p2g, C, 1, c > 1);
+    if (valid) load_particle();
+    put_rounds(L, s_rw);
+    if (tid < 8) s_grid[TL_BOX_SLOTS * 8 + tid] = 0.0f;
+    if (tid == 0) s_cs[TL_WG] = TL_NO_SLOT;
+    // ---- phase 2: P2G sums of the own node, coupling (Eq. 8), v^n and dv (Eq. 9)
+    codes_put(S, D.scode[cur], T, mt, gid, u4, pre);
+    for (int s = 0; s < c; s += 2) {
+        if (s > 0) {
+            g0.load(D.p2g, C, s, true);
+            g1.load(D.p2g, C, s + 1, s + 1 < c);
+        }
+        if (xsplit) {
+            g0.add(D.p2g_x, D.xp2g, C, s);
+            if (s + 1 < c) g1.add(D.p2g_x, D.xp2g, C, s + 1);
+        }
+        float a0[7], a1[7];
+        g0.sum(a0);
+        g1.sum(a1);
+        if (c == 1) { // one slot: no exchange
+            const float im = a0[0] > 0.0f ? 1.0f / a0[0] : 0.0f;
+            const float vn = (u4 == 0 ? a0[1] : u4 == 1 ? a0[2] : a0[3]) * im;
+            const float dv = (u4 == 0 ? a0[4] : u4 == 1 ? a0[5] : a0[6]) * im;
+            s_grid[b0 * 8 + u4] = (1.0f - beta) * vn + dv;
+            s_grid[b0 * 8 + 4 + u4] = vn + dv;
+        } else {
+            float* o = s_sum + (b0 + s) * 7;
+            if (u4 == 0)
+#pragma unroll
+                for (int q = 0; q < 7; q++) o[q] = a0[q];
+            if (u4 == 1 && s + 1 < c)
+#pragma unroll
+                for (int q = 0; q < 7; q++) o[7 + q] = a1[q];
+        }
+    }
+    wave_lds_fence();
+    if (c > 1 && u4 < 3) {
+        couple_component<7>(T, b0, c, s_sum, 1 + u4, [&](int sl, float m, float f) {
+            const float im = m > 0.0f ? 1.0f / m : 0.0f;
+            s_grid[sl * 8 + u4] = f * im;
+        });
+        couple_component<7>(T, b0, c, s_sum, 4 + u4, [&](int sl, float m, float f) {
+            const float im = m > 0.0f ? 1.0f / m : 0.0f;
+            const float vn = s_grid[sl * 8 + u4], dv = f * im;
+            s_grid[sl * 8 + u4] = (1.0f - beta) * vn + dv;
+            s_grid[sl * 8 + 4 + u4] = vn + dv;
+        });
+    }
+    lds_barrier();
+    const int rounds = (split && part == 0) ? 1 : grouped ? D.bround[bi] : get_rounds(s_rw);
+    const float4* const gr = (const float4*)s_grid;
+    // box of x^{n+1}, speed bound, and the largest |u^{n+1} - a| about the anchor a
+    // (for the pair-search skip)
+    float bb[8] = {1e30f, 1e30f, 1e30f, -1e30f, -1e30f, -1e30f, 0.0f, 0.0f};
+    for (int r = r0; r < rounds; r++) {
+        const int tl = late(tid);
+        L = lane_at(tl);
+        if (r > r0) {
+            lane_cell(D, brick, L);
+            valid = lane_particle(D, bi, grouped, L, r, p);
+            if (valid) load_particle();
+        }
+        float t[3] = {0.0f, 0.0f, 0.0f};
+        uint32_t key = 0;
+        float m = 0.0f, vn1[3] = {0.0f, 0.0f, 0.0f};
+        if (valid) {
+            frac_of(S, Xp, info.y * TL_B + L.cxl, info.z * TL_B + L.cyl, info.w * TL_B + L.czl, t);
+            key = slot_key(S, code);
+        }
+        if (r > r0) lds_barrier(); // the places of the last round have been read
+        find_corner_slot(D, T, L, tl, valid, key, s_cs);
+        wave_lds_fence();
+        CellSlots cs;
+        cs.read(s_cs, tl);
+        if (valid) {
+            float av[3] = {0.0f, 0.0f, 0.0f}, ax[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < 8; k++) { // (a zero weight adds zero: node values are finite)
+                float wx, wy, wz;
+                corner_weights(t, k, wx, wy, wz);
+                const float w = wx * wy * wz;
+                const int sl = cs(k) < TL_BOX_SLOTS ? cs(k) : TL_BOX_SLOTS;
+                const float4 fv = gr[2 * sl], fx = gr[2 * sl + 1];
+                av[0] += w * fv.x;
+                av[1] += w * fv.y;
+                av[2] += w * fv.z;
+                ax[0] += w * fx.x;
+                ax[1] += w * fx.y;
+                ax[2] += w * fx.z;
+            }
+            move_particle(S, D, N, p, Xp, v, u, av, ax, ap, vn1, bb);
+            m = S.m_uniform ? S.m0 : D.m[p];
+        }
+        const float mm = valid ? m : 0.0f;
+        const CornerW cw = corner_table(t, L.j);
+        float res[4];
+        reduce_scatter8<4, true>(
+            [&](int q, float* o) {
+                const float wx = cw.wx[q & 1], wy = cw.wy[(q >> 1) & 1], wz = cw.wz[q >> 2];
+                float w = wx * wy * wz * mm;
+                o[0] = w;
+                o[1] = w * vn1[0];
+                o[2] = w * vn1[1];
+                o[3] = w * vn1[2];
+            },
+            res, L.j);
+        *(float4*)(s_part + tl * 4) = make_float4(res[0], res[1], res[2], res[3]);
+        lds_barrier();
+        NodePlaces np;
+        np.set(late(tid) >> 2);
+        if (bn < TL_BOXN)
+            add_places<1, 4>(np, mt, bn, u4, s_part, s_cs, s_acc, r == r0, r + 1 == rounds,
+                          (part ? D.rs_x : D.rs) + (size_t)bi * (unsigned)(S.scap * TL_BOXN * 4));
+    }
+    if (SPLIT && part == 0 && tid == 0) D.xrs[bi] = split ? 1 : 0;
+    put_box(S, D, bi, brick, part, track, ap, bb, s_bb);
+}
+
 // ------------------------------------------------------------- mixed-code bricks
 // Per cell of a brick whose codes changed (or of every brick, when forced): the
 // one slot key of its particles (or empty / mixed).  A brick with a mixed cell
@@ -1173,7 +1674,8 @@ DEV void cell_summaries(const SceneK& S, const SceneD& D, int bi, int brick)
         s_bor = 0u;
     }
     __syncthreads();
-    bool mixed = false;
+    bool mixed = false, some = false;
+    uint32_t key = 0u;
     for (int c = threadIdx.x; c < TL_CELLS; c += blockDim.x) {
         const long long cs = (long long)brick * TL_CELLS + c;
         const int b0 = D.cell_start[cs], b1 = D.cell_start[cs + 1];
@@ -1216,11 +1718,20 @@ DEV void cell_summaries(const SceneK& S, const SceneD& D, int bi, int brick)
             for (int q = 0; q < nk; q++) D.ckeys[cs * TL_CKEYS + q] = ks[q];
         if (S.material_contact) D.cmask[cs] = orm;
         if (S.pair_skip && orm) atomicOr(&s_bor, orm);
+        some = true;
+        key = k0;
         mixed |= cm;
+    }
+    // the key of a one-code brick: the first wave holds its cells, one per lane
+    if (threadIdx.x < TL_CELLS) {
+        const unsigned long long cells = __ballot(some);
+        const uint32_t k0 = __shfl(key, cells ? __ffsll(cells) - 1 : 0, 64);
+        key = __any(some && key != k0) ? TL_CC_MIXED : k0;
     }
     const int m = __syncthreads_or(mixed);
     if (threadIdx.x == 0) {
         if (S.pair_skip) D.bor[brick] = s_bor; // (the barrier above ordered the LDS ORs)
+        D.bkey[brick] = m ? TL_CC_MIXED : key;
         D.bmixed[brick] = m;
         if (!m) {
             D.bround[bi] = 0; // no split workgroup for this brick
@@ -1338,9 +1849,9 @@ DEV void labels_brick(const SceneK& S, const SceneD& D, int bi, int brick, int m
     for (int p = beg + threadIdx.x; p < end; p += blockDim.x) {
         uint32_t code = D.code[p];
         uint32_t nc = code;
-        double x[3] = {(double)D.X[p] + (double)D.u[p], (double)D.X[N + p] + (double)D.u[N + p],
-                       (double)D.X[2 * N + p] + (double)D.u[2 * N + p]};
-        double v[3] = {(double)D.v[p], (double)D.v[N + p], (double)D.v[2 * N + p]};
+        double x[3] = {(double)D.X[at3(p, 0)] + (double)D.u[at3(p, 0)], (double)D.X[at3(p, 1)] + (double)D.u[at3(p, 1)],
+                       (double)D.X[at3(p, 2)] + (double)D.u[at3(p, 2)]};
+        double v[3] = {(double)D.v[at3(p, 0)], (double)D.v[at3(p, 1)], (double)D.v[at3(p, 2)]};
         for (int b = 0; b < s_nb; b++) {
             const DevBlade& B = s_bl[b];
             uint32_t bit1 = 1u << B.cut, bit2 = 1u << (15 + B.cut);
@@ -1481,13 +1992,13 @@ DEV void aabb_body(const SceneK& S, const SceneD& D, int bi)
     for (int p = beg + threadIdx.x; p < end; p += blockDim.x) {
         float sp = 0.0f;
         for (int a = 0; a < 3; a++) {
-            const float X = D.X[a * N + p];
-            float xa = X + D.u[a * N + p];
+            const float X = D.X[at3(p, a)];
+            float xa = X + D.u[at3(p, a)];
             bb[a] = fminf(bb[a], xa);
             bb[3 + a] = fmaxf(bb[3 + a], xa);
             bb[7 + a] = fminf(bb[7 + a], X);
             bb[10 + a] = fmaxf(bb[10 + a], X);
-            sp += D.v[a * N + p] * D.v[a * N + p];
+            sp += D.v[at3(p, a)] * D.v[at3(p, a)];
         }
         bb[6] = fmaxf(bb[6], sqrtf(sp));
     }
@@ -1523,7 +2034,7 @@ DEV void aabb_body(const SceneK& S, const SceneD& D, int bi)
     // spread about the anchor: exact, from a second pass over the particles
     float dv = 0.0f;
     for (int p = beg + threadIdx.x; p < end; p += blockDim.x)
-        for (int a = 0; a < 3; a++) dv = fmaxf(dv, fabsf(D.u[a * N + p] - s_a[a]));
+        for (int a = 0; a < 3; a++) dv = fmaxf(dv, fabsf(D.u[at3(p, a)] - s_a[a]));
     for (int o = 32; o >= 1; o >>= 1) dv = fmaxf(dv, __shfl_xor(dv, o, 64));
     __syncthreads();
     if (lane == 0) s_bb[w][7] = dv;
@@ -1671,7 +2182,7 @@ __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(MAT == 0 
     }
 }
 template <bool SPLIT>
-__global__ __launch_bounds__(TL_WG) void k_g2p(SceneK S, SceneD D, int cur)
+__global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(6))) void k_g2p(SceneK S, SceneD D, int cur)
 {
     const int b = blockIdx.x;
     if constexpr (!SPLIT) {
@@ -1683,7 +2194,7 @@ __global__ __launch_bounds__(TL_WG) void k_g2p(SceneK S, SceneD D, int cur)
     }
 }
 template <bool SPLIT>
-__global__ __launch_bounds__(TL_WG) void k_g2p_b(const SceneK* __restrict__ Ks, const SceneD* __restrict__ Ds,
+__global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(6))) void k_g2p_b(const SceneK* __restrict__ Ks, const SceneD* __restrict__ Ds,
                                                  const int2* __restrict__ it, const int2* __restrict__ xit, int nx,
                                                  int cur)
 {

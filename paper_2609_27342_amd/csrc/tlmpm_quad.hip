@@ -238,7 +238,7 @@ __global__ __launch_bounds__(TL_QWG) void k_q_slots(SceneK S, SceneD D, int par)
             atomicOr(D.status, TL_ST_BOX);
             continue;
         }
-        const float X[3] = {D.X[p], D.X[N + p], D.X[2 * N + p]};
+        const float X[3] = {D.X[at3(p, 0)], D.X[at3(p, 1)], D.X[at3(p, 2)]};
         QStencil Q;
         q_stencil(S, X, c, h, Q);
         const int ox = Q.lo[0] - (bx * TL_B - 1), oy = Q.lo[1] - (by * TL_B - 1), oz = Q.lo[2] - (bz * TL_B - 1);
@@ -370,11 +370,11 @@ __global__ __launch_bounds__(TL_QWG) void k_q_p2g(SceneK S, SceneD D, int par)
         if (valid) {
             float H[9];
             const uint32_t code = D.code[p];
-            const float X[3] = {D.X[p], D.X[N + p], D.X[2 * N + p]};
+            const float X[3] = {D.X[at3(p, 0)], D.X[at3(p, 1)], D.X[at3(p, 2)]};
 #pragma unroll
-            for (int a = 0; a < 9; a++) H[a] = D.H[a * N + p];
+            for (int a = 0; a < 9; a++) H[a] = D.H[at9(N, p, a)];
 #pragma unroll
-            for (int a = 0; a < 3; a++) vel[a] = D.v[a * N + p];
+            for (int a = 0; a < 3; a++) vel[a] = D.v[at3(p, a)];
             m = S.m_uniform ? S.m0 : D.m[p];
             const float V0 = S.v_uniform ? S.V0 : D.V0[p];
             const float E = S.e_uniform ? S.E0 : D.E[p];
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(TL_QWG) void k_q_p2g(SceneK S, SceneD D, int par)
                     // P = P_fcr(F_e) F_p^{-T}, F_e - I = H + Gp + H Gp, F_p^{-1} = I + Gp
                     float Gp[9], K[9], Pe[9];
 #pragma unroll
-                    for (int a = 0; a < 9; a++) Gp[a] = D.Gp[a * N + p];
+                    for (int a = 0; a < 9; a++) Gp[a] = D.Gp[at9(N, p, a)];
 #pragma unroll
                     for (int i = 0; i < 3; i++)
 #pragma unroll
@@ -410,7 +410,7 @@ __global__ __launch_bounds__(TL_QWG) void k_q_p2g(SceneK S, SceneD D, int par)
                 if (ok && S.visc > 0.0f) {
                     float Fd[9];
 #pragma unroll
-                    for (int a = 0; a < 9; a++) Fd[a] = D.Fdot[a * N + p];
+                    for (int a = 0; a < 9; a++) Fd[a] = D.Fdot[at9(N, p, a)];
                     add_viscous(S.visc, H, Fd, Pk);
                 }
             } else {
@@ -423,14 +423,14 @@ __global__ __launch_bounds__(TL_QWG) void k_q_p2g(SceneK S, SceneD D, int par)
             }
             float Jc[3] = {0.0f, 0.0f, 0.0f};
             if (rig) {
-                Jc[0] += D.Jrig[p];
-                Jc[1] += D.Jrig[N + p];
-                Jc[2] += D.Jrig[2 * N + p];
+                Jc[0] += D.Jrig[at3(p, 0)];
+                Jc[1] += D.Jrig[at3(p, 1)];
+                Jc[2] += D.Jrig[at3(p, 2)];
             }
             if (S.material_contact && (code & TL_CAND_BIT)) {
-                Jc[0] += D.Jmat[p];
-                Jc[1] += D.Jmat[N + p];
-                Jc[2] += D.Jmat[2 * N + p];
+                Jc[0] += D.Jmat[at3(p, 0)];
+                Jc[1] += D.Jmat[at3(p, 1)];
+                Jc[2] += D.Jmat[at3(p, 2)];
             }
 #pragma unroll
             for (int a = 0; a < 3; a++) ext[a] = Jc[a] + dt * m * (a == 0 ? S.gx : a == 1 ? S.gy : S.gz);
@@ -632,7 +632,7 @@ __global__ __launch_bounds__(TL_QWG) void k_q_g2p(SceneK S, SceneD D, int par)
         float m = 0.0f, vn1[3] = {0.0f, 0.0f, 0.0f};
         QStencil Q = {};
         if (valid) {
-            const float X[3] = {D.X[p], D.X[N + p], D.X[2 * N + p]};
+            const float X[3] = {D.X[at3(p, 0)], D.X[at3(p, 1)], D.X[at3(p, 2)]};
             q_stencil(S, X, c, h, Q);
             float av[3] = {0.0f, 0.0f, 0.0f}, ax[3] = {0.0f, 0.0f, 0.0f};
             auto add_node = [&](float w, const float* vn, const float* dv) {
@@ -674,10 +674,10 @@ __global__ __launch_bounds__(TL_QWG) void k_q_g2p(SceneK S, SceneD D, int par)
             }
 #pragma unroll
             for (int j = 0; j < 3; j++) {
-                vn1[j] = beta * D.v[j * N + p] + av[j];
-                const float un = D.u[j * N + p] + dt * ax[j];
-                D.v[j * N + p] = vn1[j];
-                D.u[j * N + p] = un;
+                vn1[j] = beta * D.v[at3(p, j)] + av[j];
+                const float un = D.u[at3(p, j)] + dt * ax[j];
+                D.v[at3(p, j)] = vn1[j];
+                D.u[at3(p, j)] = un;
                 const float xa = X[j] + un;
                 bb[j] = fminf(bb[j], xa);
                 bb[3 + j] = fmaxf(bb[3 + j], xa);
@@ -783,7 +783,7 @@ __global__ __launch_bounds__(TL_QWG) void k_q_F(SceneK S, SceneD D, int par)
         const uint32_t key = slot_key(S, D.code[p]);
         const int k = q_key_lookup(s_keys, key);
         if (k < 0) continue;
-        const float X[3] = {D.X[p], D.X[N + p], D.X[2 * N + p]};
+        const float X[3] = {D.X[at3(p, 0)], D.X[at3(p, 1)], D.X[at3(p, 2)]};
         QStencil Q;
         q_stencil(S, X, c, h, Q);
         float Lg[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -829,19 +829,19 @@ __global__ __launch_bounds__(TL_QWG) void k_q_F(SceneK S, SceneD D, int par)
         bool fin = true;
 #pragma unroll
         for (int a = 0; a < 9; a++) {
-            H[a] = D.H[a * N + p] + dt * Lg[a];
-            D.H[a * N + p] = H[a];
+            H[a] = D.H[at9(N, p, a)] + dt * Lg[a];
+            D.H[at9(N, p, a)] = H[a];
             fin = fin && isfinite(H[a]);
         }
         if (!fin) atomicOr(D.status, TL_ST_NONFINITE);
         if constexpr (MAT == 1) {
             if (S.visc > 0.0f)
 #pragma unroll
-                for (int a = 0; a < 9; a++) D.Fdot[a * N + p] = Lg[a];
+                for (int a = 0; a < 9; a++) D.Fdot[at9(N, p, a)] = Lg[a];
             if (S.ystress > 0.0f) {
                 float Gp[9], K[9];
 #pragma unroll
-                for (int a = 0; a < 9; a++) Gp[a] = D.Gp[a * N + p];
+                for (int a = 0; a < 9; a++) Gp[a] = D.Gp[at9(N, p, a)];
 #pragma unroll
                 for (int i = 0; i < 3; i++)
 #pragma unroll
@@ -854,7 +854,7 @@ __global__ __launch_bounds__(TL_QWG) void k_q_F(SceneK S, SceneD D, int par)
                 const float E = S.e_uniform ? S.E0 : D.E[p];
                 if (vm_project(E, S.nu, S.ystress, K, Gp))
 #pragma unroll
-                    for (int a = 0; a < 9; a++) D.Gp[a * N + p] = Gp[a];
+                    for (int a = 0; a < 9; a++) D.Gp[at9(N, p, a)] = Gp[a];
             }
         }
     }

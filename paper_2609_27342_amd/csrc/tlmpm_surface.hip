@@ -72,8 +72,8 @@ __global__ void k_surf_sites(SceneK S, SceneD D, SurfGrid G, SurfMem M)
 {
     const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= S.N) return;
-    const double q0 = ((double)D.X[p] - G.ox) / G.h, q1 = ((double)D.X[S.N + p] - G.oy) / G.h,
-                 q2 = ((double)D.X[2 * S.N + p] - G.oz) / G.h;
+    const double q0 = ((double)D.X[at3(p, 0)] - G.ox) / G.h, q1 = ((double)D.X[at3(p, 1)] - G.oy) / G.h,
+                 q2 = ((double)D.X[at3(p, 2)] - G.oz) / G.h;
     const long long s = site_index(G, (int)floor(q0), (int)floor(q1), (int)floor(q2));
     if (s < 0) return;
     const unsigned long long key = ((unsigned long long)(unsigned)D.perm[p] << 32) | (unsigned long long)p;
@@ -393,9 +393,9 @@ __global__ void k_surf_embed(SceneK S, SceneD D, SurfMem M, int nv)
         const int p = M.vp[(long long)v * 8 + k];
         if (p < 0) continue;
         const float w = M.vw[(long long)v * 8 + k];
-        d[0] += w * D.u[p];
-        d[1] += w * D.u[S.N + p];
-        d[2] += w * D.u[2 * S.N + p];
+        d[0] += w * D.u[at3(p, 0)];
+        d[1] += w * D.u[at3(p, 1)];
+        d[2] += w * D.u[at3(p, 2)];
     }
     M.vx[v] = make_float4(X.x + d[0], X.y + d[1], X.z + d[2], 0.0f);
 }
