@@ -34,6 +34,7 @@ hipError_t tl_launch_cand(const TlLaunch*, int force);
 hipError_t tl_launch_contact(const TlLaunch*);
 hipError_t tl_launch_labels_rigid(const TlLaunch*);
 hipError_t tl_launch_cand_contact_slots(const TlLaunch*, int dst, int src);
+hipError_t tl_launch_export(const TlLaunch*, const TlExport*, void* out, int o0, int o1, int max_cuts);
 hipError_t tl_launch_fill_f32(float*, long long, float, hipStream_t);
 hipError_t tl_launch_fill_i32(int*, long long, int, hipStream_t);
 hipError_t tl_launch_quad(const TlLaunch*, int par, int stage);
@@ -121,6 +122,7 @@ struct tlmpm_scene {
     int in_batch = 0; // member of a live batch: single-scene calls are refused
     int fuse_bricks = 0; // one-stream substeps up to this many active bricks (tuning at creation)
     std::vector<int> active_host;
+    size_t stage_bytes = 0; // of the partial arrays, where a state copy is staged
     Timing prof;
     GraphCache graphs;
     Fork fork;
@@ -340,6 +342,10 @@ Offsets plan(const tlmpm_scene_desc* d, long long n_active)
     o.rs = L.take((size_t)n_active * scap * TL_BOXN * 4 * f);
     o.p2g_x = L.take((size_t)n_active * scap * TL_BOXN * 8 * f);
     o.rs_x = L.take((size_t)n_active * scap * TL_BOXN * 4 * f);
+    // these four arrays also stage state copies: at least one 48-byte row per particle (a
+    // few bricks with very many particles per cell would not reach that)
+    const size_t staged = L.take(0) - o.p2g;
+    if (staged < N * 48) L.take(N * 48 - staged);
     o.xp2g = L.take((size_t)n_active * 4);
     o.xrs = L.take((size_t)n_active * 4);
     o.aabb_x = L.take((size_t)g.n_bricks * 8 * f);
@@ -633,6 +639,7 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     D.rs = (float*)(base + o.rs);
     D.p2g_x = (float*)(base + o.p2g_x);
     D.rs_x = (float*)(base + o.rs_x);
+    sc->stage_bytes = o.xp2g - o.p2g; // (the four partial arrays follow one another)
     D.xp2g = (int*)(base + o.xp2g);
     D.xrs = (int*)(base + o.xrs);
     D.aabb_x = (float*)(base + o.aabb_x);
@@ -1326,6 +1333,10 @@ static uint64_t code_to_ternary(uint32_t c, int K)
     return v;
 }
 
+// Copies the wanted fields to the caller's buffers.  They are first brought into the
+// caller's order on the device (k_export), in the partial arrays: with no F update pending
+// they hold nothing that is still needed (the next P2G and G2P write them before they are
+// read).  Where the fields do not fit, a range of particles at a time.
 extern "C" tlmpm_status tlmpm_read_state(tlmpm_scene* sc, uint32_t mask, void* const* out)
 {
     if (tlmpm_status r = refuse_batched(sc)) return r;
@@ -1333,52 +1344,39 @@ extern "C" tlmpm_status tlmpm_read_state(tlmpm_scene* sc, uint32_t mask, void* c
     tlmpm_status s = flush_F(sc);
     if (s) return s;
     const long long N = sc->K.N;
-    SceneD& D = sc->D;
-    std::vector<int> perm(N);
-    if (N) HIPCHK(hipMemcpyAsync(perm.data(), D.perm, N * 4, hipMemcpyDeviceToHost, sc->st));
-    std::vector<float> buf;
-    std::vector<uint32_t> cb;
-    HIPCHK(hipStreamSynchronize(sc->st));
+    const int K = sc->max_cuts;
+    const size_t bytes[8] = {12, 12, 12, 36, 8, 4, (size_t)K, 36};
+    char* dst[8] = {};
+    size_t row = 0;
     int slot = 0;
-    for (uint32_t bit = 1; bit <= TLMPM_FIELD_H; bit <<= 1) {
-        if (!(mask & bit)) continue;
-        void* dst = out[slot++];
-        if (!dst) return fail(TLMPM_E_INVALID, "null output buffer");
-        if (bit == TLMPM_FIELD_X || bit == TLMPM_FIELD_U || bit == TLMPM_FIELD_V || bit == TLMPM_FIELD_F ||
-            bit == TLMPM_FIELD_D || bit == TLMPM_FIELD_H) {
-            int comps = (bit == TLMPM_FIELD_F || bit == TLMPM_FIELD_H) ? 9 : (bit == TLMPM_FIELD_D ? 1 : 3);
-            const float* src = bit == TLMPM_FIELD_X ? D.X
-                               : bit == TLMPM_FIELD_U ? D.u
-                               : bit == TLMPM_FIELD_V ? D.v
-                               : (bit == TLMPM_FIELD_F || bit == TLMPM_FIELD_H) ? D.H
-                                                                                : D.D;
-            buf.resize((size_t)comps * N);
-            if (N) HIPCHK(hipMemcpyAsync(buf.data(), src, (size_t)comps * N * 4, hipMemcpyDeviceToHost, sc->st));
-            HIPCHK(hipStreamSynchronize(sc->st));
-            float* o = (float*)dst;
-            for (long long q = 0; q < N; q++)
-                for (int a = 0; a < comps; a++) {
-                    // (vectors [N][3]; matrices by rows [3][N][3])
-                    float val = buf[comps == 1 ? (size_t)q : 3 * ((size_t)(a / 3) * N + q) + a % 3];
-                    if (bit == TLMPM_FIELD_F && (a == 0 || a == 4 || a == 8)) val += 1.0f;
-                    o[(size_t)perm[q] * comps + a] = val;
-                }
-        } else {
-            cb.resize(N);
-            if (N) HIPCHK(hipMemcpyAsync(cb.data(), D.code, N * 4, hipMemcpyDeviceToHost, sc->st));
-            HIPCHK(hipStreamSynchronize(sc->st));
-            for (long long q = 0; q < N; q++) {
-                uint32_t c = cb[q];
-                if (bit == TLMPM_FIELD_CODE) {
-                    ((uint64_t*)dst)[perm[q]] = code_to_ternary(c, sc->max_cuts);
-                } else {
-                    uint8_t* o = (uint8_t*)dst + (size_t)perm[q] * sc->max_cuts;
-                    for (int k = 0; k < sc->max_cuts; k++)
-                        o[k] = (c >> k) & 1 ? 1 : ((c >> (15 + k)) & 1 ? 2 : 0);
-                }
+    for (int f = 0; f < 8; f++) {
+        if (!(mask & (1u << f))) continue;
+        dst[f] = (char*)out[slot++];
+        if (!dst[f]) return fail(TLMPM_E_INVALID, "null output buffer");
+        row += bytes[f];
+    }
+    if (N > 0 && row > 0) {
+        char* stage = (char*)sc->D.p2g;
+        // each field starts 256-byte aligned
+        const long long fit = ((long long)sc->stage_bytes - 8 * 256) / (long long)row;
+        if (fit < 1) return fail(TLMPM_E_DEVICE, "no room to stage a state copy");
+        const TlLaunch L = single_launch(sc);
+        for (long long o0 = 0; o0 < N; o0 += fit) {
+            const long long o1 = std::min(N, o0 + fit);
+            TlExport E;
+            size_t at = 0;
+            for (int f = 0; f < 8; f++) {
+                E.at[f] = dst[f] ? (long long)at : -1;
+                if (dst[f]) at += ((size_t)(o1 - o0) * bytes[f] + 255) & ~(size_t)255;
             }
+            HIPCHK(tl_launch_export(&L, &E, stage, (int)o0, (int)o1, K));
+            for (int f = 0; f < 8; f++)
+                if (dst[f])
+                    HIPCHK(hipMemcpyAsync(dst[f] + (size_t)o0 * bytes[f], stage + E.at[f], (size_t)(o1 - o0) * bytes[f],
+                                          hipMemcpyDeviceToHost, sc->st));
         }
     }
+    HIPCHK(hipStreamSynchronize(sc->st));
     return TLMPM_OK;
 }
 

@@ -197,6 +197,12 @@ struct SceneD {
     int* qmap;          // [rounds][512] particle of thread h * 64 + l: cell slot l, half pattern h (-1: none)
 };
 
+// Fields of a state copy in the order of the ABI's field bits (X, u, v, F, code, D, digits,
+// H): byte offset of each in the staging area, -1: not wanted
+struct TlExport {
+    long long at[8];
+};
+
 // Surface reconstruction (tlmpm_surface.hip): the site lattice of one scene and
 // the arrays of a surface workspace
 struct SurfGrid {
