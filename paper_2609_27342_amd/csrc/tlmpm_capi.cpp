@@ -34,6 +34,7 @@ hipError_t tl_launch_cand(const TlLaunch*, int force);
 hipError_t tl_launch_contact(const TlLaunch*);
 hipError_t tl_launch_labels_rigid(const TlLaunch*);
 hipError_t tl_launch_cand_contact_slots(const TlLaunch*, int dst, int src);
+hipError_t tl_launch_frac(const SceneK*, const SceneD*, hipStream_t);
 hipError_t tl_launch_export(const TlLaunch*, const TlExport*, void* out, int o0, int o1, int max_cuts);
 hipError_t tl_launch_fill_f32(float*, long long, float, hipStream_t);
 hipError_t tl_launch_fill_i32(int*, long long, int, hipStream_t);
@@ -237,7 +238,7 @@ Dims dims_of(const tlmpm_scene_desc* d)
 }
 
 struct Offsets {
-    size_t X, u, v, H, code, code_prev, D, perm, E, m, V0, cell_start, active, binfo, bkey, cnt0, cnt1, sc0, sc1, p2g, rs, p2g_x,
+    size_t X, T, u, v, H, code, code_prev, D, perm, E, m, V0, cell_start, active, binfo, bkey, cnt0, cnt1, sc0, sc1, p2g, rs, p2g_x,
         rs_x, xp2g, xrs, aabb_x, xlist, xin, xg, hist,
         aabb, wpart, Fdot, Gp, wacc, Jmat, Jrig, brig, bmixed, ccode, ckeys, gmeta, gperm, bround, tools, tinfo, ctr, bact, status, dirty, bdirty, pcell, cand_idx, coff, cmask, cstatic, bcand, hbin, hmax, uanc, uanc_x, uref, bor, umm,
         bcount, bids, crec, htab, hnext, ph_n, ph_q, ph_u,
@@ -319,6 +320,7 @@ Offsets plan(const tlmpm_scene_desc* d, long long n_active)
     size_t N = (size_t)std::max<long long>(g.N, 1);
     size_t f = sizeof(float);
     o.X = L.take(3 * N * f);
+    o.T = d->stencil == 0 ? L.take(3 * N * f) : 0;
     o.u = L.take(3 * N * f);
     o.v = L.take(3 * N * f);
     o.H = L.take(9 * N * f);
@@ -578,6 +580,8 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     K.E0 = d->E_uniform;
     K.m0 = d->mass_uniform;
     K.V0 = d->vol0_uniform;
+    K.mu0 = K.E0 / (2.0f * (1.0f + K.nu));
+    K.lam0 = K.E0 * K.nu / ((1.0f + K.nu) * (1.0f - 2.0f * K.nu));
     K.s_R = d->s_R;
     K.s_n = d->s_n;
     K.gamma_k = d->gamma_k;
@@ -616,6 +620,7 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     SceneD& D = sc->D;
     memset(&D, 0, sizeof(D));
     D.X = (float*)(base + o.X);
+    D.T = d->stencil == 0 ? (float*)(base + o.T) : nullptr;
     D.u = (float*)(base + o.u);
     D.v = (float*)(base + o.v);
     D.H = (float*)(base + o.H);
@@ -800,6 +805,7 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     // contact-history stamp 1 (stored stamps of 0 read as the previous substep's
     // empty history), no F update pending
     if ((e = tl_launch_fill_i32(D.ctr, 1, 1, sc->st)) != hipSuccess) return bail(e, "counters");
+    if (d->stencil == 0 && (e = tl_launch_frac(&K, &D, sc->st)) != hipSuccess) return bail(e, "cell positions");
     // cells of bricks without particles (the summaries below cover the others): a zero
     // would read as a cell of code 0 and give the nodes next to it a slot of that code
     if ((e = tl_launch_fill_i32((int*)D.ccode, g.n_bricks * TL_CELLS, (int)TL_CC_EMPTY, sc->st)) != hipSuccess)

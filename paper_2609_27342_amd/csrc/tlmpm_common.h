@@ -88,6 +88,7 @@ struct SceneK {
     float nu;
     int e_uniform, m_uniform, v_uniform;
     float E0, m0, V0;
+    float mu0, lam0;      // Lame parameters of E0 and nu
     float s_R, s_n, gamma_k, gamma_c, mu_s, mu_d;
     float Rmax;           // largest contact radius s_R V0^{1/3} / 2
     int floor_on;
@@ -110,6 +111,7 @@ struct SceneK {
 // device pointers of a scene
 struct SceneD {
     float* X;      // [N][3]
+    float* T;      // [N][3] position in the reference cell, in cells (static; trilinear stencil)
     float* u;      // [N][3]
     float* v;      // [N][3]
     float* H;      // [3][N][3], row r of F - I at H[r]

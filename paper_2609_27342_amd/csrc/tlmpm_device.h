@@ -120,16 +120,27 @@ DEV void lds_barrier()
 }
 
 // ------------------------------------------------------------- constitutive model
+// Lame parameters of particle p.  With one stiffness for the scene they come with its
+// parameters (the host forms them by the same FP32 operations): two divisions less.
+DEV void lame(const SceneK& S, float E, float& mu, float& lam)
+{
+    if (S.e_uniform) {
+        mu = S.mu0;
+        lam = S.lam0;
+    } else {
+        mu = E / (2.0f * (1.0f + S.nu));
+        lam = E * S.nu / ((1.0f + S.nu) * (1.0f - 2.0f * S.nu));
+    }
+}
+
 // Compressible Neo-Hookean first Piola-Kirchhoff stress written in H = F - I so
 // that small strains keep their relative precision in FP32:
 //   cof(F) = (1 + tr H) I - H^T + cof(H),  J = 1 + tr H + I2(H) + det H,
 //   F - F^{-T} = [(I2 + det H) I + J H + H^T - cof(H)] / J,
 //   P = mu (F - F^{-T}) + lambda ln J F^{-T}.
 // Returns false when J <= 0 or the state is not finite.
-DEV bool neo_hookean(float E, float nu, const float* H, float* P)
+DEV bool neo_hookean(float mu, float lam, const float* H, float* P)
 {
-    const float mu = E / (2.0f * (1.0f + nu));
-    const float lam = E * nu / ((1.0f + nu) * (1.0f - 2.0f * nu));
     float cH[9];
     cH[0] = H[4] * H[8] - H[5] * H[7];
     cH[1] = H[5] * H[6] - H[3] * H[8];
@@ -168,10 +179,8 @@ DEV bool neo_hookean(float E, float nu, const float* H, float* P)
 // H^T H = Q diag(e) Q^T (Jacobi rotations), S - I = Q diag(e / (sqrt(1 + e) + 1)) Q^T,
 // S^{-1} = Q diag(1 / sqrt(1 + e)) Q^T, R = F S^{-1} and F - R = R (S - I).
 // Returns false when J <= 0 or the state is not finite.
-DEV bool fixed_corotated(float E, float nu, const float* H, float* P)
+DEV bool fixed_corotated(float mu, float lam, const float* H, float* P)
 {
-    const float mu = E / (2.0f * (1.0f + nu));
-    const float lam = E * nu / ((1.0f + nu) * (1.0f - 2.0f * nu));
     float A[9];
 #pragma unroll
     for (int i = 0; i < 3; i++)
@@ -317,9 +326,8 @@ DEV void add_viscous(float eta, const float* H, const float* Fdot, float* P)
 // scaled back onto |2 mu dev(eps)| = sqrt(2/3) sigma_y (volume kept).  The
 // projected F_e = F_e M with M = V diag(exp(eps_new - eps)) V^T, so F_p^{-1} = I +
 // G becomes (I + G) M.  Updates G and K; returns whether it yielded.
-DEV bool vm_project(float E, float nu, float sigma_y, float* K, float* G)
+DEV bool vm_project(float mu, float sigma_y, float* K, float* G)
 {
-    const float mu = E / (2.0f * (1.0f + nu));
     float A[9];
 #pragma unroll
     for (int i = 0; i < 3; i++)

@@ -26,9 +26,14 @@
 // 8 incident cells, in ascending code order; coupling (Eq. 8) is done per node when
 // a box is finalized, by the node's quad, a component per lane.
 //
-// What bounds P2G and G2P is the chain of dependent phases in a workgroup (brick record,
-// cell index and partial gather, coupling, particle stage, sums) and their instruction
-// count, at three workgroups per CU (80 registers, 43 to 53 KB of LDS).  The registers
+// What bounds P2G and G2P: in a large scene vector issue and memory together (14M
+// particles: P2G 78 % of the issue slots at 3.7 TB/s, G2P 64 % at 3.8, where a device copy
+// reaches 5.1), in a small one the chain of dependent phases in a workgroup (brick record,
+// cell index and partial gather, coupling, particle stage, sums); at three workgroups per
+// CU (80 registers, 43 to 53 KB of LDS).  Geometry that depends on the thread alone comes
+// from tables, rows of particles at 32-bit offsets from the brick's first (1250 -> 1050
+// vector instructions per wave of P2G: 183k particles on a cut 23.7 -> 22.9 us, 64 scenes
+// 301 -> 287 us, the plastic P2G 58.9 -> 54.6 us, 14M particles 572 -> 564 us).  The registers
 // hold only because a round recomputes its lane geometry (`late`): hoisted out of the
 // round loop it spills 20 and more words a lane.
 #include <hip/hip_runtime.h>
@@ -158,22 +163,45 @@ struct QPad {
 // The two contributors of box node bn that lane u of its quad loads: contributor d is
 // the brick at home - (d & 1, d >> 1 & 1, d >> 2 & 1), which holds the node at box
 // position (l + 4 * offset); lane u takes d = u and u + 4.  nb: the active indices of the
-// 27 bricks around in lanes 0..26; every lane of the wave calls this.
+// 27 bricks around in lanes 0..26; every lane of the wave calls this.  Which of the 27 and
+// which of its nodes are a table per thread.
+struct ContribTable {
+    uint16_t from[TL_WG][2]; // 4 x index into the 27 (a byte address across lanes), or 4 x 63: none
+    uint16_t node[TL_WG][2];
+    constexpr ContribTable() : from(), node()
+    {
+        for (int t = 0; t < TL_WG; t++)
+            for (int e = 0; e < 2; e++) {
+                const int bn = t >> 2, d = (t & 3) + 4 * e;
+                const int N[3] = {bn % 5, (bn / 5) % 5, bn / 25};
+                int at = 0, pn = 0, f27 = 1, f5 = 1;
+                bool in = bn < TL_BOXN;
+                for (int a = 0; a < 3; a++) {
+                    const int o = (d >> a) & 1, l = N[a] & 3;
+                    if (o && l) in = false;
+                    at += f27 * ((N[a] >> 2) - o + 1);
+                    pn += f5 * (l + 4 * o);
+                    f27 *= 3;
+                    f5 *= 5;
+                }
+                from[t][e] = (uint16_t)(4 * (in ? at : 63));
+                node[t][e] = (uint16_t)(in ? pn : 0);
+            }
+    }
+};
+static __device__ const ContribTable k_contrib __attribute__((aligned(16))) = ContribTable();
+
 struct Contrib {
     int ai[2];       // active index, -1: none
     unsigned rec[2]; // record of slot 0 (in nodes)
-    DEV void set(const SceneK& S, int nb, int bn, int u)
+    DEV void set(const SceneK& S, int nb, int tid)
     {
-        const int X = bn % 5, Y = (bn / 5) % 5, Z = bn / 25;
-        const int lx = X & 3, ly = Y & 3, lz = Z & 3;
-        const int dx = u & 1, dy = u >> 1;
+        const uint32_t from = *(const uint32_t*)k_contrib.from[tid], node = *(const uint32_t*)k_contrib.node[tid];
 #pragma unroll
-        for (int dz = 0; dz < 2; dz++) {
-            const int at = ((Z >> 2) - dz + 1) * 9 + ((Y >> 2) - dy + 1) * 3 + ((X >> 2) - dx + 1);
-            const int i = __shfl(nb, at, 64);
-            ai[dz] = (bn < TL_BOXN && !((dx && lx) || (dy && ly) || (dz && lz))) ? i : -1;
-            const int pn = (lx + 4 * dx) + 5 * (ly + 4 * dy) + 25 * (lz + 4 * dz);
-            rec[dz] = (unsigned)i * (unsigned)(S.scap * TL_BOXN) + (unsigned)pn;
+        for (int e = 0; e < 2; e++) {
+            // (lanes 27 .. 63 hold -1)
+            ai[e] = __builtin_amdgcn_ds_bpermute((int)(e ? from >> 16 : from & 0xFFFFu), nb);
+            rec[e] = (unsigned)ai[e] * (unsigned)(S.scap * TL_BOXN) + (e ? node >> 16 : node & 0xFFFFu);
         }
     }
 };
@@ -279,6 +307,54 @@ DEV void lane_cell(const SceneD& D, int brick, Lane& L)
     L.count = cs[1] - cs[0];
 }
 
+// Arrays from a brick's first particle on: rows of the brick's particles at 32-bit offsets
+// from a scalar base.
+struct Local {
+    int p0; // first particle of the brick
+    long long N;
+    DEV Local(const SceneK& S, const SceneD& D, int brick)
+        : p0(D.cell_start[(long long)brick * TL_CELLS]), N(S.N)
+    {
+    }
+    DEV float* row(float* a, int p) const { return (float*)((char*)(a + 3 * (size_t)p0) + 12u * (unsigned)(p - p0)); }
+    DEV float* row(float* a, int r, int p) const // row r of a matrix
+    {
+        return (float*)((char*)(a + 3 * ((size_t)r * (size_t)N + (size_t)p0)) + 12u * (unsigned)(p - p0));
+    }
+    template <class T>
+    DEV T* one(T* a, int p) const
+    {
+        return (T*)((char*)(a + (size_t)p0) + 4u * (unsigned)(p - p0));
+    }
+    DEV void get(float* a, int p, float* v) const
+    {
+        const float* q = row(a, p);
+        v[0] = q[0];
+        v[1] = q[1];
+        v[2] = q[2];
+    }
+    DEV void get9(float* a, int p, float* v) const
+    {
+#pragma unroll
+        for (int r = 0; r < 3; r++) {
+            const float* q = row(a, r, p);
+            v[3 * r] = q[0];
+            v[3 * r + 1] = q[1];
+            v[3 * r + 2] = q[2];
+        }
+    }
+    DEV void put9(float* a, int p, const float* v) const
+    {
+#pragma unroll
+        for (int r = 0; r < 3; r++) {
+            float* q = row(a, r, p);
+            q[0] = v[3 * r];
+            q[1] = v[3 * r + 1];
+            q[2] = v[3 * r + 2];
+        }
+    }
+};
+
 // The same value, computed from no earlier than here: keeps what is derived from it (the
 // addresses of a round's loads, stores and LDS places) out of the registers of the code
 // before, where it would be spilled
@@ -316,6 +392,22 @@ DEV void frac_of(const SceneK& S, const float* X, int gxc, int gyc, int gzc, flo
     t[0] = fminf(fmaxf((float)q0, 0.0f), 1.0f);
     t[1] = fminf(fmaxf((float)q1, 0.0f), 1.0f);
     t[2] = fminf(fmaxf((float)q2, 0.0f), 1.0f);
+}
+
+// The positions inside the reference cells, once per scene: P2G reads them in place of X
+// (the same bytes, and no FP64 chain per particle and substep)
+__global__ __launch_bounds__(256) void k_frac(SceneK S, SceneD D)
+{
+    const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= S.N) return;
+    const long long cs = D.pcell[p], brick = cs / TL_CELLS;
+    const int w = (int)(cs & 63) >> 3, i = (int)cs & 7;
+    const int bx = (int)(brick % S.cbx), by = (int)((brick / S.cbx) % S.cby), bz = (int)(brick / (S.cbx * S.cby));
+    const float X[3] = {D.X[at3(p, 0)], D.X[at3(p, 1)], D.X[at3(p, 2)]};
+    float t[3];
+    frac_of(S, X, bx * TL_B + 2 * (i & 1) + (w & 1), by * TL_B + 2 * ((i >> 1) & 1) + ((w >> 1) & 1),
+            bz * TL_B + 2 * ((i >> 2) & 1) + ((w >> 2) & 1), t);
+    for (int a = 0; a < 3; a++) D.T[at3(p, a)] = t[a];
 }
 
 DEV void corner_weights(const float t[3], int k, float& wx, float& wy, float& wz)
@@ -640,21 +732,59 @@ DEV void rigid_body(const SceneK& S, const SceneD& D, int bi)
 }
 
 // ------------------------------------------------------- particle stage of P2G
-// F update from the gradient Lg of the remapped velocities (MUSL), stored with the
-// finite check; a particle whose code changed in this substep's label pass used its
-// previous code for it and drops that mark.
-DEV void store_F(const SceneD& D, long long N, long long p, float dt, const float* Lg, float* H, uint32_t& code)
+// Gradient Lg of the field v(k) at the corners k of a particle's cell.  A zero weight
+// contributes nothing (reading R7); where no particle of the wave has a weight at or near
+// zero along an axis (nearly every wave), no product of three is zero and the tests are
+// left out.  The other waves go over the corners once more, one by one (a second unrolled
+// copy would share its products with the first across the branch, and spill them).
+template <class V>
+DEV void grad_of(const SceneK& S, const float* t, V&& v, float* Lg)
 {
-    bool fin = true;
-    for (int a = 0; a < 9; a++) {
-        H[a] += dt * Lg[a];
-        D.H[at9(N, p, a)] = H[a];
-        fin = fin && isfinite(H[a]);
+    auto add = [&](int k, bool test) {
+        float wx, wy, wz;
+        corner_weights(t, k, wx, wy, wz);
+        const float4 v4 = v(k);
+        float g0 = ((k & 1) ? S.inv_dx : -S.inv_dx) * wy * wz;
+        float g1 = ((k & 2) ? S.inv_dx : -S.inv_dx) * wx * wz;
+        float g2 = ((k & 4) ? S.inv_dx : -S.inv_dx) * wx * wy;
+        if (test && wx * wy * wz == 0.0f) g0 = g1 = g2 = 0.0f;
+        const float va[3] = {v4.x, v4.y, v4.z};
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            Lg[3 * a + 0] = test || k ? Lg[3 * a + 0] + va[a] * g0 : va[a] * g0;
+            Lg[3 * a + 1] = test || k ? Lg[3 * a + 1] + va[a] * g1 : va[a] * g1;
+            Lg[3 * a + 2] = test || k ? Lg[3 * a + 2] + va[a] * g2 : va[a] * g2;
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < 8; k++) add(k, false);
+    const float lo = fminf(fminf(t[0], t[1]), t[2]), hi = fmaxf(fmaxf(t[0], t[1]), t[2]);
+    if (__any(lo < 1e-12f || 1.0f - hi < 1e-12f)) {
+#pragma unroll
+        for (int a = 0; a < 9; a++) Lg[a] = 0.0f;
+#pragma unroll 1
+        for (int k = 0; k < 8; k++) add(k, true);
     }
-    if (!fin) atomicOr(D.status, TL_ST_NONFINITE);
+}
+
+// F update from the gradient Lg of the remapped velocities (MUSL), stored; a particle
+// whose code changed in this substep's label pass used its previous code for it and drops
+// that mark.  A state that is not finite sets the status: here with `check`, else by the
+// stress that follows (no entry of H that is not finite leaves J finite).
+DEV void store_F(const SceneD& D, const Local& loc, int p, float dt, const float* Lg, bool check, float* H,
+                 uint32_t& code)
+{
+#pragma unroll
+    for (int a = 0; a < 9; a++) H[a] += dt * Lg[a];
+    loc.put9(D.H, p, H);
+    if (check) {
+        bool fin = true;
+        for (int a = 0; a < 9; a++) fin = fin && isfinite(H[a]);
+        if (!fin) atomicOr(D.status, TL_ST_NONFINITE);
+    }
     if (code & TL_PREV_BIT) {
         code &= ~TL_PREV_BIT;
-        D.code[p] = code;
+        *loc.one(D.code, p) = code;
     }
 }
 
@@ -662,14 +792,13 @@ DEV void store_F(const SceneD& D, long long N, long long p, float dt, const floa
 // (kept for the substeps whose P2G has no pending update: the first, or after a
 // state read)
 template <int MAT>
-DEV void plastic_rate(const SceneK& S, const SceneD& D, long long N, long long p, bool updated, const float* H,
+DEV void plastic_rate(const SceneK& S, const SceneD& D, const Local& loc, int p, bool updated, const float* H,
                       float* Lg, float* Gp)
 {
     if constexpr (MAT == 1) {
         // plasticity: F_p^{-1} = I + Gp; projection after each F update
         if (S.ystress > 0.0f) {
-#pragma unroll
-            for (int a = 0; a < 9; a++) Gp[a] = D.Gp[at9(N, p, a)];
+            loc.get9(D.Gp, p, Gp);
             if (updated) {
                 float K[9]; // F_e - I = H + Gp + H Gp
 #pragma unroll
@@ -681,20 +810,16 @@ DEV void plastic_rate(const SceneK& S, const SceneD& D, long long N, long long p
                         for (int m = 0; m < 3; m++) k += H[3 * i + m] * Gp[3 * m + j];
                         K[3 * i + j] = k;
                     }
-                const float Ey = S.e_uniform ? S.E0 : D.E[p];
-                if (vm_project(Ey, S.nu, S.ystress, K, Gp))
-#pragma unroll
-                    for (int a = 0; a < 9; a++) D.Gp[at9(N, p, a)] = Gp[a];
+                float mu, lam;
+                lame(S, S.e_uniform ? 0.0f : *loc.one(D.E, p), mu, lam);
+                if (vm_project(mu, S.ystress, K, Gp)) loc.put9(D.Gp, p, Gp);
             }
         }
         if (S.visc > 0.0f) {
-            if (updated) {
-#pragma unroll
-                for (int a = 0; a < 9; a++) D.Fdot[at9(N, p, a)] = Lg[a];
-            } else {
-#pragma unroll
-                for (int a = 0; a < 9; a++) Lg[a] = D.Fdot[at9(N, p, a)];
-            }
+            if (updated)
+                loc.put9(D.Fdot, p, Lg);
+            else
+                loc.get9(D.Fdot, p, Lg);
         }
     }
 }
@@ -706,6 +831,8 @@ DEV void particle_stress(const SceneK& S, const SceneD& D, float E, const float*
                          float* Pk)
 {
     bool ok;
+    float mu, lam;
+    lame(S, E, mu, lam);
     if constexpr (MAT == 1) {
         if (S.ystress > 0.0f) {
             // P = P_fcr(F_e) F_p^{-T}, F_e - I = H + Gp + H Gp, F_p^{-1} = I + Gp
@@ -719,7 +846,7 @@ DEV void particle_stress(const SceneK& S, const SceneD& D, float E, const float*
                     for (int m = 0; m < 3; m++) k += H[3 * i + m] * Gp[3 * m + j];
                     K[3 * i + j] = k;
                 }
-            ok = fixed_corotated(E, S.nu, K, Pe);
+            ok = fixed_corotated(mu, lam, K, Pe);
 #pragma unroll
             for (int i = 0; i < 3; i++)
 #pragma unroll
@@ -730,10 +857,10 @@ DEV void particle_stress(const SceneK& S, const SceneD& D, float E, const float*
                     Pk[3 * i + j] = a;
                 }
         } else {
-            ok = S.material == 1 ? fixed_corotated(E, S.nu, H, Pk) : neo_hookean(E, S.nu, H, Pk);
+            ok = S.material == 1 ? fixed_corotated(mu, lam, H, Pk) : neo_hookean(mu, lam, H, Pk);
         }
     } else {
-        ok = neo_hookean(E, S.nu, H, Pk);
+        ok = neo_hookean(mu, lam, H, Pk);
     }
     if (ok && MAT == 1 && S.visc > 0.0f) add_viscous(S.visc, H, Lg, Pk);
     if (!ok) {
@@ -743,63 +870,65 @@ DEV void particle_stress(const SceneK& S, const SceneD& D, float E, const float*
 }
 
 // What a particle adds to the 8 corners of its cell: w (m, m v) and A grad N + w ext
-// with A = -dt V0 P (Eq. 2); a zero weight contributes nothing (reading R7).
+// with A = -dt V0 P (Eq. 2); a zero weight contributes nothing (reading R7).  Corners in
+// the order of CornerW; the gradient's sign along x and y is that of the lane's own corner
+// on its side and the opposite one on the other.
 struct Scatter {
-    float t[3], A[9], ext[3], vel[3], m, inv_dx;
-    bool valid;
-    // (absolute corners: the CornerW order needs more registers here than the selects
-    // it saves, the impulses also need per-lane gradient signs)
-    DEV void mp(int k, float* o) const // mass and momentum
+    CornerW c;
+    float A[9], ext[3], vel[3], m, inv_dx, sx, sy;
+    DEV void mp(int r, float* o) const // mass and momentum
     {
-        float wx, wy, wz;
-        corner_weights(t, k, wx, wy, wz);
+        const float wx = c.wx[r & 1], wy = c.wy[(r >> 1) & 1], wz = c.wz[r >> 2];
         float wm = wx * wy * wz * m;
         o[0] = wm;
         o[1] = wm * vel[0];
         o[2] = wm * vel[1];
         o[3] = wm * vel[2];
     }
-    DEV void dp(int k, float* o) const // internal, external and contact impulse
+    DEV void dp(int r, float* o) const // internal, external and contact impulse
     {
-        float wx, wy, wz;
-        corner_weights(t, k, wx, wy, wz);
+        const float wx = c.wx[r & 1], wy = c.wy[(r >> 1) & 1], wz = c.wz[r >> 2];
         float w = wx * wy * wz;
-        float g0 = ((k & 1) ? inv_dx : -inv_dx) * wy * wz;
-        float g1 = ((k & 2) ? inv_dx : -inv_dx) * wx * wz;
-        float g2 = ((k & 4) ? inv_dx : -inv_dx) * wx * wy;
-        bool on = valid && w != 0.0f;
+        float g0 = ((r & 1) ? -sx : sx) * wy * wz;
+        float g1 = ((r & 2) ? -sy : sy) * wx * wz;
+        float g2 = ((r & 4) ? inv_dx : -inv_dx) * wx * wy;
 #pragma unroll
         for (int a = 0; a < 3; a++) {
             float f = A[3 * a] * g0 + A[3 * a + 1] * g1 + A[3 * a + 2] * g2 + w * ext[a];
-            o[a] = on ? f : 0.0f;
+            o[a] = w != 0.0f ? f : 0.0f;
         }
+    }
+    // The sums over the cell's particles for the lane's corner: impulses first (their
+    // butterfly then runs while fewer values are live)
+    DEV void sums(int j, float (&d)[3], float (&q)[4]) const
+    {
+        reduce_scatter8<3, true>([&](int r, float* o) { dp(r, o); }, d, j);
+        reduce_scatter8<4, true>([&](int r, float* o) { mp(r, o); }, q, j);
     }
 };
 
-// Stress and external impulses of the lane's particle, ready to scatter
+// Stress and external impulses of the lane's particle, ready to scatter (a lane without
+// a particle adds zeros)
 template <int MAT>
-DEV void scatter_setup(const SceneK& S, const SceneD& D, long long N, long long p, bool valid, bool rig, uint32_t code,
-                       const float* H, const float* Lg, const float* Gp, const float* t, Scatter& C)
+DEV void scatter_setup(const SceneK& S, const SceneD& D, const Local& loc, int p, bool valid, bool rig, uint32_t code,
+                       const float* H, const float* Lg, const float* Gp, const float* t, int j, Scatter& C)
 {
     const float dt = S.dt;
     float m = 0.0f, V0 = 0.0f;
-    C.valid = valid;
+    C.c = corner_table(t, j);
     C.inv_dx = S.inv_dx;
-    for (int a = 0; a < 3; a++) {
-        C.t[a] = t[a];
-        C.vel[a] = C.ext[a] = 0.0f;
-    }
+    C.sx = (j & 1) ? S.inv_dx : -S.inv_dx;
+    C.sy = (j & 2) ? S.inv_dx : -S.inv_dx;
+    for (int a = 0; a < 3; a++) C.vel[a] = C.ext[a] = 0.0f;
     if (valid) {
         // (loaded here, not with the rest: in flight during the stress)
         float jr[3] = {0.0f, 0.0f, 0.0f}, jm[3] = {0.0f, 0.0f, 0.0f};
-        for (int a = 0; a < 3; a++) C.vel[a] = D.v[at3(p, a)];
-        m = S.m_uniform ? S.m0 : D.m[p];
-        V0 = S.v_uniform ? S.V0 : D.V0[p];
-        const float E = S.e_uniform ? S.E0 : D.E[p];
-        if (rig) // floor and tool impulses of this substep (k_rigid)
-            for (int a = 0; a < 3; a++) jr[a] = D.Jrig[at3(p, a)];
-        if (S.material_contact && (code & TL_CAND_BIT))
-            for (int a = 0; a < 3; a++) jm[a] = D.Jmat[at3(p, a)];
+        loc.get(D.v, p, C.vel);
+        m = S.m_uniform ? S.m0 : *loc.one(D.m, p);
+        V0 = S.v_uniform ? S.V0 : *loc.one(D.V0, p);
+        const float E = S.e_uniform ? S.E0 : *loc.one(D.E, p);
+        if (rig) loc.get(D.Jrig, p, jr); // floor and tool impulses of this substep (k_rigid)
+        if (S.material_contact && (code & TL_CAND_BIT)) loc.get(D.Jmat, p, jm);
         particle_stress<MAT>(S, D, E, H, Lg, Gp, C.A);
         C.ext[0] = (jr[0] + jm[0]) + dt * m * S.gx;
         C.ext[1] = (jr[1] + jm[1]) + dt * m * S.gy;
@@ -855,25 +984,36 @@ DEV bool one_code(const SceneK& S, const SceneD& D, int bx, int by, int bz, int&
 // Where node bn finds its sum of class w = (px, py, pz): of the two cells that touch it
 // along an axis one has parity p; place = wave p bits << 6 | lane bits of the cell's i
 // and the corner's j (lane layout of Lane).  Classes without a cell of the brick there
-// read the zero at place TL_WG.
-struct NodePlaces {
-    int x[2], y[2], z[2];
-    DEV void set(int bn)
+// read the zero at place TL_WG.  A table, 16 bytes per node (forming the 8 places took
+// about 60 instructions).
+struct PlaceTable {
+    uint16_t at[TL_WG / 4][8];
+    constexpr PlaceTable() : at()
     {
-        const int X = bn % 5, Y = (bn / 5) % 5, Z = bn / 25;
-#pragma unroll
-        for (int p = 0; p < 2; p++) {
-            const int cx = (X ^ p) & 1, cy = (Y ^ p) & 1, cz = (Z ^ p) & 1; // corner bits
-            const int ax = X - cx, ay = Y - cy, az = Z - cz;                // cells
-            x[p] = (ax < 0 || ax > 3) ? TL_WG : ((ax >> 1) << 2) | cx | (p << 6);
-            y[p] = (ay < 0 || ay > 3) ? TL_WG : ((ay >> 1) << 3) | (cy << 1) | (p << 7);
-            z[p] = (az < 0 || az > 3) ? TL_WG : ((az >> 1) << 5) | (cz << 4) | (p << 8);
-        }
+        for (int bn = 0; bn < TL_WG / 4; bn++)
+            for (int w = 0; w < 8; w++) {
+                const int N[3] = {bn % 5, (bn / 5) % 5, bn / 25};
+                const int cell_bit[3] = {2, 3, 5}, corner_bit[3] = {0, 1, 4};
+                int s = 0;
+                bool in = bn < TL_BOXN;
+                for (int a = 0; a < 3; a++) {
+                    const int p = (w >> a) & 1, c = (N[a] ^ p) & 1, cell = N[a] - c; // corner bit, cell
+                    if (cell < 0 || cell > 3) in = false;
+                    s |= ((cell >> 1) << cell_bit[a]) | (c << corner_bit[a]) | (p << (6 + a));
+                }
+                at[bn][w] = (uint16_t)(in ? s : TL_WG);
+            }
     }
+};
+static __device__ const PlaceTable k_places __attribute__((aligned(16))) = PlaceTable();
+
+struct NodePlaces {
+    uint4 t;
+    DEV void set(int bn) { t = *(const uint4*)k_places.at[bn]; }
     DEV int operator()(int w) const
     {
-        const int s = x[w & 1] + y[(w >> 1) & 1] + z[w >> 2];
-        return s < TL_WG ? s : TL_WG;
+        const uint32_t x = w < 2 ? t.x : w < 4 ? t.y : w < 6 ? t.z : t.w;
+        return (w & 1) ? (int)(x >> 16) : (int)(x & 0xFFFFu);
     }
 };
 
@@ -901,10 +1041,9 @@ DEV void p2g_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int 
                  float* s_part, int* s_rw)
 {
     const int tid = threadIdx.x, bn = tid >> 2, u = tid & 3;
-    const long long N = S.N;
-    const float dt = S.dt;
+    const Local loc(S, D, info.x);
     Contrib con;
-    con.set(S, nb, bn, u);
+    con.set(S, nb, tid);
     Gather<4> G;
     if (fp) G.load(D.rs, con, 0, true);
     Lane L = lane_at(tid);
@@ -915,11 +1054,9 @@ DEV void p2g_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int 
     float t[3] = {0.0f, 0.0f, 0.0f}, H[9];
     uint32_t code = 0;
     auto load_particle = [&]() {
-        const float Xp[3] = {D.X[at3(p, 0)], D.X[at3(p, 1)], D.X[at3(p, 2)]};
-        code = D.code[p];
-#pragma unroll
-        for (int a = 0; a < 9; a++) H[a] = D.H[at9(N, p, a)];
-        frac_of(S, Xp, info.y * TL_B + L.cxl, info.z * TL_B + L.cyl, info.w * TL_B + L.czl, t);
+        loc.get(D.T, p, t);
+        code = *loc.one(D.code, p);
+        loc.get9(D.H, p, H);
     };
     if (valid) load_particle();
     put_rounds(L, s_rw);
@@ -948,34 +1085,16 @@ DEV void p2g_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int 
         const float4* vb = (const float4*)s_v + box_index(L.cxl, L.cyl, L.czl);
         if (valid) {
             if (fp) {
-#pragma unroll
-                for (int k = 0; k < 8; k++) {
-                    float wx, wy, wz;
-                    corner_weights(t, k, wx, wy, wz);
-                    const bool on = wx * wy * wz != 0.0f; // reading R7
-                    const float4 v4 = vb[(k & 1) + 5 * ((k >> 1) & 1) + 25 * (k >> 2)];
-                    float g0 = ((k & 1) ? S.inv_dx : -S.inv_dx) * wy * wz;
-                    float g1 = ((k & 2) ? S.inv_dx : -S.inv_dx) * wx * wz;
-                    float g2 = ((k & 4) ? S.inv_dx : -S.inv_dx) * wx * wy;
-                    if (!on) g0 = g1 = g2 = 0.0f;
-                    const float va[3] = {v4.x, v4.y, v4.z};
-#pragma unroll
-                    for (int a = 0; a < 3; a++) {
-                        Lg[3 * a + 0] += va[a] * g0;
-                        Lg[3 * a + 1] += va[a] * g1;
-                        Lg[3 * a + 2] += va[a] * g2;
-                    }
-                }
-                store_F(D, N, p, dt, Lg, H, code);
+                grad_of(S, t, [&](int k) { return vb[(k & 1) + 5 * ((k >> 1) & 1) + 25 * (k >> 2)]; }, Lg);
+                store_F(D, loc, p, S.dt, Lg, !A.do_p2g, H, code);
             }
-            plastic_rate<MAT>(S, D, N, p, fp, H, Lg, Gp);
+            plastic_rate<MAT>(S, D, loc, p, fp, H, Lg, Gp);
         }
         if (!A.do_p2g) continue;
         Scatter C;
-        scatter_setup<MAT>(S, D, N, p, valid, rig, code, H, Lg, Gp, t, C);
+        scatter_setup<MAT>(S, D, loc, p, valid, rig, code, H, Lg, Gp, t, L.j, C);
         float dp[3], mp[4];
-        reduce_scatter8<3, false>([&](int k, float* o) { C.dp(k, o); }, dp, L.j);
-        reduce_scatter8<4, false>([&](int k, float* o) { C.mp(k, o); }, mp, L.j);
+        C.sums(L.j, dp, mp);
         if (r > 0) lds_barrier(); // the places of the last round have been read
         float4* pl = (float4*)(s_part + tl * 8);
         pl[0] = make_float4(mp[0], mp[1], mp[2], mp[3]);
@@ -1010,7 +1129,7 @@ struct CellSlots {
         w[0] = *(const unsigned long long*)(s_slot + b);
         w[1] = *(const unsigned long long*)(s_slot + b + 16);
     }
-    DEV int operator()(int k) const { return (int)((w[k >> 2] >> (16 * (k & 3))) & 0xFFFFu); }
+    DEV int operator()(int k) const { return (int)(((k & 4 ? w[1] : w[0]) >> (16 * (k & 3))) & 0xFFFFu); }
 };
 
 // Every 8-lane group of a round holds particles of one code (bricks with a mixed cell are
@@ -1111,8 +1230,7 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
     const bool split = SPLIT && grouped && nround > 1 && S.xcap > 0 && D.ctr[3] <= S.xcap;
     const int r0 = part; // first round of this workgroup
     const int tid = threadIdx.x, bn = tid >> 2, u = tid & 3;
-    const long long N = S.N;
-    const float dt = S.dt;
+    const Local loc(S, D, brick);
     const bool use_r = fp; // finalize v~ (tables rs)
     // separate P2G tables, where a label pass changed the codes around (the two buffers
     // agree elsewhere)
@@ -1132,11 +1250,9 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
     float t[3] = {0.0f, 0.0f, 0.0f}, H[9];
     uint32_t code = 0;
     auto load_particle = [&]() {
-        const float Xp[3] = {D.X[at3(p, 0)], D.X[at3(p, 1)], D.X[at3(p, 2)]};
-        code = D.code[p];
-#pragma unroll
-        for (int a = 0; a < 9; a++) H[a] = D.H[at9(N, p, a)];
-        frac_of(S, Xp, info.y * TL_B + L.cxl, info.z * TL_B + L.cyl, info.w * TL_B + L.czl, t);
+        loc.get(D.T, p, t);
+        code = *loc.one(D.code, p);
+        loc.get9(D.H, p, H);
     };
     int mr = 0, mc = 0;
     const int total_r = use_r ? nr.scan(Tr, bn, mr) : 0;
@@ -1148,7 +1264,7 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
     if (bn >= TL_BOXN) mr = mc = 0;
     const long long gid = bn < TL_BOXN ? box_gid(S, bx, by, bz, bn % 5, (bn / 5) % 5, bn / 25) : -1;
     Contrib C;
-    C.set(S, nbv, bn, u);
+    C.set(S, nbv, tid);
     const int cr = tab_count(mr), br = tab_base(mr);
     Gather<4> g0, g1;
     uint32_t pre_r = 0, pre_c = 0;
@@ -1249,36 +1365,16 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
                 cs.w[1] = half(1);
             }
             if (valid) {
-#pragma unroll
-                for (int k = 0; k < 8; k++) {
-                    float wx, wy, wz;
-                    corner_weights(t, k, wx, wy, wz);
-                    const bool on = wx * wy * wz != 0.0f; // reading R7
-                    const int sl = cs(k);
-                    const float4 v4 = vt[sl < TL_BOX_SLOTS ? sl : TL_BOX_SLOTS];
-                    float h0 = ((k & 1) ? S.inv_dx : -S.inv_dx) * wy * wz;
-                    float h1 = ((k & 2) ? S.inv_dx : -S.inv_dx) * wx * wz;
-                    float h2 = ((k & 4) ? S.inv_dx : -S.inv_dx) * wx * wy;
-                    if (!on) h0 = h1 = h2 = 0.0f;
-                    const float va[3] = {v4.x, v4.y, v4.z};
-#pragma unroll
-                    for (int a = 0; a < 3; a++) {
-                        Lg[3 * a + 0] += va[a] * h0;
-                        Lg[3 * a + 1] += va[a] * h1;
-                        Lg[3 * a + 2] += va[a] * h2;
-                    }
-                }
-                store_F(D, N, p, dt, Lg, H, code);
+                grad_of(S, t, [&](int k) { return vt[cs(k) < TL_BOX_SLOTS ? cs(k) : TL_BOX_SLOTS]; }, Lg);
+                store_F(D, loc, p, S.dt, Lg, !A.do_p2g, H, code);
             }
         }
-        if (valid) plastic_rate<MAT>(S, D, N, p, use_r, H, Lg, Gp);
+        if (valid) plastic_rate<MAT>(S, D, loc, p, use_r, H, Lg, Gp);
         if (!A.do_p2g) continue;
         Scatter W;
-        scatter_setup<MAT>(S, D, N, p, valid, rig, code, H, Lg, Gp, t, W);
-        // impulses first: their butterfly then runs while fewer values are live
+        scatter_setup<MAT>(S, D, loc, p, valid, rig, code, H, Lg, Gp, t, L.j, W);
         float dp[3], mp[4];
-        reduce_scatter8<3, false>([&](int k, float* o) { W.dp(k, o); }, dp, L.j);
-        reduce_scatter8<4, false>([&](int k, float* o) { W.mp(k, o); }, mp, L.j);
+        W.sums(L.j, dp, mp);
         float4* pl = (float4*)(s_part + tl * 8);
         pl[0] = make_float4(mp[0], mp[1], mp[2], mp[3]);
         pl[1] = make_float4(dp[0], dp[1], dp[2], 0.0f);
@@ -1301,17 +1397,18 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
 
 // PIC/FLIP update of the lane's particle from the interpolated increments av and ax;
 // joins x^{n+1}, the speed and |u^{n+1} - a| into bb.
-DEV void move_particle(const SceneK& S, const SceneD& D, long long N, long long p, const float* Xp, const float* v,
+DEV void move_particle(const SceneK& S, const SceneD& D, const Local& loc, int p, const float* Xp, const float* v,
                        const float* u, const float* av, const float* ax, const float* ap, float* vn1, float* bb)
 {
     const float dt = S.dt, beta = S.beta;
+    float *vo = loc.row(D.v, p), *uo = loc.row(D.u, p);
     for (int a = 0; a < 3; a++) {
         vn1[a] = beta * v[a] + av[a];
         float un = u[a] + dt * ax[a];
-        D.v[at3(p, a)] = vn1[a];
-        D.u[at3(p, a)] = un;
+        vo[a] = vn1[a];
+        uo[a] = un;
         float xa = Xp[a] + un;
-        bb[a] = fminf(bb[a], xa);
+        bb[a] = fmaxf(bb[a], -xa);
         bb[3 + a] = fmaxf(bb[3 + a], xa);
         bb[7] = fmaxf(bb[7], fabsf(un - ap[a]));
     }
@@ -1325,22 +1422,30 @@ DEV void put_box(const SceneK& S, const SceneD& D, int bi, int brick, int part, 
                  const float* bb, float (*s_bb)[8])
 {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    // maxima of 8 values over 64 lanes: three stages that halve the values a lane keeps
+    // (its bit chooses which half, the partner gets the other), then three on the one left
+    float m4[4], m2[2];
 #pragma unroll
-    for (int q = 0; q < 8; q++) {
-        if (q == 7 && !track) break;
-        float val = bb[q];
-        auto mm = [&](float other) { val = (q < 3) ? fminf(val, other) : fmaxf(val, other); };
-        mm(lane_xor<1>(val));
-        mm(lane_xor<2>(val));
-        mm(lane_xor<4>(val));
-        for (int o = 8; o <= 32; o <<= 1) mm(__shfl_xor(val, o, 64));
-        if (lane == 0) s_bb[w][q] = val;
+    for (int q = 0; q < 4; q++) {
+        const float send = (lane & 1) ? bb[q] : bb[q + 4], keep = (lane & 1) ? bb[q + 4] : bb[q];
+        m4[q] = fmaxf(keep, lane_xor<1>(send));
     }
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        const float send = (lane & 2) ? m4[q] : m4[q + 2], keep = (lane & 2) ? m4[q + 2] : m4[q];
+        m2[q] = fmaxf(keep, lane_xor<2>(send));
+    }
+    float m = fmaxf((lane & 4) ? m2[1] : m2[0], lane_xor<4>((lane & 4) ? m2[0] : m2[1]));
+    // lane bits 0, 1, 2 now hold value 4 b0 + 2 b1 + b2
+    m = fmaxf(m, __shfl_xor(m, 8, 64));
+    m = fmaxf(m, __shfl_xor(m, 16, 64));
+    m = fmaxf(m, __shfl_xor(m, 32, 64));
+    if (lane < 8) s_bb[w][((lane & 1) << 2) | (lane & 2) | (lane >> 2)] = m;
     lds_barrier();
     if (tid < 7) {
         float val = s_bb[0][tid];
-        for (int wv = 1; wv < 8; wv++) val = (tid < 3) ? fminf(val, s_bb[wv][tid]) : fmaxf(val, s_bb[wv][tid]);
-        (part ? D.aabb_x : D.aabb)[(long long)brick * 8 + tid] = val;
+        for (int wv = 1; wv < 8; wv++) val = fmaxf(val, s_bb[wv][tid]);
+        (part ? D.aabb_x : D.aabb)[(long long)brick * 8 + tid] = tid < 3 ? -val : val;
         // the next binning's bin edge needs the largest speed bound; the maximum
         // of non-negative floats is taken on their bit patterns (order-independent)
         if (tid == 6 && S.material_contact && val > 0.0f)
@@ -1359,10 +1464,10 @@ DEV void g2p_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int 
                  float* s_g, float* s_part, int* s_rw, float (*s_bb)[8])
 {
     const int tid = threadIdx.x, bn = tid >> 2, u4 = tid & 3;
-    const long long N = S.N;
+    const Local loc(S, D, info.x);
     const float beta = S.beta;
     Contrib con;
-    con.set(S, nb, bn, u4);
+    con.set(S, nb, tid);
     Gather<8> G;
     G.load(D.p2g, con, 0, true);
     Lane L = lane_at(tid);
@@ -1371,11 +1476,9 @@ DEV void g2p_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int 
     bool valid = lane_particle(D, bi, false, L, 0, p);
     float Xp[3] = {0.0f, 0.0f, 0.0f}, v[3] = {0.0f, 0.0f, 0.0f}, u[3] = {0.0f, 0.0f, 0.0f};
     auto load_particle = [&]() {
-        for (int a = 0; a < 3; a++) {
-            Xp[a] = D.X[at3(p, a)];
-            v[a] = D.v[at3(p, a)];
-            u[a] = D.u[at3(p, a)];
-        }
+        loc.get(D.X, p, Xp);
+        loc.get(D.v, p, v);
+        loc.get(D.u, p, u);
     };
     if (valid) load_particle();
     put_rounds(L, s_rw);
@@ -1395,9 +1498,9 @@ DEV void g2p_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int 
     lds_barrier();
     const int rounds = get_rounds(s_rw);
     float sum = 0.0f;
-    // box of x^{n+1}, speed bound, and the largest |u^{n+1} - a| about the anchor a
+    // box of x^{n+1} (its lower faces negated), speed bound, and the largest |u^{n+1} - a| about the anchor a
     // (for the pair-search skip)
-    float bb[8] = {1e30f, 1e30f, 1e30f, -1e30f, -1e30f, -1e30f, 0.0f, 0.0f};
+    float bb[8] = {-1e30f, -1e30f, -1e30f, -1e30f, -1e30f, -1e30f, 0.0f, 0.0f};
     for (int r = 0; r < rounds; r++) {
         const int tl = late(tid);
         L = lane_at(tl);
@@ -1426,8 +1529,8 @@ DEV void g2p_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int 
                 ax[1] += w * fx.y;
                 ax[2] += w * fx.z;
             }
-            move_particle(S, D, N, p, Xp, v, u, av, ax, ap, vn1, bb);
-            m = S.m_uniform ? S.m0 : D.m[p];
+            move_particle(S, D, loc, p, Xp, v, u, av, ax, ap, vn1, bb);
+            m = S.m_uniform ? S.m0 : *loc.one(D.m, p);
         }
         const float mm = valid ? m : 0.0f;
         const CornerW cw = corner_table(t, L.j);
@@ -1507,7 +1610,7 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
     const bool split = grouped && nround > 1 && xsplit;
     const int r0 = part;
     const int tid = threadIdx.x, bn = tid >> 2, u4 = tid & 3;
-    const long long N = S.N;
+    const Local loc(S, D, brick);
     const float beta = S.beta;
 
     // ---- phase 1: counts, cell index, codes and partials of the own node, particle loads
@@ -1520,12 +1623,10 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
     float Xp[3] = {0.0f, 0.0f, 0.0f}, v[3] = {0.0f, 0.0f, 0.0f}, u[3] = {0.0f, 0.0f, 0.0f};
     uint32_t code = 0;
     auto load_particle = [&]() {
-        for (int a = 0; a < 3; a++) {
-            Xp[a] = D.X[at3(p, a)];
-            v[a] = D.v[at3(p, a)];
-            u[a] = D.u[at3(p, a)];
-        }
-        code = D.code[p];
+        loc.get(D.X, p, Xp);
+        loc.get(D.v, p, v);
+        loc.get(D.u, p, u);
+        code = *loc.one(D.code, p);
     };
     int mt = 0;
     const int total = nc.scan(T, bn, mt);
@@ -1537,7 +1638,7 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
     const int c = tab_count(mt), b0 = tab_base(mt);
     const long long gid = bn < TL_BOXN ? box_gid(S, bx, by, bz, bn % 5, (bn / 5) % 5, bn / 25) : -1;
     Contrib C;
-    C.set(S, nbv, bn, u4);
+    C.set(S, nbv, tid);
     const uint32_t pre = codes_pre(S, D.scode[cur], mt, gid, u4);
     Gather<8> g0, g1;
     g0.load(D.p2g, C, 0, c > 0);
@@ -1592,9 +1693,9 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
     lds_barrier();
     const int rounds = (split && part == 0) ? 1 : grouped ? D.bround[bi] : get_rounds(s_rw);
     const float4* const gr = (const float4*)s_grid;
-    // box of x^{n+1}, speed bound, and the largest |u^{n+1} - a| about the anchor a
+    // box of x^{n+1} (its lower faces negated), speed bound, and the largest |u^{n+1} - a| about the anchor a
     // (for the pair-search skip)
-    float bb[8] = {1e30f, 1e30f, 1e30f, -1e30f, -1e30f, -1e30f, 0.0f, 0.0f};
+    float bb[8] = {-1e30f, -1e30f, -1e30f, -1e30f, -1e30f, -1e30f, 0.0f, 0.0f};
     for (int r = r0; r < rounds; r++) {
         const int tl = late(tid);
         L = lane_at(tl);
@@ -1631,8 +1732,8 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
                 ax[1] += w * fx.y;
                 ax[2] += w * fx.z;
             }
-            move_particle(S, D, N, p, Xp, v, u, av, ax, ap, vn1, bb);
-            m = S.m_uniform ? S.m0 : D.m[p];
+            move_particle(S, D, loc, p, Xp, v, u, av, ax, ap, vn1, bb);
+            m = S.m_uniform ? S.m0 : *loc.one(D.m, p);
         }
         const float mm = valid ? m : 0.0f;
         const CornerW cw = corner_table(t, L.j);
@@ -2187,13 +2288,9 @@ __global__ __launch_bounds__(256) void k_labels_rigid_b(const SceneK* __restrict
 // workgroup (at most S.xcap of them); otherwise every brick keeps all its rounds, so
 // the results do not depend on the order of xlist.  Block b -> (active index, part);
 // -1: nothing to do.
-DEV int brick_of_block(const SceneK& S, const SceneD& D, int b, int j, int& part)
+// Brick of workgroup j of the split launches (j < S.xcap, part 1); -1: nothing to do
+DEV int split_brick(const SceneK& S, const SceneD& D, int j)
 {
-    if (j < 0) {
-        part = 0;
-        return b;
-    }
-    part = 1;
     const int count = D.ctr[3];
     return (j < count && count <= S.xcap) ? D.xlist[j] : -1;
 }
@@ -2205,14 +2302,10 @@ __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(MAT == 0 
                                                                                                      SceneD D,
                                                                                                      KA_Args A)
 {
-    const int b = blockIdx.x;
-    if constexpr (!SPLIT) {
-        p2g_body<MAT, false>(S, D, b, A, 0);
-    } else {
-        int part;
-        const int bi = brick_of_block(S, D, b - S.xcap, b < S.xcap ? b : -1, part);
-        if (bi >= 0) p2g_body<MAT, true>(S, D, bi, A, part);
-    }
+    const int b = blockIdx.x, nx = SPLIT ? S.xcap : 0;
+    const int bi = SPLIT && b < nx ? split_brick(S, D, b) : b - nx;
+    if (SPLIT && bi < 0) return;
+    p2g_body<MAT, SPLIT>(S, D, bi, A, SPLIT && b < nx);
 }
 template <int MAT, bool SPLIT>
 __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(MAT == 0 ? 6 : 4))) void k_p2g_b(
@@ -2220,43 +2313,33 @@ __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(MAT == 0 
     const int2* __restrict__ xit, int nx, KA_Args A)
 {
     const int b = blockIdx.x;
-    if constexpr (!SPLIT) {
-        const int2 t = it[xcd_order(b, gridDim.x)];
-        p2g_body<MAT, false>(Ks[t.x], Ds[t.x], t.y, A, 0);
-    } else {
-        const int2 t = b < nx ? xit[b] : it[xcd_order(b - nx, gridDim.x - nx)];
-        int part;
-        const int bi = brick_of_block(Ks[t.x], Ds[t.x], t.y, b < nx ? t.y : -1, part);
-        if (bi >= 0) p2g_body<MAT, true>(Ks[t.x], Ds[t.x], bi, A, part);
-    }
+    const int2 t = SPLIT && b < nx ? xit[b] : it[xcd_order(b - (SPLIT ? nx : 0), gridDim.x - (SPLIT ? nx : 0))];
+    const SceneK& S = Ks[t.x];
+    const SceneD& D = Ds[t.x];
+    const int bi = SPLIT && b < nx ? split_brick(S, D, t.y) : t.y;
+    if (SPLIT && bi < 0) return;
+    p2g_body<MAT, SPLIT>(S, D, bi, A, SPLIT && b < nx);
 }
 template <bool SPLIT>
 __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(6))) void k_g2p(SceneK S, SceneD D, int cur)
 {
-    const int b = blockIdx.x;
-    if constexpr (!SPLIT) {
-        g2p_body<false>(S, D, b, cur, 0);
-    } else {
-        int part;
-        const int bi = brick_of_block(S, D, b - S.xcap, b < S.xcap ? b : -1, part);
-        if (bi >= 0) g2p_body<true>(S, D, bi, cur, part);
-    }
+    const int b = blockIdx.x, nx = SPLIT ? S.xcap : 0;
+    const int bi = SPLIT && b < nx ? split_brick(S, D, b) : b - nx;
+    if (SPLIT && bi < 0) return;
+    g2p_body<SPLIT>(S, D, bi, cur, SPLIT && b < nx);
 }
 template <bool SPLIT>
-__global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(6))) void k_g2p_b(const SceneK* __restrict__ Ks, const SceneD* __restrict__ Ds,
-                                                 const int2* __restrict__ it, const int2* __restrict__ xit, int nx,
-                                                 int cur)
+__global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(6))) void k_g2p_b(
+    const SceneK* __restrict__ Ks, const SceneD* __restrict__ Ds, const int2* __restrict__ it,
+    const int2* __restrict__ xit, int nx, int cur)
 {
     const int b = blockIdx.x;
-    if constexpr (!SPLIT) {
-        const int2 t = it[xcd_order(b, gridDim.x)];
-        g2p_body<false>(Ks[t.x], Ds[t.x], t.y, cur, 0);
-    } else {
-        const int2 t = b < nx ? xit[b] : it[xcd_order(b - nx, gridDim.x - nx)];
-        int part;
-        const int bi = brick_of_block(Ks[t.x], Ds[t.x], t.y, b < nx ? t.y : -1, part);
-        if (bi >= 0) g2p_body<true>(Ks[t.x], Ds[t.x], bi, cur, part);
-    }
+    const int2 t = SPLIT && b < nx ? xit[b] : it[xcd_order(b - (SPLIT ? nx : 0), gridDim.x - (SPLIT ? nx : 0))];
+    const SceneK& S = Ks[t.x];
+    const SceneD& D = Ds[t.x];
+    const int bi = SPLIT && b < nx ? split_brick(S, D, t.y) : t.y;
+    if (SPLIT && bi < 0) return;
+    g2p_body<SPLIT>(S, D, bi, cur, SPLIT && b < nx);
 }
 
 // ------------------------------------------------------------------- launchers
@@ -2384,6 +2467,13 @@ hipError_t tl_launch_resetD(const TlLaunch* L)
 hipError_t tl_launch_call_start(const TlLaunch* L)
 {
     return tl_run(*L, IT_SCENE, L->S ? 1 : 0, 64, k_call_start, k_call_start_b);
+}
+
+hipError_t tl_launch_frac(const SceneK* S, const SceneD* D, hipStream_t st)
+{
+    if (S->N <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_frac, dim3(blocks_of(S->N, 256)), dim3(256), 0, st, *S, *D);
+    return hipGetLastError();
 }
 
 hipError_t tl_launch_export(const TlLaunch* L, const TlExport* E, void* out, int o0, int o1, int max_cuts)

@@ -377,7 +377,8 @@ __global__ __launch_bounds__(TL_QWG) void k_q_p2g(SceneK S, SceneD D, int par)
             for (int a = 0; a < 3; a++) vel[a] = D.v[at3(p, a)];
             m = S.m_uniform ? S.m0 : D.m[p];
             const float V0 = S.v_uniform ? S.V0 : D.V0[p];
-            const float E = S.e_uniform ? S.E0 : D.E[p];
+            float mu, lam;
+            lame(S, S.e_uniform ? 0.0f : D.E[p], mu, lam);
             bool ok;
             if constexpr (MAT == 1) {
                 if (S.ystress > 0.0f) {
@@ -394,7 +395,7 @@ __global__ __launch_bounds__(TL_QWG) void k_q_p2g(SceneK S, SceneD D, int par)
                             for (int l = 0; l < 3; l++) kk += H[3 * i + l] * Gp[3 * l + j];
                             K[3 * i + j] = kk;
                         }
-                    ok = fixed_corotated(E, S.nu, K, Pe);
+                    ok = fixed_corotated(mu, lam, K, Pe);
 #pragma unroll
                     for (int i = 0; i < 3; i++)
 #pragma unroll
@@ -405,7 +406,7 @@ __global__ __launch_bounds__(TL_QWG) void k_q_p2g(SceneK S, SceneD D, int par)
                             Pk[3 * i + j] = a;
                         }
                 } else {
-                    ok = S.material == 1 ? fixed_corotated(E, S.nu, H, Pk) : neo_hookean(E, S.nu, H, Pk);
+                    ok = S.material == 1 ? fixed_corotated(mu, lam, H, Pk) : neo_hookean(mu, lam, H, Pk);
                 }
                 if (ok && S.visc > 0.0f) {
                     float Fd[9];
@@ -414,7 +415,7 @@ __global__ __launch_bounds__(TL_QWG) void k_q_p2g(SceneK S, SceneD D, int par)
                     add_viscous(S.visc, H, Fd, Pk);
                 }
             } else {
-                ok = neo_hookean(E, S.nu, H, Pk);
+                ok = neo_hookean(mu, lam, H, Pk);
             }
             if (!ok) {
                 atomicOr(D.status, TL_ST_NONFINITE);
@@ -851,8 +852,9 @@ __global__ __launch_bounds__(TL_QWG) void k_q_F(SceneK S, SceneD D, int par)
                         for (int l = 0; l < 3; l++) kk += H[3 * i + l] * Gp[3 * l + j];
                         K[3 * i + j] = kk;
                     }
-                const float E = S.e_uniform ? S.E0 : D.E[p];
-                if (vm_project(E, S.nu, S.ystress, K, Gp))
+                float mu, lam;
+                lame(S, S.e_uniform ? 0.0f : D.E[p], mu, lam);
+                if (vm_project(mu, S.ystress, K, Gp))
 #pragma unroll
                     for (int a = 0; a < 9; a++) D.Gp[at9(N, p, a)] = Gp[a];
             }

@@ -78,3 +78,35 @@ def test_one_code_and_several(tl, n_cells, dense, kind):
     assert np.array_equal(a["digits"], dig)
     eu, ev, eH = state_errs(a, b, s["X"], s["params"])
     assert eu < TOL and ev < TOL and eH < TOL, (eu, ev, eH)
+
+
+@pytest.mark.parametrize("kind", ["none", "inside"])
+@pytest.mark.parametrize("planes", [1, 2, 3])
+def test_particles_on_grid_planes(tl, planes, kind):
+    """Particles exactly on grid planes (zero weights along 1 to 3 axes: those corners
+    take no part in any sum or gradient), mixed with ordinary ones; dx is a power of two,
+    so that the positions are exact."""
+    dx = 2.0 ** -7
+    s = W.box_scene(n_cells=(6, 5, 4), dx=dx, seed=33, floor_on=0, slot_capacity=8)
+    X = s["X"].astype(np.float64)
+    n = X.shape[0]
+    rng = np.random.default_rng([34, planes])
+    some = rng.random(n) < 0.3
+    for a in range(planes):  # to the lower plane of the particle's cell
+        X[some, a] = np.floor(X[some, a] / dx) * dx
+    s["X"] = X.astype(np.float32)
+    dig = _digits(kind, X, dx, rng)
+    F = (np.eye(3)[None] + 0.03 * rng.normal(size=(n, 3, 3))).astype(np.float32)
+    v = (rng.normal(size=(n, 3)) * 0.1).astype(np.float32)
+    print(f"[case] on grid planes {planes} {kind} n={n}", flush=True)
+    g = tl.Scene(s)
+    g.write(v=v, F=F, digits=dig)
+    o = oracle.OracleScene(s)
+    o.set(v=v, F=F.reshape(n, 9), digits=dig)
+    for _ in range(STEPS):
+        g.step([])
+        o.step([])
+    assert g.status() == 0
+    a, b = g.read(("u", "v", "H")), o.get()
+    eu, ev, eH = state_errs(a, b, s["X"], s["params"])
+    assert eu < TOL and ev < TOL and eH < TOL, (eu, ev, eH)
