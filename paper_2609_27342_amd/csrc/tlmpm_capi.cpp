@@ -238,7 +238,7 @@ Dims dims_of(const tlmpm_scene_desc* d)
 }
 
 struct Offsets {
-    size_t X, T, u, v, H, code, code_prev, D, perm, E, m, V0, cell_start, active, binfo, bkey, cnt0, cnt1, sc0, sc1, p2g, rs, p2g_x,
+    size_t tstamp, X, T, u, v, H, code, code_prev, D, perm, E, m, V0, cell_start, active, binfo, bkey, cnt0, cnt1, sc0, sc1, p2g, rs, p2g_x,
         rs_x, xp2g, xrs, aabb_x, xlist, xin, xg, hist,
         aabb, wpart, Fdot, Gp, wacc, Jmat, Jrig, brig, bmixed, ccode, ckeys, gmeta, gperm, bround, tools, tinfo, ctr, bact, status, dirty, bdirty, pcell, cand_idx, coff, cmask, cstatic, bcand, hbin, hmax, uanc, uanc_x, uref, bor, umm,
         bcount, bids, crec, htab, hnext, ph_n, ph_q, ph_u,
@@ -340,6 +340,7 @@ Offsets plan(const tlmpm_scene_desc* d, long long n_active)
     const size_t scap = slot_cap(d);
     o.sc0 = L.take((size_t)g.NN * scap * 4);
     o.sc1 = L.take((size_t)g.NN * scap * 4);
+    o.tstamp = L.take(2 * 4);
     o.p2g = L.take((size_t)n_active * scap * TL_BOXN * 8 * f); // 7 components padded to 8
     o.rs = L.take((size_t)n_active * scap * TL_BOXN * 4 * f);
     o.p2g_x = L.take((size_t)n_active * scap * TL_BOXN * 8 * f);
@@ -640,6 +641,7 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     D.cnt[1] = (uint8_t*)(base + o.cnt1);
     D.scode[0] = (uint32_t*)(base + o.sc0);
     D.scode[1] = (uint32_t*)(base + o.sc1);
+    D.tstamp = (int*)(base + o.tstamp);
     D.p2g = (float*)(base + o.p2g);
     D.rs = (float*)(base + o.rs);
     D.p2g_x = (float*)(base + o.p2g_x);
@@ -813,6 +815,7 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     const TlLaunch L = single_launch(sc);
     if ((e = tl_launch_mixed(&L, 1)) != hipSuccess) return bail(e, "cell summaries");
     if ((e = tl_launch_slots(&L, 0, 0, 1)) != hipSuccess) return bail(e, "slot table");
+    if ((e = tl_launch_fill_i32(D.tstamp + 1, 1, -1, sc->st)) != hipSuccess) return bail(e, "slot table"); // not built
     if ((e = tl_launch_aabb(&L)) != hipSuccess) return bail(e, "aabb");
     if (d->material_contact) {
         if ((e = tl_launch_cellmask(&L, 1, 1)) != hipSuccess) return bail(e, "cell masks");
@@ -1447,6 +1450,8 @@ extern "C" tlmpm_status tlmpm_write_state(tlmpm_scene* sc, uint32_t mask, const 
         HIPCHK(tl_launch_fill_i32(sc->D.ctr + 3, 1, 0, sc->st));
         HIPCHK(tl_launch_mixed(&L, 1));
         HIPCHK(tl_launch_slots(&L, sc->cur, sc->cur, 1));
+        // (these changes carry no stamp: the other buffer is copied whole when it is next built)
+        HIPCHK(tl_launch_fill_i32(sc->D.tstamp + (1 - sc->cur), 1, -1, sc->st));
         sc->rsb = sc->cur;
         if (sc->K.material_contact) HIPCHK(tl_launch_cand(&L, 1));
     }

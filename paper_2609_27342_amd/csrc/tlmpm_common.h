@@ -129,6 +129,7 @@ struct SceneD {
     int n_active;
     uint8_t* cnt[2];
     uint32_t* scode[2];
+    int* tstamp;   // [2] each slot-table buffer holds the label changes up to this substep stamp
     float* p2g;    // [active brick][scap][125 box nodes][8]: each brick's P2G box sums
     float* rs;     // [active brick][scap][125 box nodes][4]: each brick's re-scatter box sums
     float* p2g_x;  // the same two for the later same-code rounds of a split brick

@@ -1581,6 +1581,7 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
         // end of the substep for this scene: next history stamp, F update pending
         // (no other kernel of the substep reads these after this point); whether this
         // G2P splits its mixed bricks (read by the next P2G and box tests)
+        D.tstamp[cur] = D.ctr[0]; // (the slot tables in use are up to date)
         D.ctr[0] += 1;
         D.ctr[1] = 1;
         D.ctr[2] += 1;

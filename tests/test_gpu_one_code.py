@@ -110,3 +110,32 @@ def test_particles_on_grid_planes(tl, planes, kind):
     a, b = g.read(("u", "v", "H")), o.get()
     eu, ev, eH = state_errs(a, b, s["X"], s["params"])
     assert eu < TOL and ev < TOL and eH < TOL, (eu, ev, eH)
+
+
+@pytest.mark.parametrize("n_codes", [1, 2, 4, 5, 7])
+def test_slot_tables(tl, n_codes):
+    """Slots per node against a count of the distinct codes of its 8 cells: up to the four
+    that are kept in registers, and beyond; in both tables, unchanged and rewritten."""
+    s = _scene((6, 5, 9), False, 35)
+    rng = np.random.default_rng([36, n_codes])
+    X, p = s["X"].astype(np.float64), s["params"]
+    n = X.shape[0]
+    cell = np.floor((X - np.asarray(p["origin"], np.float64)) / p["dx"]).astype(int)
+    codes = np.array([[a, b, 0, 0] for a in range(3) for b in range(3)], np.uint8)[:n_codes]
+
+    def expected(dig):
+        seen = {}
+        for c, k in zip(cell, dig[:, 0].astype(int) * 3 + dig[:, 1]):
+            for d in np.ndindex(2, 2, 2):
+                seen.setdefault(tuple(c + d), set()).add(k)
+        return np.bincount([len(v) for v in seen.values()], minlength=17)[1:17]
+
+    print(f"[case] slot tables codes={n_codes} n={n}", flush=True)
+    g = tl.Scene(s)
+    for every in (1.0, 0.3, 0.0):  # all particles of mixed codes, some, none
+        dig = codes[np.where(rng.random(n) < every, rng.integers(0, n_codes, n), 0)]
+        g.write(digits=dig)
+        for _ in range(3):
+            assert list(g.slot_histogram()[1:]) == list(expected(dig))
+            g.step([])
+        assert g.status() == 0
