@@ -238,7 +238,7 @@ Dims dims_of(const tlmpm_scene_desc* d)
 }
 
 struct Offsets {
-    size_t tstamp, X, T, u, v, H, code, code_prev, D, perm, E, m, V0, cell_start, active, binfo, bkey, cnt0, cnt1, sc0, sc1, p2g, rs, p2g_x,
+    size_t tstamp, X, T, u, v, H, code, code_prev, D, perm, E, m, V0, cell_start, active, binfo, ball, bkey, cnt0, cnt1, sc0, sc1, p2g, rs, p2g_x,
         rs_x, xp2g, xrs, aabb_x, xlist, xin, xg, hist,
         aabb, wpart, Fdot, Gp, wacc, Jmat, Jrig, brig, bmixed, ccode, ckeys, gmeta, gperm, bround, tools, tinfo, ctr, bact, status, dirty, bdirty, pcell, cand_idx, coff, cmask, cstatic, bcand, hbin, hmax, uanc, uanc_x, uref, bor, umm,
         bcount, bids, crec, htab, hnext, ph_n, ph_q, ph_u,
@@ -334,6 +334,7 @@ Offsets plan(const tlmpm_scene_desc* d, long long n_active)
     o.cell_start = L.take(((size_t)g.n_bricks * TL_CELLS + 1) * 4);
     o.active = L.take((size_t)g.n_bricks * 4);
     o.binfo = L.take((size_t)n_active * sizeof(int4));
+    o.ball = L.take((size_t)g.n_bricks * 4);
     o.bkey = L.take((size_t)g.n_bricks * 4);
     o.cnt0 = L.take((size_t)g.NN);
     o.cnt1 = L.take((size_t)g.NN);
@@ -636,6 +637,7 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     D.active = (int*)(base + o.active);
     D.n_active = (int)active.size();
     D.binfo = (int4*)(base + o.binfo);
+    D.ball = (uint32_t*)(base + o.ball);
     D.bkey = (uint32_t*)(base + o.bkey);
     D.cnt[0] = (uint8_t*)(base + o.cnt0);
     D.cnt[1] = (uint8_t*)(base + o.cnt1);

@@ -125,6 +125,7 @@ struct SceneD {
     int* cell_start;   // [n_bricks*64 + 1]
     int* active;       // active brick ids
     int4* binfo;       // [active brick] brick id and its brick coordinates x, y, z
+    uint32_t* ball;    // [bricks] cuts (bits) for which every particle of the brick holds a digit
     uint32_t* bkey;    // [bricks] the one slot key of a brick's particles, or TL_CC_MIXED
     int n_active;
     uint8_t* cnt[2];

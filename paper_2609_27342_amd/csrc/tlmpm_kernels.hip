@@ -646,88 +646,136 @@ struct KA_Args {
 // Floor and tool contact of every particle of bricks whose AABB can reach a rigid
 // body this substep (Eqs. 14-16, 5): impulses to Jrig, cutting progress D, contact
 // springs, and per-brick wrench sums added to those of the call (wave tree, then
-// waves in order).
-DEV void rigid_body(const SceneK& S, const SceneD& D, int bi)
+// waves in order).  Bound by the FP64 chain per particle and the loads around it where
+// a body is near, by the number of workgroups elsewhere.
+#define TL_GROUP 16   // most bricks per workgroup of these passes
+#define TL_BODIES (TL_MAX_TOOLS + 1)
+
+// Rigid contact of a brick within reach of the bodies of mask `near` (bit 0 the floor, bit
+// 1 + b tool b), whole block.
+DEV void rigid_brick(const SceneK& S, const SceneD& D, int bi, int brick, int near)
 {
-    if (!S.floor_on && !D.tinfo[1]) return; // no rigid body touches this scene
+    __shared__ float s_wr[4][TL_MAX_TOOLS * 6];
     const int n_tools = D.tinfo[0];
     const int stamp = D.ctr[0];
     const double jdt = (double)D.ctr[2] * S.dt_d; // substep of the call (TL_TOOL_ADVANCE poses)
-    __shared__ int s_near[TL_MAX_TOOLS + 1];
-    __shared__ int s_any;
-    __shared__ float s_wr[4][TL_MAX_TOOLS * 6];
-    const int brick = D.active[bi];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const long long N = S.N;
-    if (tid <= TL_MAX_TOOLS) {
-        float bb[7];
-        brick_aabb(S, D, bi, brick, bb);
-        int nr = 0;
-        if (tid == 0)
-            nr = S.floor_on ? brick_near_floor(bb, S.floor_z, S.Rmax, S.dt) : 0;
-        else if (tid - 1 < n_tools)
-            nr = (D.tools[tid - 1].flags & TL_TOOL_CONTACT) ? brick_near_tool(bb, D.tools[tid - 1], S.Rmax, S.dt, jdt)
-                                                             : 0;
-        s_near[tid] = nr;
-    }
-    if (lane < TL_MAX_TOOLS * 6) s_wr[wv][lane] = 0.0f;
-    __syncthreads();
-    if (tid == 0) {
-        int any = 0;
-        for (int b = 0; b <= n_tools; b++) any |= s_near[b];
-        s_any = any;
-        D.brig[brick] = any;
-    }
-    __syncthreads();
     const bool want_wrench = D.tinfo[1] != 0;
-    if (s_any) {
-        const int beg = D.cell_start[(long long)brick * TL_CELLS], end = D.cell_start[(long long)(brick + 1) * TL_CELLS];
-        for (int p0 = beg; p0 < end; p0 += blockDim.x) {
-            const int p = p0 + tid;
-            const bool valid = p < end;
-            double x[3] = {0.0, 0.0, 0.0};
-            float v[3] = {0.0f, 0.0f, 0.0f}, m = 0.0f, V0 = 0.0f, R = 0.0f, Dp = 0.0f;
-            float Jc[3] = {0.0f, 0.0f, 0.0f};
-            if (valid) {
-                for (int a = 0; a < 3; a++) {
-                    x[a] = (double)D.X[at3(p, a)] + (double)D.u[at3(p, a)];
-                    v[a] = D.v[at3(p, a)];
-                }
-                m = S.m_uniform ? S.m0 : D.m[p];
-                V0 = S.v_uniform ? S.V0 : D.V0[p];
-                R = 0.5f * S.s_R * cbrtf(V0);
-                Dp = D.D[p];
-                if (s_near[0]) rigid_one(S, D, nullptr, 0, p, x, v, m, V0, R, stamp, jdt, Jc, Dp, Dp, nullptr);
+    const int beg = D.cell_start[(long long)brick * TL_CELLS], end = D.cell_start[(long long)(brick + 1) * TL_CELLS];
+    if (lane < TL_MAX_TOOLS * 6) s_wr[wv][lane] = 0.0f;
+    for (int p0 = beg; p0 < end; p0 += 256) {
+        const int p = p0 + tid;
+        const bool valid = p < end;
+        double x[3] = {0.0, 0.0, 0.0};
+        float v[3] = {0.0f, 0.0f, 0.0f}, m = 0.0f, V0 = 0.0f, R = 0.0f, Dp = 0.0f;
+        float Jc[3] = {0.0f, 0.0f, 0.0f};
+        if (valid) {
+            for (int a = 0; a < 3; a++) {
+                x[a] = (double)D.X[at3(p, a)] + (double)D.u[at3(p, a)];
+                v[a] = D.v[at3(p, a)];
             }
-            const float Ds = valid ? D.D[p] : 0.0f;
-            for (int b = 0; b < n_tools; b++) {
-                if (!s_near[b + 1]) continue;
-                float wr[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-                if (valid) rigid_one(S, D, &D.tools[b], 1 + b, p, x, v, m, V0, R, stamp, jdt, Jc, Dp, Ds, wr);
-                bool nz = wr[0] != 0.0f || wr[1] != 0.0f || wr[2] != 0.0f;
-                if (want_wrench && __any(nz)) {
-                    for (int q = 0; q < 6; q++) {
-                        float val = wr[q];
-                        for (int o = 32; o >= 1; o >>= 1) val += __shfl_xor(val, o, 64);
-                        if (lane == 0) s_wr[wv][b * 6 + q] += val;
-                    }
+            m = S.m_uniform ? S.m0 : D.m[p];
+            V0 = S.v_uniform ? S.V0 : D.V0[p];
+            R = 0.5f * S.s_R * cbrtf(V0);
+            Dp = D.D[p];
+        }
+        const float Ds = Dp;
+        if (valid && (near & 1)) rigid_one(S, D, nullptr, 0, p, x, v, m, V0, R, stamp, jdt, Jc, Dp, Dp, nullptr);
+        for (int b = 0; b < n_tools; b++) {
+            if (!((near >> (b + 1)) & 1)) continue;
+            float wr[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+            if (valid) rigid_one(S, D, &D.tools[b], 1 + b, p, x, v, m, V0, R, stamp, jdt, Jc, Dp, Ds, wr);
+            bool nz = wr[0] != 0.0f || wr[1] != 0.0f || wr[2] != 0.0f;
+            if (want_wrench && __any(nz)) {
+                for (int q = 0; q < 6; q++) {
+                    float val = wr[q];
+                    for (int o = 32; o >= 1; o >>= 1) val += __shfl_xor(val, o, 64);
+                    if (lane == 0) s_wr[wv][b * 6 + q] += val;
                 }
-            }
-            if (valid) {
-                D.Jrig[at3(p, 0)] = Jc[0];
-                D.Jrig[at3(p, 1)] = Jc[1];
-                D.Jrig[at3(p, 2)] = Jc[2];
-                if (Dp != Ds) D.D[p] = Dp;
             }
         }
+        if (valid) {
+            D.Jrig[at3(p, 0)] = Jc[0];
+            D.Jrig[at3(p, 1)] = Jc[1];
+            D.Jrig[at3(p, 2)] = Jc[2];
+            if (Dp != Ds) D.D[p] = Dp;
+        }
     }
-    if (want_wrench && s_any) { // other bricks add nothing to the call's sums
+    if (want_wrench) { // bricks out of reach add nothing to the call's sums
         __syncthreads();
         if (tid < n_tools * 6) {
             float acc = 0.0f;
             for (int w = 0; w < 4; w++) acc += s_wr[w][tid];
             D.wpart[(long long)tid * D.n_active + bi] += (double)acc;
         }
+    }
+}
+
+// Bodies (mask as in rigid_brick) that can reach a brick this substep, one test per lane
+DEV bool body_near(const SceneK& S, const SceneD& D, int bi, int brick, int body)
+{
+    if (body == 0 ? !S.floor_on : (body > D.tinfo[0] || !(D.tools[body - 1].flags & TL_TOOL_CONTACT))) return false;
+    float bb[7];
+    brick_aabb(S, D, bi, brick, bb);
+    if (body == 0) return brick_near_floor(bb, S.floor_z, S.Rmax, S.dt);
+    return brick_near_tool(bb, D.tools[body - 1], S.Rmax, S.dt, (double)D.ctr[2] * S.dt_d);
+}
+
+// The work items of a brick pass: the bricks of one scene, or (scene, brick) pairs
+struct BricksOfScene {
+    const SceneK& S;
+    const SceneD& D;
+    int n;
+    DEV const SceneK& scene(int) const { return S; }
+    DEV const SceneD& data(int) const { return D; }
+    DEV int brick(int i) const { return i; }
+};
+struct BricksOfBatch {
+    const SceneK* Ks;
+    const SceneD* Ds;
+    const int2* it;
+    int n;
+    DEV const SceneK& scene(int i) const { return Ks[it[i].x]; }
+    DEV const SceneD& data(int i) const { return Ds[it[i].x]; }
+    DEV int brick(int i) const { return it[i].y; }
+};
+
+// Rigid contact of nb bricks per workgroup, bricks w, w + G, w + 2 G, ... (G workgroups:
+// neighbours near one body fall to different ones): the first lanes test every body
+// against every brick at once, then the workgroup goes through the bricks within reach.
+template <class Items>
+DEV void rigid_group(const Items& I, int w, int G, int nb)
+{
+    __shared__ int s_near[TL_GROUP * 8];
+    const int t = threadIdx.x;
+    if (t < nb * 8) {
+        const int i = w + (t >> 3) * G, body = t & 7;
+        bool nr = false;
+        if (i < I.n && body < TL_BODIES) {
+            const SceneD& D = I.data(i);
+            const int bi = I.brick(i);
+            nr = body_near(I.scene(i), D, bi, D.active[bi], body);
+        }
+        // the mask of a brick from its 8 lanes
+        const unsigned long long all = __ballot(nr);
+        const int mask = (int)((all >> (t & 56)) & 0xFF);
+        if (body == 0) {
+            s_near[t >> 3] = mask;
+            if (i < I.n && (I.scene(i).floor_on || I.data(i).tinfo[1])) {
+                const SceneD& D = I.data(i);
+                D.brig[D.active[I.brick(i)]] = mask != 0;
+            }
+        }
+    }
+    __syncthreads();
+    for (int k = 0; k < nb; k++) {
+        const int m = s_near[k];
+        if (!m) continue;
+        const int i = w + k * G;
+        const SceneD& D = I.data(i);
+        const int bi = I.brick(i);
+        rigid_brick(I.scene(i), D, bi, D.active[bi], m);
+        __syncthreads(); // the brick's LDS words are reused by the next one
     }
 }
 
@@ -1777,7 +1825,7 @@ DEV void cell_summaries(const SceneK& S, const SceneD& D, int bi, int brick)
     }
     __syncthreads();
     bool mixed = false, some = false;
-    uint32_t key = 0u;
+    uint32_t key = 0u, done = TL_CODE_MASK; // cuts with a digit in all particles
     for (int c = threadIdx.x; c < TL_CELLS; c += blockDim.x) {
         const long long cs = (long long)brick * TL_CELLS + c;
         const int b0 = D.cell_start[cs], b1 = D.cell_start[cs + 1];
@@ -1786,14 +1834,16 @@ DEV void cell_summaries(const SceneK& S, const SceneD& D, int bi, int brick)
             if (S.material_contact) D.cmask[cs] = 0;
             continue;
         }
-        const uint32_t k0 = slot_key(S, D.code[b0]);
+        const uint32_t c0 = D.code[b0], k0 = slot_key(S, c0);
+        done &= c0 | ((c0 & TL_CODE_MASK) >> 15);
         uint32_t orm = k0; // OR of the codes of the cell (material contact candidates)
         uint32_t ks[TL_CKEYS] = {k0, 0u, 0u, 0u};
         int nk = 1;
         bool many = false;
 #pragma unroll 4
         for (int p = b0 + 1; p < b1; p++) {
-            const uint32_t k = slot_key(S, D.code[p]);
+            const uint32_t cp = D.code[p], k = slot_key(S, cp);
+            done &= cp | ((cp & TL_CODE_MASK) >> 15);
             orm |= k;
             // distinct keys in ascending order (insertion; at most TL_CKEYS kept)
             bool seen = false;
@@ -1829,11 +1879,13 @@ DEV void cell_summaries(const SceneK& S, const SceneD& D, int bi, int brick)
         const unsigned long long cells = __ballot(some);
         const uint32_t k0 = __shfl(key, cells ? __ffsll(cells) - 1 : 0, 64);
         key = __any(some && key != k0) ? TL_CC_MIXED : k0;
+        for (int o = 32; o >= 1; o >>= 1) done &= (uint32_t)__shfl_xor((int)done, o, 64);
     }
     const int m = __syncthreads_or(mixed);
     if (threadIdx.x == 0) {
         if (S.pair_skip) D.bor[brick] = s_bor; // (the barrier above ordered the LDS ORs)
         D.bkey[brick] = m ? TL_CC_MIXED : key;
+        D.ball[brick] = done & 0x7FFFu;
         D.bmixed[brick] = m;
         if (!m) {
             D.bround[bi] = 0; // no split workgroup for this brick
@@ -1918,18 +1970,16 @@ DEV DevBlade blade_at(const DevTool& T, double jdt)
     return B;
 }
 
-// Blades whose band can reach active brick bi (= brick) this substep: bit b for
-// tools[b] (label tools only; brick_near_band, conservative).
-DEV int label_mask(const SceneK& S, const SceneD& D, int bi, int brick, int n_tools, double jdt)
+// Whether the band of tool b can give a digit to a particle of active brick bi (= brick)
+// this substep: it labels, some particle has no digit of its cut yet (an assigned digit
+// never changes), and its band can meet the brick's box (brick_near_band, conservative).
+DEV bool band_near(const SceneK& S, const SceneD& D, int bi, int brick, int b, double jdt)
 {
+    if (b >= D.tinfo[0] || !(D.tools[b].flags & TL_TOOL_LABELS)) return false;
+    if ((D.ball[brick] >> D.tools[b].b.cut) & 1u) return false;
     float bb[7];
     brick_aabb(S, D, bi, brick, bb);
-    int m = 0;
-    for (int b = 0; b < n_tools; b++) {
-        if (!(D.tools[b].flags & TL_TOOL_LABELS)) continue;
-        if (brick_near_band(bb, blade_at(D.tools[b], jdt), S.dt_d)) m |= 1 << b;
-    }
-    return m;
+    return brick_near_band(bb, blade_at(D.tools[b], jdt), S.dt_d);
 }
 
 // Label pass of one brick within reach of the blades of mask m (whole block).
@@ -1979,70 +2029,76 @@ DEV void labels_brick(const SceneK& S, const SceneD& D, int bi, int brick, int m
     }
 }
 
-DEV void labels_body(const SceneK& S, const SceneD& D, int bi)
+// Label pass of nb bricks per workgroup (as rigid_group): four lanes per brick test the
+// bands at once, then the workgroup labels the bricks within reach one after another.
+template <class Items>
+DEV void labels_group(const Items& I, int w, int G, int nb)
 {
-    const double jdt = (double)D.ctr[2] * S.dt_d; // substep of the call (TL_TOOL_ADVANCE poses)
-    __shared__ int s_m;
-    const int brick = D.active[bi];
-    if (threadIdx.x == 0) s_m = label_mask(S, D, bi, brick, D.tinfo[0], jdt);
-    __syncthreads();
-    const int m = s_m;
-    if (!m) return;
-    labels_brick(S, D, bi, brick, m, jdt);
-}
-
-// Label pass of one scene with TL_LBRICKS bricks per workgroup: the first lanes test
-// the bands of bricks w, w + G, w + 2G, ... (G workgroups: the bricks of a blade's
-// band, neighbours in the active order, fall to different workgroups), then the
-// workgroup labels the bricks within reach one after another.  Far fewer workgroups
-// than bricks, most of which only test.
-#define TL_LBRICKS 16
-__global__ __launch_bounds__(256) void k_labels_multi(SceneK S, SceneD D)
-{
-    __shared__ int s_m[TL_LBRICKS];
-    const double jdt = (double)D.ctr[2] * S.dt_d;
-    const int G = gridDim.x;
-    if (threadIdx.x < TL_LBRICKS) {
-        const int bi = blockIdx.x + threadIdx.x * G;
-        s_m[threadIdx.x] = bi < D.n_active ? label_mask(S, D, bi, D.active[bi], D.tinfo[0], jdt) : 0;
+    __shared__ int s_m[TL_GROUP];
+    const int t = threadIdx.x;
+    if (t < nb * TL_MAX_TOOLS) {
+        const int i = w + (t / TL_MAX_TOOLS) * G;
+        bool nr = false;
+        if (i < I.n) {
+            const SceneK& S = I.scene(i);
+            const SceneD& D = I.data(i);
+            const int bi = I.brick(i);
+            nr = band_near(S, D, bi, D.active[bi], t % TL_MAX_TOOLS, (double)D.ctr[2] * S.dt_d);
+        }
+        const unsigned long long all = __ballot(nr);
+        if (t % TL_MAX_TOOLS == 0) s_m[t / TL_MAX_TOOLS] = (int)((all >> (t & 60)) & 0xF);
     }
     __syncthreads();
-    for (int k = 0; k < TL_LBRICKS; k++) {
+    for (int k = 0; k < nb; k++) {
         const int m = s_m[k];
         if (!m) continue;
-        const int bi = blockIdx.x + k * G;
-        labels_brick(S, D, bi, D.active[bi], m, jdt);
+        const int i = w + k * G;
+        const SceneK& S = I.scene(i);
+        const SceneD& D = I.data(i);
+        const int bi = I.brick(i);
+        labels_brick(S, D, bi, D.active[bi], m, (double)D.ctr[2] * S.dt_d);
         __syncthreads(); // the brick's LDS words are reused by the next one
     }
 }
 
-// The same over the n (scene, brick) work items of a batch.
-__global__ __launch_bounds__(256) void k_labels_multi_b(const SceneK* __restrict__ Ks, const SceneD* __restrict__ Ds,
-                                                        const int2* __restrict__ it, int n)
+// Bricks per workgroup of these two passes for n bricks (a batch: work items): one each
+// below 4096, where a workgroup per brick starts about as fast as the tests run; beyond
+// that most workgroups only test, and bricks share them so that their number stays near
+// 2048, up to TL_GROUP.  2.5k bricks: labels 45 us in groups of 16, 17 us one each.  28k
+// bricks in groups of 14: labels 48 us with one lane testing all bands, 42 us with a lane
+// per band; rigid contact 120 us one each, 66 us in groups.
+static int group_of(int n) { return n < 4096 ? 1 : n / 2048 > TL_GROUP ? TL_GROUP : n / 2048; }
+
+__global__ __launch_bounds__(256) void k_labels(SceneK S, SceneD D, int nb)
 {
-    __shared__ int s_m[TL_LBRICKS];
-    const int G = gridDim.x;
-    if (threadIdx.x < TL_LBRICKS) {
-        const int i = blockIdx.x + threadIdx.x * G;
-        int m = 0;
-        if (i < n) {
-            const int2 t = it[i];
-            const SceneK& S = Ks[t.x];
-            const SceneD& D = Ds[t.x];
-            m = label_mask(S, D, t.y, D.active[t.y], D.tinfo[0], (double)D.ctr[2] * S.dt_d);
-        }
-        s_m[threadIdx.x] = m;
-    }
-    __syncthreads();
-    for (int k = 0; k < TL_LBRICKS; k++) {
-        const int m = s_m[k];
-        if (!m) continue;
-        const int2 t = it[blockIdx.x + k * G];
-        const SceneK& S = Ks[t.x];
-        const SceneD& D = Ds[t.x];
-        labels_brick(S, D, t.y, D.active[t.y], m, (double)D.ctr[2] * S.dt_d);
-        __syncthreads();
-    }
+    labels_group(BricksOfScene{S, D, D.n_active}, blockIdx.x, gridDim.x, nb);
+}
+__global__ __launch_bounds__(256) void k_labels_b(const SceneK* __restrict__ Ks, const SceneD* __restrict__ Ds,
+                                                    const int2* __restrict__ it, int n, int nb)
+{
+    labels_group(BricksOfBatch{Ks, Ds, it, n}, blockIdx.x, gridDim.x, nb);
+}
+__global__ __launch_bounds__(256) void k_rigid(SceneK S, SceneD D, int nb)
+{
+    rigid_group(BricksOfScene{S, D, D.n_active}, blockIdx.x, gridDim.x, nb);
+}
+__global__ __launch_bounds__(256) void k_rigid_b(const SceneK* __restrict__ Ks, const SceneD* __restrict__ Ds,
+                                                   const int2* __restrict__ it, int n, int nb)
+{
+    rigid_group(BricksOfBatch{Ks, Ds, it, n}, blockIdx.x, gridDim.x, nb);
+}
+
+// The label pass and rigid contact of one scene in one launch: blocks below nl take the
+// label pass of a brick, the others its rigid contact.  Rigid contact reads only the last
+// substep's motion, the tools and the cutting progress, none of which the label pass
+// writes, and the label pass reads nothing rigid contact writes.
+__global__ __launch_bounds__(256) void k_labels_rigid(SceneK S, SceneD D, int nl)
+{
+    const BricksOfScene I{S, D, D.n_active};
+    if ((int)blockIdx.x < nl)
+        labels_group(I, blockIdx.x, nl, 1);
+    else
+        rigid_group(I, blockIdx.x - nl, nl, 1);
 }
 
 // --------------------------------------------------------------- small kernels
@@ -2250,35 +2306,12 @@ DEV void wrench_body(const SceneK& S, const SceneD& D, int bi)
     }
 
 #define TL_COMMA ,
-TL_WRAP(rigid, 256, , )
 TL_WRAP(slots, 256, TL_COMMA int dst TL_COMMA int src TL_COMMA int force, TL_COMMA dst TL_COMMA src TL_COMMA force)
 TL_WRAP(mixed, 256, TL_COMMA int force, TL_COMMA force)
 TL_WRAP(aabb, 256, , )
 TL_WRAP(wrench, 256, , )
 TL_WRAP(resetD, 256, , )
 TL_WRAP(call_start, 64, , )
-
-// The label pass and rigid contact in one launch: blocks below nl take the label
-// pass of a brick, the others its rigid contact.  Rigid contact reads only the last
-// substep's motion, the tools and the cutting progress, none of which the label pass
-// writes, and the label pass reads nothing rigid contact writes.
-__global__ __launch_bounds__(256) void k_labels_rigid(SceneK S, SceneD D, int nl)
-{
-    if ((int)blockIdx.x < nl)
-        labels_body(S, D, blockIdx.x);
-    else
-        rigid_body(S, D, blockIdx.x - nl);
-}
-__global__ __launch_bounds__(256) void k_labels_rigid_b(const SceneK* __restrict__ Ks, const SceneD* __restrict__ Ds,
-                                                        const int2* __restrict__ it, int nl)
-{
-    const bool lb = (int)blockIdx.x < nl;
-    const int2 t = it[lb ? blockIdx.x : blockIdx.x - nl];
-    if (lb)
-        labels_body(Ks[t.x], Ds[t.x], t.y);
-    else
-        rigid_body(Ks[t.x], Ds[t.x], t.y);
-}
 
 // at most 80 VGPRs: three 512-thread workgroups per CU
 // Neo-Hookean: at most 80 VGPRs (three workgroups per CU); the general path (polar
@@ -2390,10 +2423,24 @@ static int plain_bflags(const TlLaunch& L)
     return L.S ? blocks_of((long long)L.S->cbx * L.S->cby * L.S->cbz, 256) : 0;
 }
 
+// the label pass and rigid contact: group_of(n) bricks per workgroup
+template <class KP, class KB>
+static hipError_t run_groups(const TlLaunch& L, KP kp, KB kb)
+{
+    const int n = L.S ? L.D->n_active : L.n_items[IT_BRICK];
+    if (n <= 0) return hipSuccess;
+    const int nb = group_of(n), G = (n + nb - 1) / nb;
+    if (L.S)
+        hipLaunchKernelGGL(kp, dim3(G), dim3(256), 0, L.st, *L.S, *L.D, nb);
+    else
+        hipLaunchKernelGGL(kb, dim3(G), dim3(256), 0, L.st, L.Ks, L.Ds, L.items[IT_BRICK], n, nb);
+    return hipGetLastError();
+}
+
 extern "C" {
 hipError_t tl_launch_rigid(const TlLaunch* L)
 {
-    return tl_run(*L, IT_BRICK, plain_bricks(*L), 256, k_rigid, k_rigid_b);
+    return run_groups(*L, k_rigid, k_rigid_b);
 }
 
 hipError_t tl_launch_p2g(const TlLaunch* L, int do_p2g, int tabs_differ, int cur, int rsb)
@@ -2415,28 +2462,14 @@ hipError_t tl_launch_g2p(const TlLaunch* L, int cur)
 
 hipError_t tl_launch_labels(const TlLaunch* L)
 {
-    if (L->S) { // one scene: TL_LBRICKS bricks per workgroup
-        const int n = plain_bricks(*L);
-        if (n <= 0) return hipSuccess;
-        hipLaunchKernelGGL(k_labels_multi, dim3((n + TL_LBRICKS - 1) / TL_LBRICKS), dim3(256), 0, L->st, *L->S,
-                           *L->D);
-        return hipGetLastError();
-    }
-    const int n = L->n_items[IT_BRICK]; // a batch: TL_LBRICKS work items per workgroup
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_labels_multi_b, dim3((n + TL_LBRICKS - 1) / TL_LBRICKS), dim3(256), 0, L->st, L->Ks, L->Ds,
-                       L->items[IT_BRICK], n);
-    return hipGetLastError();
+    return run_groups(*L, k_labels, k_labels_b);
 }
 
 hipError_t tl_launch_labels_rigid(const TlLaunch* L)
 {
-    const int n = L->S ? plain_bricks(*L) : L->n_items[IT_BRICK];
+    const int n = plain_bricks(*L); // (single scenes only)
     if (n <= 0) return hipSuccess;
-    if (L->S)
-        hipLaunchKernelGGL(k_labels_rigid, dim3(2 * n), dim3(256), 0, L->st, *L->S, *L->D, n);
-    else
-        hipLaunchKernelGGL(k_labels_rigid_b, dim3(2 * n), dim3(256), 0, L->st, L->Ks, L->Ds, L->items[IT_BRICK], n);
+    hipLaunchKernelGGL(k_labels_rigid, dim3(2 * n), dim3(256), 0, L->st, *L->S, *L->D, n);
     return hipGetLastError();
 }
 

@@ -1,0 +1,93 @@
+"""The label pass and rigid contact with several bricks per workgroup (4096 bricks and
+more): numbers of bricks around the first group sizes, with remainders, against the
+oracle, and many-scene groups against the scenes stepped alone; bricks whose particles
+all hold a digit are passed over."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_27342_amd import workloads as W
+
+from harness import oracle_substep, state_errs
+
+pytestmark = pytest.mark.gpu
+
+STEPS = 3
+TOL = 1e-5 * STEPS  # FP32 sums of one substep, added up
+
+
+@pytest.fixture(scope="module")
+def tl():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_27342_amd import tlmpm
+    tlmpm.lib()
+    return tlmpm
+
+
+def _scene(n_bricks, side, seed):
+    """n_bricks bricks of a side^3 arrangement, in their order, with two particles each,
+    falling on a floor among the lowest ones and sideways against a blade's plane."""
+    s = W.box_scene(n_cells=(2, 2, 2), seed=seed, gravity=[0.0, 0.0, -9.81], slot_capacity=8)
+    dx = s["params"]["dx"]
+    rng = np.random.default_rng([seed, n_bricks])
+    b = np.repeat(np.stack([np.arange(n_bricks) % side, np.arange(n_bricks) // side % side,
+                            np.arange(n_bricks) // side ** 2], 1), 2, 0)
+    n = b.shape[0]
+    X = (b * 4 + 1.0 + 2.0 * rng.random((n, 3))) * dx
+    s.update(X=X.astype(np.float32), vol0=np.full(n, s["vol0"][0], np.float32),
+             mass=np.full(n, s["mass"][0], np.float32), E=np.full(n, s["E"][0], np.float32),
+             v0=(rng.normal(size=(n, 3)) * 0.1).astype(np.float32))
+    s["params"].update(origin=[0.0] * 3, cells=[4 * side] * 3, floor_on=1, floor_z=0.9 * dx)
+    L = 4 * side * dx
+    top = 0.5 * (X[:, 2].min() + X[:, 2].max())
+    bl = W.blade(0, (0.5 * L + 2 * dx, 0.5 * L, top), (1, 0, 0), (0, 0, -1), (0, 0, -0.5), 0.4 * L, 6 * dx, 0.5 * L, dx,
+                 new_cut=True)
+    wide = W.blade(1, (0.3 * L, 0.5 * L, -dx), (1, 0, 0), (0, 0, -1), (0, 0, 0), 2 * L, 2 * L, 2 * L, 2 * L, new_cut=True)
+    s["tools_at"] = lambda j: [W.tool(dict(bl, new_cut=int(j == 0))),
+                               W.tool(dict(wide, new_cut=int(j == 0)), contact=False)]
+    return s
+
+
+@pytest.mark.parametrize("n_bricks", [4095, 4096, 4097, 6299])
+def test_groups_against_oracle(tl, n_bricks):
+    s = _scene(n_bricks, 20, 41)
+    n = s["X"].shape[0]
+    print(f"[case] brick groups bricks={n_bricks} n={n}", flush=True)
+    g, o = tl.Scene(s), oracle.OracleScene(s)
+    for j in range(STEPS):
+        g.step(s["tools_at"](j))
+        oracle_substep(o, s["tools_at"](j))
+    assert g.status() == 0
+    a, b = g.read(("u", "v", "H", "digits")), o.get()
+    d = a["digits"]
+    assert np.array_equal(d, b["digits"])
+    # the first cut gave digits on both sides to some, the second to every particle
+    assert 0 < (d[:, 0] == 1).sum() < n and 0 < (d[:, 0] == 2).sum() < n and (d[:, 1] != 0).all()
+    eu, ev, eH = state_errs(a, b, s["X"], s["params"])
+    assert eu < TOL and ev < TOL and eH < TOL, (eu, ev, eH)
+
+
+def test_groups_of_a_batch(tl):
+    scenes = [_scene(m, 14, 42 + i) for i, m in enumerate((2101, 1, 2047, 2150))]  # 6299: groups of 3
+    fields = ("u", "v", "F", "code", "D")
+    print("[case] brick groups of a batch", flush=True)
+    alone = []
+    for s in scenes:
+        g = tl.Scene(s)
+        w = [g.step(s["tools_at"](j), wrench=True) for j in range(STEPS)]
+        assert g.status() == 0
+        alone.append((g.read(fields), w))
+        g.close()
+    gs = [tl.Scene(s) for s in scenes]
+    with tl.Batch(gs) as b:
+        ws = [b.step([s["tools_at"](j) for s in scenes], 1, wrench=True) for j in range(STEPS)]
+    for i, g in enumerate(gs):
+        assert g.status() == 0
+        st = g.read(fields)
+        for f in fields:
+            assert np.array_equal(st[f], alone[i][0][f]), (i, f)
+        for j in range(STEPS):
+            assert np.array_equal(ws[j][i][:2], alone[i][1][j]), (i, j)
+    assert any(np.any(w) for _, ws1 in alone for w in ws1)  # a blade touched something
