@@ -349,8 +349,8 @@ DEV void make_rec(const SceneK& S, const SceneD& D, int p, const float x[3], flo
 }
 
 // Flag in the fourth word of a candidate record (beside the cell's z, 16 bits): the
-// binning found that the candidate has no contact partner this substep, and the pair
-// pass writes its zero impulse without searching.
+// binning found that the candidate has no contact partner this substep; it wrote the zero
+// impulse and the empty spring list itself, and the pair pass passes it over.
 #define TL_REC_SKIP (1 << 30)
 
 // Can a candidate of brick `brick` (active index bi) have a contact partner this
@@ -472,8 +472,13 @@ DEV void bin_insert_body(const SceneK& S, const SceneD& D, int bi, int self_scan
         cur_pos(S, D, p, x);
         float4 r[3];
         make_rec(S, D, p, x, r);
-        if (may_skip && !cconflict(ckey(S, __float_as_uint(r[0].y)), orn))
+        if (may_skip && !cconflict(ckey(S, __float_as_uint(r[0].y)), orn)) {
             r[0].w = __int_as_float(__float_as_int(r[0].w) | TL_REC_SKIP);
+            D.ph_n[(long long)(gen & 1u) * S.N + p] = (int)(gen << 8);
+            D.Jmat[at3(p, 0)] = 0.0f;
+            D.Jmat[at3(p, 1)] = 0.0f;
+            D.Jmat[at3(p, 2)] = 0.0f;
+        }
         float4* dst = D.crec + (long long)g * 3;
         dst[0] = r[0];
         dst[1] = r[1];
@@ -618,6 +623,10 @@ DEV void bucket_sorted(const SceneD& D, uint32_t h, int c, int e[TL_BCAP])
     }
 }
 
+// LDS words written before are read after by lanes of the same wave (LDS serves a wave's
+// accesses in order: only the compiler must keep them so)
+DEV void wave_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 #define TL_PLIST (TL_PLANES == 8 ? 96 : 64) // compacted neighbour entries per candidate held in LDS
 DEV void pairs_body(const SceneK& S, const SceneD& D, int bi)
 {
@@ -653,29 +662,27 @@ DEV void pairs_body(const SceneK& S, const SceneD& D, int bi)
     // exceeds R_p + R_q + dt |v_p - v_q| for every pair (see bin_edge)
     const float reach2 = hb * hb;
     const long long N = S.N;
+    // a wave takes 64 / TL_PLANES candidates at a time, by itself: no lane group shares
+    // anything with other waves (their LDS words are its own), so there are no barriers
     const int sub = threadIdx.x / TL_PLANES; // candidate of this lane group
     const int l = threadIdx.x % TL_PLANES;   // lane in the group
     constexpr int NBL = (27 + TL_PLANES - 1) / TL_PLANES; // bins per lane
     const int stride = S.pair_blocks * TL_PCAND;
-    for (int c0 = bi * TL_PCAND; c0 < total; c0 += stride) {
-        const int g = c0 + sub;
-        const bool has = g < total;
+    for (int c0 = bi * TL_PCAND + (sub & ~(64 / TL_PLANES - 1)); c0 < total; c0 += stride) {
+        const int g = c0 + (sub & (64 / TL_PLANES - 1));
         float4 rp[3];
-        if (has) {
-            const float4* src = D.crec + (long long)g * 3;
-            rp[0] = src[0];
-            rp[1] = src[1];
-            rp[2] = src[2];
-        }
-        const int p = has ? __float_as_int(rp[0].x) : -1;
-        // a candidate the binning found without a possible partner: zero impulse, no springs
-        const bool look = has && !(__float_as_int(rp[0].w) & TL_REC_SKIP);
+        const float4* src = D.crec + (long long)(g < total ? g : 0) * 3;
+        rp[0] = src[0];
+        // (the binning dealt with a candidate that has no possible partner)
+        const bool look = g < total && !(__float_as_int(rp[0].w) & TL_REC_SKIP);
+        if (!__any(look)) continue;
+        rp[1] = src[1];
+        rp[2] = src[2];
+        const int p = __float_as_int(rp[0].x);
         // this lane's bins: l, l + TL_PLANES, ... of the 27 around the candidate
-        int bq[3] = {0, 0, 0};
-        if (has) {
-            const float xp[3] = {rp[1].x, rp[1].y, rp[1].z};
-            bin_of(xp, inv_h, bq);
-        }
+        int bq[3];
+        const float xp[3] = {rp[1].x, rp[1].y, rp[1].z};
+        bin_of(xp, inv_h, bq);
         // distances from the candidate to the faces of its own bin
         float lo[3], hi[3];
 #pragma unroll
@@ -752,7 +759,7 @@ DEV void pairs_body(const SceneK& S, const SceneD& D, int bi)
                 }
             }
         }
-        __syncthreads();
+        wave_order();
         float Jt[3] = {0.0f, 0.0f, 0.0f};
         if (look) {
             const uint32_t kp = ckey(S, __float_as_uint(rp[0].y));
@@ -864,8 +871,8 @@ DEV void pairs_body(const SceneK& S, const SceneD& D, int bi)
             Jt[a] += lane_xor<2>(Jt[a]);
             Jt[a] += lane_xor<1>(Jt[a]);
         }
-        __syncthreads();
-        if (has && l == 0) {
+        wave_order();
+        if (look && l == 0) {
             const int nn = s_nnew[sub];
             D.ph_n[(long long)hnew * N + p] = (stamp << 8) | (nn < TL_PCAP ? nn : TL_PCAP);
             D.Jmat[at3(p, 0)] = Jt[0];
