@@ -193,8 +193,8 @@ struct SceneD {
     float* ph_u;        // [2][N][TL_PCAP][3] spring, oriented for the pair's lower index
     // quadratic stencil
     uint32_t* qcode;    // [2][scap][NN] side keys of the node slots by substep parity (~0u: free)
-    float* qacc;        // [NN][scap][8] P2G sums m, p, dp; after the grid update m, v^n, dv
-    float* qrs;         // [NN][scap][4] re-scatter sums of m v^{n+1}; after the remap v~
+    float* qacc;        // [scap][NN][8] P2G sums m, p, dp; after the grid update m, v^n, dv
+    float* qrs;         // [scap][NN][4] re-scatter sums of m v^{n+1}; after the remap v~
     int* qnodes;        // nodes of the 7x7x7 boxes of the active bricks (ascending)
     int n_qnodes;
     int* qround;        // [active bricks + 1] first lane-map round of each brick

@@ -414,6 +414,15 @@ DEV bool vm_project(float mu, float sigma_y, float* K, float* G)
     return true;
 }
 
+// The same value, computed from no earlier than here: keeps what is derived from it (the
+// addresses of a round's loads, stores and LDS places) out of the registers of the code
+// before, where it would be spilled
+DEV int late(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // ------------------------------------------------------------------- slot tables
 // For every node: the distinct codes of the particles in its 8 incident cells, in
 // ascending order (compact slots, Sec. III-G).  Rebuilt only next to the bricks whose

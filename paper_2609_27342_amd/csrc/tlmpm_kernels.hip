@@ -355,15 +355,6 @@ struct Local {
     }
 };
 
-// The same value, computed from no earlier than here: keeps what is derived from it (the
-// addresses of a round's loads, stores and LDS places) out of the registers of the code
-// before, where it would be spilled
-DEV int late(int x)
-{
-    asm volatile("" : "+v"(x));
-    return x;
-}
-
 // Particle of this lane in round r.  Bricks whose cells each hold one code take
 // particle 8 r + j of the lane's cell; bricks with a mixed cell take particle j of
 // the cell's r-th same-code group (group table built when the codes change).

@@ -17,13 +17,14 @@
 // positions do not move), with more rounds where a cell holds two particles of
 // one pattern.  A wave's particles then lie in distinct cells with one pattern, so
 // their base nodes, and the nodes of any one stencil offset, are distinct, and
-// all of them lie in a 6x6x6 region fixed by the pattern.  For the brick's first
-// side key each wave adds into its own LDS region with plain read-modify-writes
-// (no atomics, no barriers); the regions are summed in wave order when the box
-// goes out.  Further side keys of a brick (bricks on a cut) use LDS atomics, and
-// beyond TL_QK keys HBM atomics.  The box sums go once per (node, slot) into HBM
-// with floating-point atomics (up to 8 bricks share a node): results agree with
-// the fixed-order trilinear path to rounding but are not bitwise reproducible.
+// all of them lie in a 6x6x6 region fixed by the pattern.  Each wave adds into its own LDS
+// region with plain read-modify-writes (no atomics, no barriers), one side key of the
+// brick at a time (bricks on a cut hold two or three); the regions are summed in wave
+// order when the box goes out: to the brick's own partials, one box per side key, and the
+// node kernels add up the (at most 8) boxes that hold a node in a fixed order.  Keys of a
+// brick beyond the slot capacity go to the node slots with floating-point atomics (with
+// them for every key the 1.5M atomics of 586 bricks kept the P2G waiting 18 us per box,
+// up to 50 us, of 85 us).
 #include <hip/hip_runtime.h>
 #include <hip/amd_detail/amd_hip_unsafe_atomics.h>
 #include <math.h>
@@ -34,10 +35,16 @@
 
 #define TL_QBOX 7
 #define TL_QBOXN 343      // nodes of a brick's 7x7x7 box
-#define TL_QK 4           // side keys of a brick summed in LDS; further keys go to HBM directly
 #define TL_QWG 512        // threads of a brick workgroup
+#define TL_QNODE 64       // threads of a workgroup of the node kernels
 #define TL_QEMPTY 0xFFFFFFFFu
-#define TL_QREG 216       // nodes of one wave's 6x6x6 region (its 64 cells' stencils)
+// LDS places of a wave's 6x6x6 region and of a brick's 7x7x7 box, in 16-byte units: two z
+// planes side by side, and pitches that put the 16 cells of two parity classes (a quarter
+// of a wave's lanes) in 16 different bank groups whatever the stencil offset
+#define TL_QREG 224
+#define TL_QBOXP 403
+DEV int q_reg_at(int x, int y, int z) { return (z >> 1) * 76 + y * 12 + (z & 1) * 6 + x; }
+DEV int q_box_at(int x, int y, int z) { return (z >> 1) * 104 + y * 14 + (z & 1) * 7 + x; }
 
 // brick-major id of grid node (gx, gy, gz); -1 outside the grid
 DEV long long q_gid(const SceneK& S, int gx, int gy, int gz)
@@ -70,6 +77,17 @@ struct QStencil {
     int lo[3];        // base node per axis
     float w[3][3];    // [axis][node]
     float g[3][3];    // derivative / dx
+    // some weight is zero (the middle ones are at least 1/2): its nodes take no part (R7)
+    DEV bool zero() const
+    {
+        return w[0][0] == 0.0f || w[0][2] == 0.0f || w[1][0] == 0.0f || w[1][2] == 0.0f || w[2][0] == 0.0f ||
+               w[2][2] == 0.0f;
+    }
+};
+// a gather with tests for zero weights, or without (waves that hold none)
+template <bool B>
+struct QGuard {
+    static constexpr bool value = B;
 };
 
 DEV void q_stencil(const SceneK& S, const float* X, const int c[3], int h, QStencil& Q)
@@ -96,11 +114,16 @@ DEV void q_stencil(const SceneK& S, const float* X, const int c[3], int h, QSten
 DEV int q_key_index(uint32_t* s_keys, uint32_t key)
 {
     for (int k = 0; k < TL_SCAP_MAX; k++) {
+        if (s_keys[k] == key) return k; // (most lanes find it: no serial exchanges)
         const uint32_t old = atomicCAS(&s_keys[k], TL_QEMPTY, key);
         if (old == TL_QEMPTY || old == key) return k;
     }
     return -1;
 }
+
+// place of slot s of node g in the arrays of sums: slot by slot, so that the first slots,
+// nearly all there are, lie side by side
+DEV size_t q_at(const SceneK& S, long long g, int s) { return (size_t)s * (size_t)S.NN + (size_t)g; }
 
 // slot of key at node g in a table (slots fill from 0; the first empty one ends
 // the list); -1 if absent
@@ -140,6 +163,18 @@ DEV void q_couple(int c, const float* m, const uint32_t* codes, float (*f)[3])
         for (int j = 0; j < 3; j++) f[a][j] = out[a][j];
 }
 
+// the same for two slots, in registers (nearly every node with more than one)
+DEV void q_couple2(float m0, float m1, bool compatible, float (&f0)[3], float (&f1)[3])
+{
+    const float M = m0 + m1, invM = M > 0.0f ? 1.0f / M : 0.0f;
+#pragma unroll
+    for (int j = 0; j < 3; j++) {
+        const float a = f0[j], b = f1[j];
+        f0[j] = a + (compatible ? m0 * b - m1 * a : 0.0f) * invM;
+        f1[j] = b + (compatible ? m1 * a - m0 * b : 0.0f) * invM;
+    }
+}
+
 // particle of this thread in round r of active brick bi (-1: none)
 DEV int q_particle(const SceneD& D, int bi, int r)
 {
@@ -148,20 +183,25 @@ DEV int q_particle(const SceneD& D, int bi, int r)
 
 DEV int q_rounds(const SceneD& D, int bi) { return D.qround[bi + 1] - D.qround[bi]; }
 
-// element i (0..2) of a 3-array by selects, so that a rolled loop keeps the array
-// in registers
-DEV float q_pick(const float (&a)[3], int i) { return i == 0 ? a[0] : (i == 1 ? a[1] : a[2]); }
-
-// index of a key already in the brick's LDS key list; -1 if absent
-DEV int q_key_lookup(const uint32_t* s_keys, uint32_t key)
-{
-    for (int k = 0; k < TL_SCAP_MAX; k++) {
-        const uint32_t c = s_keys[k];
-        if (c == key) return k;
-        if (c == TL_QEMPTY) return -1;
+// Particle of this thread in round r, its code and reference position.  Round 0, nearly
+// always the only one, is loaded before a brick's box, so that the two chains of loads
+// overlap.
+struct QFirst {
+    int p;
+    uint32_t code;
+    float X[3];
+    DEV QFirst(const SceneD& D, int bi, int rounds, int r = 0)
+    {
+        p = r < rounds ? q_particle(D, bi, r) : -1;
+        code = 0u;
+        X[0] = X[1] = X[2] = 0.0f;
+        if (p < 0) return;
+        code = D.code[p];
+        X[0] = D.X[at3(p, 0)];
+        X[1] = D.X[at3(p, 1)];
+        X[2] = D.X[at3(p, 2)];
     }
-    return -1;
-}
+};
 
 // registers the side keys of a brick's particles in its LDS key list (call between
 // barriers)
@@ -172,30 +212,6 @@ DEV void q_register_keys(const SceneK& S, const SceneD& D, int bi, uint32_t* s_k
         const int p = q_particle(D, bi, r);
         if (p < 0) continue;
         if (q_key_index(s_keys, slot_key(S, D.code[p])) < 0) atomicOr(D.status, TL_ST_BOX);
-    }
-}
-
-// loads Q floats per node slot (from src, stride QS, offset off) for the first
-// TL_QK keys of the brick over its box into dst[key][box node][Q]; absent slots
-// read as zero
-template <int Q, int QS, int OFF>
-DEV void q_load_box(const SceneK& S, const uint32_t* tab, const float* src, int bx, int by, int bz,
-                    const uint32_t* s_keys, float* dst)
-{
-    for (int t = threadIdx.x; t < TL_QK * TL_QBOXN; t += TL_QWG) {
-        const uint32_t key = s_keys[t / TL_QBOXN];
-        if (key == TL_QEMPTY) continue;
-        const long long g = q_box_gid(S, bx, by, bz, t % TL_QBOXN);
-        const int s = g >= 0 ? q_find(S, tab, g, key) : -1;
-        float* o = dst + (size_t)t * Q;
-        if (s < 0) {
-#pragma unroll
-            for (int c = 0; c < Q; c++) o[c] = 0.0f;
-            continue;
-        }
-        const float* a = src + ((size_t)g * S.scap + s) * QS + OFF;
-#pragma unroll
-        for (int c = 0; c < Q; c++) o[c] = a[c];
     }
 }
 
@@ -269,10 +285,10 @@ __global__ __launch_bounds__(TL_QWG) void k_q_slots(SceneK S, SceneD D, int par)
             for (; s < S.scap; s++) {
                 const uint32_t old = atomicCAS(&tab[(long long)s * S.NN + g], TL_QEMPTY, key);
                 if (old == TL_QEMPTY) {
-                    float4* a = (float4*)(D.qacc + ((size_t)g * S.scap + s) * 8);
+                    float4* a = (float4*)(D.qacc + q_at(S, g, s) * 8);
                     a[0] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                     a[1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    *(float4*)(D.qrs + ((size_t)g * S.scap + s) * 4) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    *(float4*)(D.qrs + q_at(S, g, s) * 4) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                     break;
                 }
                 if (old == key) break;
@@ -282,34 +298,156 @@ __global__ __launch_bounds__(TL_QWG) void k_q_slots(SceneK S, SceneD D, int par)
     }
 }
 
-// adds a brick's LDS sums (Q values per node) into the node slots in HBM (stride
-// QS floats per slot): the first key's sums from the 8 wave regions, in wave order
-// (wave h holds box node (X, Y, Z) at region (X, Y, Z) - 1 + low(h), low = 1 on the
-// axes of the lower half), the other keys' sums from s_acc [key - 1][box node]
-template <int Q, int QS>
-DEV void q_flush(const SceneK& S, const SceneD& D, const uint32_t* tab, float* dst, int bx, int by, int bz,
-                 const uint32_t* s_keys, const float* s_wv, const float* s_acc)
+// The 8 wave regions of the P2G: {m, m v} and the impulse per node (28 bytes: with 32 a CU
+// holds two workgroups instead of three)
+struct QRegions {
+    float4 a[8 * TL_QREG];
+    float2 b[8 * TL_QREG];
+    float c[8 * TL_QREG];
+    DEV void zero()
+    {
+        for (int t = late(threadIdx.x); t < 8 * TL_QREG; t += TL_QWG) {
+            a[t] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            b[t] = make_float2(0.0f, 0.0f);
+            c[t] = 0.0f;
+        }
+    }
+    DEV void sum(int at, float v[7]) const
+    {
+        const float4 x = a[at];
+        const float2 y = b[at];
+        const float z = c[at];
+        v[0] += x.x;
+        v[1] += x.y;
+        v[2] += x.z;
+        v[3] += x.w;
+        v[4] += y.x;
+        v[5] += y.y;
+        v[6] += z;
+    }
+};
+// ... and of the re-scatter: m v^{n+1}
+struct QRegions3 {
+    float4 a[8 * TL_QREG];
+    DEV void zero()
+    {
+        for (int t = late(threadIdx.x); t < 8 * TL_QREG; t += TL_QWG) a[t] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+    DEV void sum(int at, float v[3]) const
+    {
+        const float4 x = a[at];
+        v[0] += x.x;
+        v[1] += x.y;
+        v[2] += x.z;
+    }
+};
+
+// A brick's partials: boxes of its first slot-capacity side keys (8 floats per node, 4 in
+// the re-scatter), and the keys.  They use the arrays that the trilinear transfers keep
+// their partials in (12000 bytes per brick and slot; a box takes 10976, the keys 64 per
+// brick).
+DEV float* q_part(const SceneK& S, const SceneD& D, int bi, int k)
 {
-    for (int t = threadIdx.x; t < TL_QK * TL_QBOXN; t += TL_QWG) {
-        const int k = t / TL_QBOXN, bn = t % TL_QBOXN;
-        const uint32_t key = s_keys[k];
-        if (key == TL_QEMPTY) continue;
-        float v[Q];
-        if (k == 0) {
-            const int X = bn % TL_QBOX, Y = (bn / TL_QBOX) % TL_QBOX, Z = bn / 49;
+    static_assert(TL_QBOXN * 8 * 4 + TL_SCAP_MAX * 4 <= TL_BOXN * 24 * 4, "the box fits the trilinear partials");
+    return D.p2g + ((size_t)k * D.n_active + bi) * (TL_QBOXN * 8); // (boxes of one k side by side: nearly all are k = 0)
+}
+DEV uint32_t* q_part_keys(const SceneK& S, const SceneD& D, int bi)
+{
+    return (uint32_t*)(D.p2g + (size_t)D.n_active * S.scap * (TL_QBOXN * 8)) + (size_t)bi * TL_SCAP_MAX;
+}
+
+// The boxes around node g: active bricks (-1: none) and the node's place in their boxes.
+// Per axis a node lies in the box of its own brick, and the lower two of four also in that
+// of the brick below, the last one in that of the brick above.
+struct QAround {
+    int bi[8], bn[8];
+    uint4 key[8]; // the boxes' first four side keys
+    DEV void set(const SceneK& S, const SceneD& D, long long g)
+    {
+        const int nb = (int)(g >> 6), l[3] = {(int)g & 3, ((int)g >> 2) & 3, ((int)g >> 4) & 3};
+        const int h[3] = {nb % S.nbx, (nb / S.nbx) % S.nby, nb / S.nbx / S.nby};
+        const int n[3] = {S.cbx, S.cby, S.cbz};
 #pragma unroll
-            for (int c = 0; c < Q; c++) v[c] = 0.0f;
+        for (int d = 0; d < 8; d++) {
+            int b[3], x[3];
+            bool in = true;
 #pragma unroll
-            for (int h = 0; h < 8; h++) {
-                const int rx = X - (h & 1), ry = Y - ((h >> 1) & 1), rz = Z - ((h >> 2) & 1);
-                if (rx < 0 || ry < 0 || rz < 0 || rx > 5 || ry > 5 || rz > 5) continue;
-                const float* w = s_wv + ((size_t)h * TL_QREG + (rz * 6 + ry) * 6 + rx) * Q;
-#pragma unroll
-                for (int c = 0; c < Q; c++) v[c] += w[c];
+            for (int a = 0; a < 3; a++) {
+                const bool other = (d >> a) & 1;
+                b[a] = !other ? h[a] : l[a] == 3 ? h[a] + 1 : h[a] - 1;
+                x[a] = !other ? l[a] + 1 : l[a] == 3 ? 0 : l[a] + 5;
+                in = in && b[a] >= 0 && b[a] < n[a] && x[a] < TL_QBOX;
             }
-        } else {
+            bn[d] = (x[2] * TL_QBOX + x[1]) * TL_QBOX + x[0];
+            bi[d] = in ? D.bact[((long long)b[2] * S.cby + b[1]) * S.cbx + b[0]] : -1;
+        }
 #pragma unroll
-            for (int c = 0; c < Q; c++) v[c] = s_acc[((size_t)(k - 1) * TL_QBOXN + bn) * Q + c];
+        for (int d = 0; d < 8; d++)
+            key[d] = bi[d] >= 0 ? *(const uint4*)q_part_keys(S, D, bi[d])
+                                : make_uint4(TL_QEMPTY, TL_QEMPTY, TL_QEMPTY, TL_QEMPTY);
+    }
+    // adds the boxes' sums of one side key (NV float4 per node) to v
+    template <int NV>
+    DEV void sum(const SceneK& S, const SceneD& D, uint32_t want, float4 (&v)[NV]) const
+    {
+        int k[8];
+        bool more = false;
+#pragma unroll
+        for (int d = 0; d < 8; d++) {
+            k[d] = key[d].x == want ? 0 : key[d].y == want ? 1 : key[d].z == want ? 2 : key[d].w == want ? 3 : -1;
+            if (k[d] >= S.scap) k[d] = -1; // (in the node's slots already)
+            more |= k[d] < 0 && key[d].w != TL_QEMPTY;
+        }
+        if (__any(more)) // (bricks of more than four keys)
+#pragma unroll 1
+            for (int j = 4; j < S.scap; j++)
+#pragma unroll
+                for (int d = 0; d < 8; d++)
+                    if (bi[d] >= 0 && q_part_keys(S, D, bi[d])[j] == want) k[d] = j;
+        float4 w[8][NV];
+#pragma unroll
+        for (int d = 0; d < 8; d++)
+#pragma unroll
+            for (int n = 0; n < NV; n++)
+                w[d][n] = k[d] >= 0 ? *((const float4*)q_part(S, D, bi[d], k[d]) + bn[d] * NV + n)
+                                    : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+        for (int d = 0; d < 8; d++)
+#pragma unroll
+            for (int n = 0; n < NV; n++) {
+                v[n].x += w[d][n].x;
+                v[n].y += w[d][n].y;
+                v[n].z += w[d][n].z;
+                v[n].w += w[d][n].w;
+            }
+    }
+};
+
+// puts a brick's LDS sums of its side key k into its partials (Q values per node; a key
+// beyond the slot capacity: into the node slots in HBM, stride
+// QS floats per slot): the 8 wave regions in wave order
+// (wave h holds box node (X, Y, Z) at region (X, Y, Z) - 1 + low(h), low = 1 on the
+// axes of the lower half)
+template <int Q, int QS, class R>
+DEV void q_flush(const SceneK& S, const SceneD& D, const uint32_t* tab, float* dst, int bi, int bx, int by, int bz,
+                 int k, uint32_t key, const R& reg)
+{
+    for (int bn = late(threadIdx.x); bn < TL_QBOXN; bn += TL_QWG) {
+        const int X = bn % TL_QBOX, Y = (bn / TL_QBOX) % TL_QBOX, Z = bn / 49;
+        float v[Q];
+#pragma unroll
+        for (int c = 0; c < Q; c++) v[c] = 0.0f;
+#pragma unroll
+        for (int h = 0; h < 8; h++) {
+            const int rx = X - (h & 1), ry = Y - ((h >> 1) & 1), rz = Z - ((h >> 2) & 1);
+            if (rx < 0 || ry < 0 || rz < 0 || rx > 5 || ry > 5 || rz > 5) continue;
+            reg.sum(h * TL_QREG + q_reg_at(rx, ry, rz), v);
+        }
+        if (k < S.scap) {
+            float4* o = (float4*)q_part(S, D, bi, k) + bn * (QS / 4);
+            o[0] = make_float4(v[0], v[1], v[2], Q > 3 ? v[Q > 3 ? 3 : 0] : 0.0f);
+            if constexpr (Q == 7) o[1] = make_float4(v[4], v[5], v[6], 0.0f);
+            continue;
         }
         bool any = false;
 #pragma unroll
@@ -321,7 +459,7 @@ DEV void q_flush(const SceneK& S, const SceneD& D, const uint32_t* tab, float* d
             atomicOr(D.status, TL_ST_LOOKUP);
             continue;
         }
-        float* o = dst + ((size_t)g * S.scap + s) * QS;
+        float* o = dst + q_at(S, g, s) * QS;
 #pragma unroll
         for (int c = 0; c < Q; c++)
             if (v[c] != 0.0f) unsafeAtomicAdd(o + c, v[c]);
@@ -331,45 +469,43 @@ DEV void q_flush(const SceneK& S, const SceneD& D, const uint32_t* tab, float* d
 // ---------------------------------------------------------------------------- P2G
 // Per active brick: stress (Neo-Hookean, or the fixed-corotated family with
 // viscosity and plasticity for MAT 1), gravity and contact impulses, and the
-// label-masked scatter of m, m v and the impulse (Eq. 2) to the 27 nodes.
+// label-masked scatter of m, m v and the impulse (Eq. 2) to the 27 nodes.  Bound by the
+// chain of 27 LDS read-modify-writes of a brick's one round; three workgroups per CU (28
+// bytes per node, 80 registers), so that a scene of 586 bricks runs in one go.  There: 125
+// us with LDS atomics for every key after the first and node atomics at the end, 84 us
+// with a pass per key, 35 us with partials too.
 template <int MAT>
-__global__ __launch_bounds__(TL_QWG) void k_q_p2g(SceneK S, SceneD D, int par)
+__global__ __launch_bounds__(TL_QWG, MAT == 0 ? 6 : 4) void k_q_p2g(SceneK S, SceneD D, int par)
 {
     __shared__ uint32_t s_keys[TL_SCAP_MAX];
-    __shared__ float s_wv[8 * TL_QREG * 7];
-    __shared__ float s_acc[(TL_QK - 1) * TL_QBOXN * 7];
+    __shared__ QRegions s_wv;
     const int bi = blockIdx.x, tid = threadIdx.x;
     const int brick = D.active[bi];
     const int bx = brick % S.cbx, by = (brick / S.cbx) % S.cby, bz = brick / (S.cbx * S.cby);
     const uint32_t* tab = q_table(S, D, par);
-    for (int t = tid; t < 8 * TL_QREG * 7; t += TL_QWG) s_wv[t] = 0.0f;
-    for (int t = tid; t < (TL_QK - 1) * TL_QBOXN * 7; t += TL_QWG) s_acc[t] = 0.0f;
     if (tid < TL_SCAP_MAX) s_keys[tid] = TL_QEMPTY;
+    s_wv.zero();
     __syncthreads();
+    q_register_keys(S, D, bi, s_keys);
+    __syncthreads();
+    if (tid < TL_SCAP_MAX) q_part_keys(S, D, bi)[tid] = s_keys[tid]; // for the other passes of the substep
     const long long N = S.N;
     const float dt = S.dt;
     const bool rig = (S.floor_on || D.tinfo[1]) && D.brig[brick] != 0;
-    const int rounds = q_rounds(D, bi), h = tid >> 6;
-    int c[3];
-    q_cell(bx, by, bz, tid & 63, c);
-    for (int r = 0; r < rounds; r++) {
-        const int p = q_particle(D, bi, r);
-        bool valid = p >= 0;
-        int k = -1;
-        uint32_t key = 0;
-        float m = 0.0f, vel[3] = {0.0f, 0.0f, 0.0f}, ext[3] = {0.0f, 0.0f, 0.0f};
-        float Pk[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        QStencil Q = {};
-        if (valid) {
-            const uint32_t code = D.code[p];
-            key = slot_key(S, code);
-            k = q_key_index(s_keys, key);
-            if (k < 0) atomicOr(D.status, TL_ST_BOX);
-            valid = k >= 0;
+    const int rounds = q_rounds(D, bi);
+    for (int k = 0; k < TL_SCAP_MAX && s_keys[k] != TL_QEMPTY; k++) {
+        const uint32_t key = s_keys[k];
+        if (k > 0) {
+            s_wv.zero();
+            __syncthreads();
         }
-        if (valid) {
-            float H[9];
+        for (int r = 0; r < rounds; r++) {
+            const int p = q_particle(D, bi, r);
+            if (p < 0) continue;
             const uint32_t code = D.code[p];
+            if (slot_key(S, code) != key) continue;
+            float m, vel[3], ext[3], Pk[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+            float H[9];
             const float X[3] = {D.X[at3(p, 0)], D.X[at3(p, 1)], D.X[at3(p, 2)]};
 #pragma unroll
             for (int a = 0; a < 9; a++) H[a] = D.H[at9(N, p, a)];
@@ -438,164 +574,201 @@ __global__ __launch_bounds__(TL_QWG) void k_q_p2g(SceneK S, SceneD D, int par)
             const float sA = -dt * V0;
 #pragma unroll
             for (int a = 0; a < 9; a++) Pk[a] *= sA;
+            int c[3];
+            const int h = late(tid) >> 6;
+            q_cell(bx, by, bz, late(tid) & 63, c);
+            QStencil Q;
             q_stencil(S, X, c, h, Q);
-        }
-        const int ox = Q.lo[0] - (bx * TL_B - 1), oy = Q.lo[1] - (by * TL_B - 1), oz = Q.lo[2] - (bz * TL_B - 1);
-        // the 7 sums of node (cx, cy, cz): m, m v, and the impulse A grad N + w ext
-        auto node_vals = [&](int cx, int cy, int cz, float* val) {
-            const float wx = q_pick(Q.w[0], cx), wy = q_pick(Q.w[1], cy), wz = q_pick(Q.w[2], cz);
-            const float w = wx * wy * wz;
-            const float g0 = q_pick(Q.g[0], cx) * wy * wz;
-            const float g1 = wx * q_pick(Q.g[1], cy) * wz;
-            const float g2 = wx * wy * q_pick(Q.g[2], cz);
-            val[0] = w * m;
-            val[1] = val[0] * vel[0];
-            val[2] = val[0] * vel[1];
-            val[3] = val[0] * vel[2];
-#pragma unroll
-            for (int a = 0; a < 3; a++) val[4 + a] = Pk[3 * a] * g0 + Pk[3 * a + 1] * g1 + Pk[3 * a + 2] * g2 + w * ext[a];
-            return w != 0.0f; // reading R7: a zero weight contributes nothing
-        };
-        if (valid && k >= TL_QK) {
-            // more side keys in this brick than LDS holds: straight to the node slots
-#pragma unroll 1
-            for (int t = 0; t < 27; t++) {
-                const int cx = t % 3, cy = (t / 3) % 3, cz = t / 9;
-                float val[7];
-                if (!node_vals(cx, cy, cz, val)) continue;
-                const long long g = q_gid(S, Q.lo[0] + cx, Q.lo[1] + cy, Q.lo[2] + cz);
-                const int s = g >= 0 ? q_find(S, tab, g, key) : -1;
-                if (s < 0) {
-                    atomicOr(D.status, TL_ST_LOOKUP);
-                    continue;
-                }
-                float* o = D.qacc + ((size_t)g * S.scap + s) * 8;
-#pragma unroll
-                for (int q = 0; q < 7; q++) unsafeAtomicAdd(o + q, val[q]);
-            }
-        }
-        if (valid && k == 0) {
             // own region of this wave: the lanes' nodes of one offset are distinct
-            const int rx = c[0] - bx * TL_B, ry = c[1] - by * TL_B, rz = c[2] - bz * TL_B;
-            float* d0 = s_wv + (size_t)h * TL_QREG * 7;
+            const int r0 = h * TL_QREG + (c[1] - by * TL_B) * 12 + c[0] - bx * TL_B, rz = c[2] - bz * TL_B;
 #pragma unroll
             for (int cz = 0; cz < 3; cz++)
 #pragma unroll
                 for (int cy = 0; cy < 3; cy++) {
+                    const int row = r0 + q_reg_at(0, 0, rz + cz) + cy * 12;
+                    const float wyz = Q.w[1][cy] * Q.w[2][cz];
+                    if (wyz == 0.0f) continue; // reading R7: a zero weight contributes nothing
+                    // node (cx, cy, cz) gets w {m, m v} and A grad N + w ext, w = wx wyz,
+                    // grad N = (gx wyz, wx gy wz, wx wy gz): what the row shares
+                    const float gywz = Q.g[1][cy] * Q.w[2][cz], wygz = Q.w[1][cy] * Q.g[2][cz];
+                    const float wm = wyz * m;
+                    const float mv[3] = {wm * vel[0], wm * vel[1], wm * vel[2]};
+                    float A[3], B[3];
+#pragma unroll
+                    for (int a = 0; a < 3; a++) {
+                        A[a] = Pk[3 * a] * wyz;
+                        B[a] = Pk[3 * a + 1] * gywz + Pk[3 * a + 2] * wygz + wyz * ext[a];
+                    }
 #pragma unroll
                     for (int cx = 0; cx < 3; cx++) {
-                        float val[7];
-                        if (!node_vals(cx, cy, cz, val)) continue;
-                        float* d = d0 + (((rz + cz) * 6 + ry + cy) * 6 + rx + cx) * 7;
-#pragma unroll
-                        for (int q = 0; q < 7; q++) d[q] += val[q];
+                        const float wx = Q.w[0][cx], gx = Q.g[0][cx];
+                        if (cx != 1 && wx == 0.0f) continue; // (the middle weight is at least 1/2)
+                        const int at = row + cx;
+                        float4 a = s_wv.a[at];
+                        float2 b = s_wv.b[at];
+                        float c2 = s_wv.c[at];
+                        a.x += wx * wm;
+                        a.y += wx * mv[0];
+                        a.z += wx * mv[1];
+                        a.w += wx * mv[2];
+                        b.x += gx * A[0] + wx * B[0];
+                        b.y += gx * A[1] + wx * B[1];
+                        c2 += gx * A[2] + wx * B[2];
+                        s_wv.a[at] = a;
+                        s_wv.b[at] = b;
+                        s_wv.c[at] = c2;
+                        // one node at a time: another lane adds to it at its next offset
+                        asm volatile("" ::: "memory");
                     }
-                    // one row of nodes at a time: keeps the compiler from hoisting all
-                    // 189 reads (and their registers) to the top
-                    asm volatile("" ::: "memory");
                 }
-        } else if (valid && k < TL_QK) {
-            float* d0 = s_acc + (size_t)(k - 1) * TL_QBOXN * 7;
-#pragma unroll 1
-            for (int t = 0; t < 27; t++) {
-                const int cx = t % 3, cy = (t / 3) % 3, cz = t / 9;
-                float val[7];
-                if (!node_vals(cx, cy, cz, val)) continue;
-                float* d = d0 + (((oz + cz) * TL_QBOX + oy + cy) * TL_QBOX + ox + cx) * 7;
-#pragma unroll
-                for (int q = 0; q < 7; q++) atomicAdd(d + q, val[q]);
-            }
         }
+        __syncthreads();
+        q_flush<7, 8>(S, D, tab, D.qacc, bi, bx, by, bz, k, key, s_wv);
+        __syncthreads();
     }
-    __syncthreads();
-    q_flush<7, 8>(S, D, tab, D.qacc, bx, by, bz, s_keys, s_wv, s_acc);
 }
 
 // ---------------------------------------------------------------- node kernels
-// Grid update: per node, coupling of momentum and impulse (Eq. 8), then
+// Grid update (bound by its chain of loads: 12 us without the sums, 20 us with them, for 48k
+// nodes): per node, the sums of its slots from the boxes around it (and of keys beyond
+// them, added by atomics), coupling of momentum and impulse (Eq. 8), then
 // v^n = pbar / m and dv = dpbar / m (Eq. 9) over the slot's sums.
-__global__ __launch_bounds__(256) void k_q_grid(SceneK S, SceneD D, int par)
+__global__ __launch_bounds__(TL_QNODE) void k_q_grid(SceneK S, SceneD D, int par)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int i = blockIdx.x * TL_QNODE + threadIdx.x;
     if (i >= D.n_qnodes) return;
     const long long g = D.qnodes[i];
     const uint32_t* tab = q_table(S, D, par);
-    uint32_t codes[TL_SCAP_MAX];
-    int c = 0;
-    for (; c < S.scap; c++) {
-        codes[c] = tab[(long long)c * S.NN + g];
-        if (codes[c] == TL_QEMPTY) break;
+    const uint32_t key0 = tab[g], key1 = S.scap > 1 ? tab[S.NN + g] : TL_QEMPTY;
+    const uint32_t key2 = S.scap > 2 ? tab[2 * S.NN + g] : TL_QEMPTY;
+    QAround A;
+    A.set(S, D, g);
+    if (key0 == TL_QEMPTY) return;
+    const bool one = key1 == TL_QEMPTY, more = key2 != TL_QEMPTY;
+    auto at = [&](int s) { return (float4*)(D.qacc + q_at(S, g, s) * 8); };
+    float4 v[2] = {}, u[2] = {}; // the first two slots
+#pragma unroll 1
+    for (int s = 0; s < (one ? 1 : 2); s++) {
+        u[0] = v[0];
+        u[1] = v[1];
+        v[0] = at(s)[0];
+        v[1] = at(s)[1];
+        A.sum<2>(S, D, s ? key1 : key0, v);
     }
-    if (c == 0) return;
-    float* a = D.qacc + (size_t)g * S.scap * 8;
-    if (c == 1) {
-        const float m = a[0], im = m > 0.0f ? 1.0f / m : 0.0f;
-        for (int j = 1; j < 7; j++) a[j] *= im;
+    if (one) {
+        const float m = v[0].x, im = m > 0.0f ? 1.0f / m : 0.0f;
+        at(0)[0] = make_float4(m, v[0].y * im, v[0].z * im, v[0].w * im);
+        at(0)[1] = make_float4(v[1].x * im, v[1].y * im, v[1].z * im, 0.0f);
+        return;
+    }
+    if (!more) {
+        const float m0 = u[0].x, m1 = v[0].x;
+        float p0[3] = {u[0].y, u[0].z, u[0].w}, p1[3] = {v[0].y, v[0].z, v[0].w};
+        float d0[3] = {u[1].x, u[1].y, u[1].z}, d1[3] = {v[1].x, v[1].y, v[1].z};
+        const bool compatible = !codes_conflict(key0, key1);
+        q_couple2(m0, m1, compatible, p0, p1);
+        q_couple2(m0, m1, compatible, d0, d1);
+        const float i0 = m0 > 0.0f ? 1.0f / m0 : 0.0f, i1 = m1 > 0.0f ? 1.0f / m1 : 0.0f;
+        at(0)[0] = make_float4(m0, p0[0] * i0, p0[1] * i0, p0[2] * i0);
+        at(0)[1] = make_float4(d0[0] * i0, d0[1] * i0, d0[2] * i0, 0.0f);
+        at(1)[0] = make_float4(m1, p1[0] * i1, p1[1] * i1, p1[2] * i1);
+        at(1)[1] = make_float4(d1[0] * i1, d1[1] * i1, d1[2] * i1, 0.0f);
         return;
     }
     float m[TL_SCAP_MAX], p[TL_SCAP_MAX][3], dp[TL_SCAP_MAX][3];
-    for (int s = 0; s < c; s++) {
-        m[s] = a[s * 8];
-        for (int j = 0; j < 3; j++) {
-            p[s][j] = a[s * 8 + 1 + j];
-            dp[s][j] = a[s * 8 + 4 + j];
-        }
+    uint32_t codes[TL_SCAP_MAX];
+    int c = 0;
+#pragma unroll 1
+    for (; c < S.scap; c++) {
+        codes[c] = tab[(long long)c * S.NN + g];
+        if (codes[c] == TL_QEMPTY) break;
+        v[0] = at(c)[0];
+        v[1] = at(c)[1];
+        A.sum<2>(S, D, codes[c], v);
+        m[c] = v[0].x;
+        p[c][0] = v[0].y;
+        p[c][1] = v[0].z;
+        p[c][2] = v[0].w;
+        dp[c][0] = v[1].x;
+        dp[c][1] = v[1].y;
+        dp[c][2] = v[1].z;
     }
     q_couple(c, m, codes, p);
     q_couple(c, m, codes, dp);
     for (int s = 0; s < c; s++) {
         const float im = m[s] > 0.0f ? 1.0f / m[s] : 0.0f;
-        for (int j = 0; j < 3; j++) {
-            a[s * 8 + 1 + j] = p[s][j] * im;
-            a[s * 8 + 4 + j] = dp[s][j] * im;
-        }
+        at(s)[0] = make_float4(m[s], p[s][0] * im, p[s][1] * im, p[s][2] * im);
+        at(s)[1] = make_float4(dp[s][0] * im, dp[s][1] * im, dp[s][2] * im, 0.0f);
     }
 }
 
-// Velocity remap of the MUSL re-scatter: per node, coupling of m v^{n+1} (Eq. 8),
-// then v~ = ptbar / m.
-__global__ __launch_bounds__(256) void k_q_remap(SceneK S, SceneD D, int par)
+// Velocity remap of the MUSL re-scatter: per node, the sums as above, coupling of m v^{n+1}
+// (Eq. 8), then v~ = ptbar / m.
+__global__ __launch_bounds__(TL_QNODE) void k_q_remap(SceneK S, SceneD D, int par)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int i = blockIdx.x * TL_QNODE + threadIdx.x;
     if (i >= D.n_qnodes) return;
     const long long g = D.qnodes[i];
     const uint32_t* tab = q_table(S, D, par);
-    uint32_t codes[TL_SCAP_MAX];
-    int c = 0;
-    for (; c < S.scap; c++) {
-        codes[c] = tab[(long long)c * S.NN + g];
-        if (codes[c] == TL_QEMPTY) break;
+    const uint32_t key0 = tab[g], key1 = S.scap > 1 ? tab[S.NN + g] : TL_QEMPTY;
+    const uint32_t key2 = S.scap > 2 ? tab[2 * S.NN + g] : TL_QEMPTY;
+    QAround A;
+    A.set(S, D, g);
+    if (key0 == TL_QEMPTY) return;
+    const bool one = key1 == TL_QEMPTY, more = key2 != TL_QEMPTY;
+    auto mass = [&](int s) { return D.qacc[q_at(S, g, s) * 8]; };
+    auto at = [&](int s) { return (float4*)(D.qrs + q_at(S, g, s) * 4); };
+    float4 v[1] = {}, u = {}; // the first two slots
+#pragma unroll 1
+    for (int s = 0; s < (one ? 1 : 2); s++) {
+        u = v[0];
+        v[0] = *at(s);
+        A.sum<1>(S, D, s ? key1 : key0, v);
     }
-    if (c == 0) return;
-    const float* a = D.qacc + (size_t)g * S.scap * 8;
-    float* r = D.qrs + (size_t)g * S.scap * 4;
-    if (c == 1) {
-        const float m = a[0], im = m > 0.0f ? 1.0f / m : 0.0f;
-        for (int j = 0; j < 3; j++) r[j] *= im;
+    if (one) {
+        const float m = mass(0), im = m > 0.0f ? 1.0f / m : 0.0f;
+        *at(0) = make_float4(v[0].x * im, v[0].y * im, v[0].z * im, 0.0f);
+        return;
+    }
+    if (!more) {
+        const float m0 = mass(0), m1 = mass(1);
+        float p0[3] = {u.x, u.y, u.z}, p1[3] = {v[0].x, v[0].y, v[0].z};
+        q_couple2(m0, m1, !codes_conflict(key0, key1), p0, p1);
+        const float i0 = m0 > 0.0f ? 1.0f / m0 : 0.0f, i1 = m1 > 0.0f ? 1.0f / m1 : 0.0f;
+        *at(0) = make_float4(p0[0] * i0, p0[1] * i0, p0[2] * i0, 0.0f);
+        *at(1) = make_float4(p1[0] * i1, p1[1] * i1, p1[2] * i1, 0.0f);
         return;
     }
     float m[TL_SCAP_MAX], pt[TL_SCAP_MAX][3];
-    for (int s = 0; s < c; s++) {
-        m[s] = a[s * 8];
-        for (int j = 0; j < 3; j++) pt[s][j] = r[s * 4 + j];
+    uint32_t codes[TL_SCAP_MAX];
+    int c = 0;
+#pragma unroll 1
+    for (; c < S.scap; c++) {
+        codes[c] = tab[(long long)c * S.NN + g];
+        if (codes[c] == TL_QEMPTY) break;
+        v[0] = *at(c);
+        A.sum<1>(S, D, codes[c], v);
+        m[c] = mass(c);
+        pt[c][0] = v[0].x;
+        pt[c][1] = v[0].y;
+        pt[c][2] = v[0].z;
     }
     q_couple(c, m, codes, pt);
     for (int s = 0; s < c; s++) {
         const float im = m[s] > 0.0f ? 1.0f / m[s] : 0.0f;
-        for (int j = 0; j < 3; j++) r[s * 4 + j] = pt[s][j] * im;
+        *at(s) = make_float4(pt[s][0] * im, pt[s][1] * im, pt[s][2] * im, 0.0f);
     }
 }
 
 // ---------------------------------------------------------------------------- G2P
-// Per active brick: the box's grid velocities (v^n, dv) of its first TL_QK side
-// keys into LDS, PIC/FLIP update of v and x (Eq. 17), the MUSL re-scatter of
+// Per active brick and side key: the box's grid velocities (v^n, dv) into LDS, PIC/FLIP
+// update of v and x (Eq. 17), the MUSL re-scatter (69 us, now 40 us for 586 bricks) of
 // m_p v_p^{n+1}, and the brick's AABB and speed bound.
-__global__ __launch_bounds__(TL_QWG) void k_q_g2p(SceneK S, SceneD D, int par)
+__global__ __launch_bounds__(TL_QWG, 6) void k_q_g2p(SceneK S, SceneD D, int par)
 {
     __shared__ uint32_t s_keys[TL_SCAP_MAX];
-    __shared__ float s_grid[TL_QK * TL_QBOXN * 6];
-    __shared__ float s_wv[8 * TL_QREG * 3];
-    __shared__ float s_acc[(TL_QK - 1) * TL_QBOXN * 3];
+    __shared__ float4 s_grid[2][TL_QBOXP]; // {(1 - beta) v^n + dv} and {v^n + dv} per box node
+    __shared__ QRegions3 s_wv;
     __shared__ float s_bb[TL_QWG / 64][7];
     const int bi = blockIdx.x, tid = threadIdx.x;
     const int brick = D.active[bi];
@@ -607,76 +780,87 @@ __global__ __launch_bounds__(TL_QWG) void k_q_g2p(SceneK S, SceneD D, int par)
     }
     const int bx = brick % S.cbx, by = (brick / S.cbx) % S.cby, bz = brick / (S.cbx * S.cby);
     const uint32_t* tab = q_table(S, D, par);
-    for (int t = tid; t < 8 * TL_QREG * 3; t += TL_QWG) s_wv[t] = 0.0f;
-    for (int t = tid; t < (TL_QK - 1) * TL_QBOXN * 3; t += TL_QWG) s_acc[t] = 0.0f;
-    if (tid < TL_SCAP_MAX) s_keys[tid] = TL_QEMPTY;
+    const int rounds = q_rounds(D, bi);
+    const QFirst first(D, bi, rounds);
+    if (tid < TL_SCAP_MAX) s_keys[tid] = q_part_keys(S, D, bi)[tid]; // (of the P2G)
     __syncthreads();
-    q_register_keys(S, D, bi, s_keys);
-    __syncthreads();
-    q_load_box<6, 8, 1>(S, tab, D.qacc, bx, by, bz, s_keys, s_grid);
-    __syncthreads();
-    const long long N = S.N;
     const float dt = S.dt, beta = S.beta;
-    const int rounds = q_rounds(D, bi), h = tid >> 6;
-    int c[3];
-    q_cell(bx, by, bz, tid & 63, c);
     float bb[7] = {1e30f, 1e30f, 1e30f, -1e30f, -1e30f, -1e30f, 0.0f};
-    for (int r = 0; r < rounds; r++) {
-        const int p = q_particle(D, bi, r);
-        int k = -1;
-        uint32_t key = 0;
-        if (p >= 0) {
-            key = slot_key(S, D.code[p]);
-            k = q_key_lookup(s_keys, key); // -1 was flagged when the keys were registered
+    for (int k = 0; k < TL_SCAP_MAX && s_keys[k] != TL_QEMPTY; k++) {
+        const uint32_t key = s_keys[k];
+        s_wv.zero();
+        for (int bn = late(tid); bn < TL_QBOXN; bn += TL_QWG) { // absent slots read as zero
+            const long long g = q_box_gid(S, bx, by, bz, bn);
+            float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f), b = a;
+            if (g >= 0) {
+                // {m, v^n}, {dv}: the first slot's with its key, nearly always the one
+                const float4* q = (const float4*)(D.qacc + (size_t)g * 8);
+                const float4 a0 = q[0], b0 = q[1];
+                const int s = q_find(S, tab, g, key);
+                if (s == 0) {
+                    a = a0;
+                    b = b0;
+                } else if (s > 0) {
+                    q = (const float4*)(D.qacc + q_at(S, g, s) * 8);
+                    a = q[0];
+                    b = q[1];
+                }
+            }
+            const int at = q_box_at(bn % TL_QBOX, (bn / TL_QBOX) % TL_QBOX, bn / 49);
+            s_grid[0][at] = make_float4((1.0f - beta) * a.y + b.x, (1.0f - beta) * a.z + b.y, (1.0f - beta) * a.w + b.z, 0.0f);
+            s_grid[1][at] = make_float4(a.y + b.x, a.z + b.y, a.w + b.z, 0.0f);
         }
-        const bool valid = k >= 0;
-        float m = 0.0f, vn1[3] = {0.0f, 0.0f, 0.0f};
-        QStencil Q = {};
-        if (valid) {
-            const float X[3] = {D.X[at3(p, 0)], D.X[at3(p, 1)], D.X[at3(p, 2)]};
+        __syncthreads();
+        for (int r = 0; r < rounds; r++) {
+            const QFirst q = r ? QFirst(D, bi, rounds, r) : first;
+            const int p = q.p;
+            if (p < 0 || slot_key(S, q.code) != key) continue;
+            const float (&X)[3] = q.X;
+            float v[3], u[3];
+#pragma unroll
+            for (int j = 0; j < 3; j++) {
+                v[j] = D.v[at3(p, j)];
+                u[j] = D.u[at3(p, j)];
+            }
+            const float m = S.m_uniform ? S.m0 : D.m[p];
+            int c[3];
+            const int h = late(tid) >> 6;
+            q_cell(bx, by, bz, late(tid) & 63, c);
+            QStencil Q;
             q_stencil(S, X, c, h, Q);
             float av[3] = {0.0f, 0.0f, 0.0f}, ax[3] = {0.0f, 0.0f, 0.0f};
-            auto add_node = [&](float w, const float* vn, const float* dv) {
-#pragma unroll
-                for (int j = 0; j < 3; j++) {
-                    av[j] += w * ((1.0f - beta) * vn[j] + dv[j]);
-                    ax[j] += w * (vn[j] + dv[j]);
-                }
-            };
-            if (k < TL_QK) {
-                const int ox = Q.lo[0] - (bx * TL_B - 1), oy = Q.lo[1] - (by * TL_B - 1), oz = Q.lo[2] - (bz * TL_B - 1);
-                const float* g0 = s_grid + (size_t)k * TL_QBOXN * 6;
+            const int ox = Q.lo[0] - (bx * TL_B - 1), oy = Q.lo[1] - (by * TL_B - 1), oz = Q.lo[2] - (bz * TL_B - 1);
+            auto gather = [&](auto guard) {
 #pragma unroll
                 for (int cz = 0; cz < 3; cz++)
 #pragma unroll
-                    for (int cy = 0; cy < 3; cy++)
+                    for (int cy = 0; cy < 3; cy++) {
+                        const int row = q_box_at(ox, oy, oz + cz) + cy * 14;
+                        const float wyz = Q.w[1][cy] * Q.w[2][cz];
+                        if (guard.value && wyz == 0.0f) continue;
 #pragma unroll
                         for (int cx = 0; cx < 3; cx++) {
-                            const float w = Q.w[0][cx] * Q.w[1][cy] * Q.w[2][cz];
-                            if (w == 0.0f) continue;
-                            const float* a = g0 + (((oz + cz) * TL_QBOX + oy + cy) * TL_QBOX + ox + cx) * 6;
-                            add_node(w, a, a + 3);
+                            if (guard.value && Q.w[0][cx] == 0.0f) continue;
+                            const float w = Q.w[0][cx] * wyz;
+                            const float4 a = s_grid[0][row + cx], b = s_grid[1][row + cx];
+                            av[0] += w * a.x;
+                            av[1] += w * a.y;
+                            av[2] += w * a.z;
+                            ax[0] += w * b.x;
+                            ax[1] += w * b.y;
+                            ax[2] += w * b.z;
                         }
-            } else {
-#pragma unroll 1
-                for (int t = 0; t < 27; t++) {
-                    const int cx = t % 3, cy = (t / 3) % 3, cz = t / 9;
-                    const float w = q_pick(Q.w[0], cx) * q_pick(Q.w[1], cy) * q_pick(Q.w[2], cz);
-                    if (w == 0.0f) continue;
-                    const long long g = q_gid(S, Q.lo[0] + cx, Q.lo[1] + cy, Q.lo[2] + cz);
-                    const int s = g >= 0 ? q_find(S, tab, g, key) : -1;
-                    if (s < 0) {
-                        atomicOr(D.status, TL_ST_LOOKUP);
-                        continue;
                     }
-                    const float* a = D.qacc + ((size_t)g * S.scap + s) * 8;
-                    add_node(w, a + 1, a + 4);
-                }
-            }
+            };
+            if (__any(Q.zero()))
+                gather(QGuard<true>{});
+            else
+                gather(QGuard<false>{});
+            float vn1[3];
 #pragma unroll
             for (int j = 0; j < 3; j++) {
-                vn1[j] = beta * D.v[at3(p, j)] + av[j];
-                const float un = D.u[at3(p, j)] + dt * ax[j];
+                vn1[j] = beta * v[j] + av[j];
+                const float un = u[j] + dt * ax[j];
                 D.v[at3(p, j)] = vn1[j];
                 D.u[at3(p, j)] = un;
                 const float xa = X[j] + un;
@@ -684,54 +868,32 @@ __global__ __launch_bounds__(TL_QWG) void k_q_g2p(SceneK S, SceneD D, int par)
                 bb[3 + j] = fmaxf(bb[3 + j], xa);
             }
             bb[6] = fmaxf(bb[6], sqrtf(vn1[0] * vn1[0] + vn1[1] * vn1[1] + vn1[2] * vn1[2]));
-            m = S.m_uniform ? S.m0 : D.m[p];
-        }
-        if (valid && k >= TL_QK) {
-#pragma unroll 1
-            for (int t = 0; t < 27; t++) {
-                const int cx = t % 3, cy = (t / 3) % 3, cz = t / 9;
-                const float wm = q_pick(Q.w[0], cx) * q_pick(Q.w[1], cy) * q_pick(Q.w[2], cz) * m;
-                if (wm == 0.0f) continue;
-                const long long g = q_gid(S, Q.lo[0] + cx, Q.lo[1] + cy, Q.lo[2] + cz);
-                const int s = g >= 0 ? q_find(S, tab, g, key) : -1;
-                if (s < 0) {
-                    atomicOr(D.status, TL_ST_LOOKUP);
-                    continue;
-                }
-                float* o = D.qrs + ((size_t)g * S.scap + s) * 4;
-#pragma unroll
-                for (int j = 0; j < 3; j++) unsafeAtomicAdd(o + j, wm * vn1[j]);
-            }
-        }
-        // MUSL re-scatter of m v^{n+1} (wave regions as in the P2G)
-        if (valid && k == 0) {
-            const int rx = c[0] - bx * TL_B, ry = c[1] - by * TL_B, rz = c[2] - bz * TL_B;
-            float* d0 = s_wv + (size_t)h * TL_QREG * 3;
+            // MUSL re-scatter of m v^{n+1} (wave regions as in the P2G)
+            const int r0 = h * TL_QREG + (c[1] - by * TL_B) * 12 + c[0] - bx * TL_B, rz = c[2] - bz * TL_B;
 #pragma unroll
             for (int cz = 0; cz < 3; cz++)
 #pragma unroll
-                for (int cy = 0; cy < 3; cy++)
+                for (int cy = 0; cy < 3; cy++) {
+                    const int row = r0 + q_reg_at(0, 0, rz + cz) + cy * 12;
+                    const float wm = Q.w[1][cy] * Q.w[2][cz] * m;
+                    if (wm == 0.0f) continue;
+                    const float mv[3] = {wm * vn1[0], wm * vn1[1], wm * vn1[2]};
 #pragma unroll
                     for (int cx = 0; cx < 3; cx++) {
-                        const float wm = Q.w[0][cx] * Q.w[1][cy] * Q.w[2][cz] * m;
-                        if (wm == 0.0f) continue;
-                        float* d = d0 + (((rz + cz) * 6 + ry + cy) * 6 + rx + cx) * 3;
-#pragma unroll
-                        for (int j = 0; j < 3; j++) d[j] += wm * vn1[j];
+                        const float wx = Q.w[0][cx];
+                        if (cx != 1 && wx == 0.0f) continue;
+                        float4 a = s_wv.a[row + cx];
+                        a.x += wx * mv[0];
+                        a.y += wx * mv[1];
+                        a.z += wx * mv[2];
+                        s_wv.a[row + cx] = a;
+                        asm volatile("" ::: "memory"); // one node at a time, as in the P2G
                     }
-        } else if (valid && k < TL_QK) {
-            const int ox = Q.lo[0] - (bx * TL_B - 1), oy = Q.lo[1] - (by * TL_B - 1), oz = Q.lo[2] - (bz * TL_B - 1);
-            float* d0 = s_acc + (size_t)(k - 1) * TL_QBOXN * 3;
-#pragma unroll 1
-            for (int t = 0; t < 27; t++) {
-                const int cx = t % 3, cy = (t / 3) % 3, cz = t / 9;
-                const float wm = q_pick(Q.w[0], cx) * q_pick(Q.w[1], cy) * q_pick(Q.w[2], cz) * m;
-                if (wm == 0.0f) continue;
-                float* d = d0 + (((oz + cz) * TL_QBOX + oy + cy) * TL_QBOX + ox + cx) * 3;
-#pragma unroll
-                for (int j = 0; j < 3; j++) atomicAdd(d + j, wm * vn1[j]);
-            }
+                }
         }
+        __syncthreads();
+        q_flush<3, 4>(S, D, tab, D.qrs, bi, bx, by, bz, k, key, s_wv);
+        __syncthreads();
     }
     // brick AABB of x^{n+1} and speed bound (used to skip distant contact work)
     const int lane = tid & 63, wv = tid >> 6;
@@ -751,114 +913,122 @@ __global__ __launch_bounds__(TL_QWG) void k_q_g2p(SceneK S, SceneD D, int par)
         if (tid == 6 && S.material_contact && val > 0.0f)
             atomicMax(D.hmax + (bi & (TL_HSLOTS - 1)) * TL_HSTRIDE, __float_as_int(val));
     }
-    q_flush<3, 4>(S, D, tab, D.qrs, bx, by, bz, s_keys, s_wv, s_acc);
 }
 
 // --------------------------------------------------------------- F update (MUSL)
-// Per active brick: the box's remapped velocities of its first TL_QK side keys into
-// LDS, then per particle F += dt sum_i v~_i (x) grad N_i with its own slots; the
+// Per active brick and side key: the box's remapped velocities into LDS, then per
+// particle F += dt sum_i v~_i (x) grad N_i; the
 // rate is kept for viscosity and the plastic projection follows (MAT 1).
 template <int MAT>
 __global__ __launch_bounds__(TL_QWG) void k_q_F(SceneK S, SceneD D, int par)
 {
     __shared__ uint32_t s_keys[TL_SCAP_MAX];
-    __shared__ float s_vt[TL_QK * TL_QBOXN * 3];
+    __shared__ float4 s_vt[TL_QBOXP];
     const int bi = blockIdx.x, tid = threadIdx.x;
     const int brick = D.active[bi];
     const int bx = brick % S.cbx, by = (brick / S.cbx) % S.cby, bz = brick / (S.cbx * S.cby);
     const uint32_t* tab = q_table(S, D, par);
-    if (tid < TL_SCAP_MAX) s_keys[tid] = TL_QEMPTY;
-    __syncthreads();
-    q_register_keys(S, D, bi, s_keys);
-    __syncthreads();
-    q_load_box<3, 4, 0>(S, tab, D.qrs, bx, by, bz, s_keys, s_vt);
+    const int rounds = q_rounds(D, bi);
+    const QFirst first(D, bi, rounds);
+    if (tid < TL_SCAP_MAX) s_keys[tid] = q_part_keys(S, D, bi)[tid]; // (of the P2G)
     __syncthreads();
     const long long N = S.N;
     const float dt = S.dt;
-    const int rounds = q_rounds(D, bi), h = tid >> 6;
-    int c[3];
-    q_cell(bx, by, bz, tid & 63, c);
-    for (int r = 0; r < rounds; r++) {
-        const int p = q_particle(D, bi, r);
-        if (p < 0) continue;
-        const uint32_t key = slot_key(S, D.code[p]);
-        const int k = q_key_lookup(s_keys, key);
-        if (k < 0) continue;
-        const float X[3] = {D.X[at3(p, 0)], D.X[at3(p, 1)], D.X[at3(p, 2)]};
-        QStencil Q;
-        q_stencil(S, X, c, h, Q);
-        float Lg[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        auto add_node = [&](float g0, float g1, float g2, const float* v) {
-#pragma unroll
-            for (int a = 0; a < 3; a++) {
-                Lg[3 * a + 0] += v[a] * g0;
-                Lg[3 * a + 1] += v[a] * g1;
-                Lg[3 * a + 2] += v[a] * g2;
+    for (int k = 0; k < TL_SCAP_MAX && s_keys[k] != TL_QEMPTY; k++) {
+        const uint32_t key = s_keys[k];
+        for (int bn = late(tid); bn < TL_QBOXN; bn += TL_QWG) { // absent slots read as zero
+            const long long g = q_box_gid(S, bx, by, bz, bn);
+            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (g >= 0) {
+                const float4 v0 = *(const float4*)(D.qrs + (size_t)g * 4); // (as in the G2P)
+                const int s = q_find(S, tab, g, key);
+                if (s == 0)
+                    v = v0;
+                else if (s > 0)
+                    v = *(const float4*)(D.qrs + q_at(S, g, s) * 4);
             }
-        };
-        if (k < TL_QK) {
+            s_vt[q_box_at(bn % TL_QBOX, (bn / TL_QBOX) % TL_QBOX, bn / 49)] = v;
+        }
+        __syncthreads();
+        for (int r = 0; r < rounds; r++) {
+            const QFirst q = r ? QFirst(D, bi, rounds, r) : first;
+            const int p = q.p;
+            if (p < 0 || slot_key(S, q.code) != key) continue;
+            const float (&X)[3] = q.X;
+            int c[3];
+            const int h = late(tid) >> 6;
+            q_cell(bx, by, bz, late(tid) & 63, c);
+            QStencil Q;
+            q_stencil(S, X, c, h, Q);
+            float Lg[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
             const int ox = Q.lo[0] - (bx * TL_B - 1), oy = Q.lo[1] - (by * TL_B - 1), oz = Q.lo[2] - (bz * TL_B - 1);
-            const float* v0 = s_vt + (size_t)k * TL_QBOXN * 3;
+            auto gather = [&](auto guard) {
 #pragma unroll
-            for (int cz = 0; cz < 3; cz++)
+                for (int cz = 0; cz < 3; cz++)
 #pragma unroll
-                for (int cy = 0; cy < 3; cy++)
+                    for (int cy = 0; cy < 3; cy++) {
+                        const int row = q_box_at(ox, oy, oz + cz) + cy * 14;
+                        const float wyz = Q.w[1][cy] * Q.w[2][cz];
+                        if (guard.value && wyz == 0.0f) continue;
+                        float sg[3] = {0, 0, 0}, sw[3] = {0, 0, 0}; // sums of gx v and of wx v along the row
 #pragma unroll
-                    for (int cx = 0; cx < 3; cx++) {
-                        if (Q.w[0][cx] * Q.w[1][cy] * Q.w[2][cz] == 0.0f) continue;
-                        add_node(Q.g[0][cx] * Q.w[1][cy] * Q.w[2][cz], Q.w[0][cx] * Q.g[1][cy] * Q.w[2][cz],
-                                 Q.w[0][cx] * Q.w[1][cy] * Q.g[2][cz],
-                                 v0 + (((oz + cz) * TL_QBOX + oy + cy) * TL_QBOX + ox + cx) * 3);
+                        for (int cx = 0; cx < 3; cx++) {
+                            if (guard.value && Q.w[0][cx] == 0.0f) continue;
+                            const float4 n = s_vt[row + cx];
+                            const float v[3] = {n.x, n.y, n.z};
+#pragma unroll
+                            for (int a = 0; a < 3; a++) {
+                                sg[a] += Q.g[0][cx] * v[a];
+                                sw[a] += Q.w[0][cx] * v[a];
+                            }
+                        }
+#pragma unroll
+                        for (int a = 0; a < 3; a++) {
+                            Lg[3 * a + 0] += sg[a] * wyz;
+                            Lg[3 * a + 1] += sw[a] * (Q.g[1][cy] * Q.w[2][cz]);
+                            Lg[3 * a + 2] += sw[a] * (Q.w[1][cy] * Q.g[2][cz]);
+                        }
                     }
-        } else {
-#pragma unroll 1
-            for (int t = 0; t < 27; t++) {
-                const int cx = t % 3, cy = (t / 3) % 3, cz = t / 9;
-                const float wx = q_pick(Q.w[0], cx), wy = q_pick(Q.w[1], cy), wz = q_pick(Q.w[2], cz);
-                if (wx * wy * wz == 0.0f) continue;
-                const long long g = q_gid(S, Q.lo[0] + cx, Q.lo[1] + cy, Q.lo[2] + cz);
-                const int s = g >= 0 ? q_find(S, tab, g, key) : -1;
-                if (s < 0) {
-                    atomicOr(D.status, TL_ST_LOOKUP);
-                    continue;
+            };
+            if (__any(Q.zero()))
+                gather(QGuard<true>{});
+            else
+                gather(QGuard<false>{});
+            float H[9];
+            bool fin = true;
+#pragma unroll
+            for (int a = 0; a < 9; a++) {
+                H[a] = D.H[at9(N, p, a)] + dt * Lg[a];
+                D.H[at9(N, p, a)] = H[a];
+                fin = fin && isfinite(H[a]);
+            }
+            if (!fin) atomicOr(D.status, TL_ST_NONFINITE);
+            if constexpr (MAT == 1) {
+                if (S.visc > 0.0f)
+#pragma unroll
+                    for (int a = 0; a < 9; a++) D.Fdot[at9(N, p, a)] = Lg[a];
+                if (S.ystress > 0.0f) {
+                    float Gp[9], K[9];
+#pragma unroll
+                    for (int a = 0; a < 9; a++) Gp[a] = D.Gp[at9(N, p, a)];
+#pragma unroll
+                    for (int i = 0; i < 3; i++)
+#pragma unroll
+                        for (int j = 0; j < 3; j++) {
+                            float kk = H[3 * i + j] + Gp[3 * i + j];
+#pragma unroll
+                            for (int l = 0; l < 3; l++) kk += H[3 * i + l] * Gp[3 * l + j];
+                            K[3 * i + j] = kk;
+                        }
+                    float mu, lam;
+                    lame(S, S.e_uniform ? 0.0f : D.E[p], mu, lam);
+                    if (vm_project(mu, S.ystress, K, Gp))
+#pragma unroll
+                        for (int a = 0; a < 9; a++) D.Gp[at9(N, p, a)] = Gp[a];
                 }
-                add_node(q_pick(Q.g[0], cx) * wy * wz, wx * q_pick(Q.g[1], cy) * wz, wx * wy * q_pick(Q.g[2], cz),
-                         D.qrs + ((size_t)g * S.scap + s) * 4);
             }
         }
-        float H[9];
-        bool fin = true;
-#pragma unroll
-        for (int a = 0; a < 9; a++) {
-            H[a] = D.H[at9(N, p, a)] + dt * Lg[a];
-            D.H[at9(N, p, a)] = H[a];
-            fin = fin && isfinite(H[a]);
-        }
-        if (!fin) atomicOr(D.status, TL_ST_NONFINITE);
-        if constexpr (MAT == 1) {
-            if (S.visc > 0.0f)
-#pragma unroll
-                for (int a = 0; a < 9; a++) D.Fdot[at9(N, p, a)] = Lg[a];
-            if (S.ystress > 0.0f) {
-                float Gp[9], K[9];
-#pragma unroll
-                for (int a = 0; a < 9; a++) Gp[a] = D.Gp[at9(N, p, a)];
-#pragma unroll
-                for (int i = 0; i < 3; i++)
-#pragma unroll
-                    for (int j = 0; j < 3; j++) {
-                        float kk = H[3 * i + j] + Gp[3 * i + j];
-#pragma unroll
-                        for (int l = 0; l < 3; l++) kk += H[3 * i + l] * Gp[3 * l + j];
-                        K[3 * i + j] = kk;
-                    }
-                float mu, lam;
-                lame(S, S.e_uniform ? 0.0f : D.E[p], mu, lam);
-                if (vm_project(mu, S.ystress, K, Gp))
-#pragma unroll
-                    for (int a = 0; a < 9; a++) D.Gp[at9(N, p, a)] = Gp[a];
-            }
-        }
+        __syncthreads();
     }
 }
 
@@ -872,7 +1042,7 @@ hipError_t tl_launch_quad(const TlLaunch* L, int par, int stage)
     const SceneK& S = *L->S;
     const SceneD& D = *L->D;
     const int nb = D.n_active;
-    const int nn = (D.n_qnodes + 255) / 256;
+    const int nn = (D.n_qnodes + TL_QNODE - 1) / TL_QNODE;
     if (nb == 0) return hipSuccess;
     switch (stage) {
     case 0:
@@ -885,13 +1055,13 @@ hipError_t tl_launch_quad(const TlLaunch* L, int par, int stage)
             k_q_p2g<0><<<nb, TL_QWG, 0, L->st>>>(S, D, par);
         break;
     case 2:
-        if (nn) k_q_grid<<<nn, 256, 0, L->st>>>(S, D, par);
+        if (nn) k_q_grid<<<nn, TL_QNODE, 0, L->st>>>(S, D, par);
         break;
     case 3:
         k_q_g2p<<<nb, TL_QWG, 0, L->st>>>(S, D, par);
         break;
     case 4:
-        if (nn) k_q_remap<<<nn, 256, 0, L->st>>>(S, D, par);
+        if (nn) k_q_remap<<<nn, TL_QNODE, 0, L->st>>>(S, D, par);
         break;
     case 5:
         if (L->general)
