@@ -173,6 +173,60 @@ DEV bool neo_hookean(float mu, float lam, const float* H, float* P)
     return true;
 }
 
+// Eigenvalues e and eigenvectors Q (columns) of the symmetric matrix H + H^T + H^T H by
+// cyclic Jacobi rotations, at most four sweeps (FP32 converges within them).  An
+// off-diagonal entry below a quarter ulp of its diagonal is taken as zero, and the sweeps
+// end when every lane of the wave is done (mostly after two or three).  Reciprocals and
+// square roots of the rotations are the hardware's (1 ulp): t only has to make the entry
+// small, and c and s = t c are normalised to rounding.  Bound by instructions: with IEEE
+// divisions, full rotations of both triangles and four sweeps always, two of these were
+// two thirds of a plastic P2G.
+DEV void eigen_sym(const float* H, float e[3], float* Q)
+{
+    float A[6]; // 00, 11, 22, 01, 02, 12
+#pragma unroll
+    for (int n = 0; n < 6; n++) {
+        const int i = n < 3 ? n : n == 5 ? 1 : 0, j = n < 3 ? n : n == 3 ? 1 : 2;
+        float a = H[3 * i + j] + H[3 * j + i];
+#pragma unroll
+        for (int k = 0; k < 3; k++) a += H[3 * k + i] * H[3 * k + j];
+        A[n] = a;
+    }
+#pragma unroll
+    for (int a = 0; a < 9; a++) Q[a] = (a & 3) == 0 ? 1.0f : 0.0f;
+#pragma unroll 1
+    for (int sweep = 0; sweep < 4; sweep++) {
+        bool work = false;
+#pragma unroll
+        for (int pq = 0; pq < 3; pq++) {
+            // rows p < q, the third one r; places of (p, q), (p, r), (q, r)
+            const int p = pq == 2 ? 1 : 0, q = pq == 0 ? 1 : 2, r = 3 - p - q;
+            const int opq = 2 + p + q, opr = 2 + p + r, oqr = 2 + q + r;
+            const float apq = A[opq], size = fabsf(A[p]) + fabsf(A[q]);
+            if (!(fabsf(apq) > fmaxf(1.4e-8f * size, 1e-36f))) continue;
+            work = true;
+            const float th = (A[q] - A[p]) * 0.5f * __builtin_amdgcn_rcpf(apq);
+            const float t = copysignf(__builtin_amdgcn_rcpf(fabsf(th) + __builtin_amdgcn_sqrtf(th * th + 1.0f)), th);
+            const float c = __builtin_amdgcn_rsqf(t * t + 1.0f), sn = t * c;
+            A[p] -= t * apq;
+            A[q] += t * apq;
+            A[opq] = 0.0f;
+            const float ap = A[opr], aq = A[oqr];
+            A[opr] = c * ap - sn * aq;
+            A[oqr] = sn * ap + c * aq;
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                const float qp = Q[3 * k + p], qq = Q[3 * k + q];
+                Q[3 * k + p] = c * qp - sn * qq;
+                Q[3 * k + q] = sn * qp + c * qq;
+            }
+        }
+        if (!__any(work)) break;
+    }
+#pragma unroll
+    for (int k = 0; k < 3; k++) e[k] = A[k];
+}
+
 // Fixed-corotated first Piola-Kirchhoff stress P = 2 mu (F - R) + lambda (J - 1)
 // J F^{-T} (Sec. III-B), F = R S the polar decomposition, in terms of H = F - I so
 // that small strains keep their precision in FP32: with E = F^T F - I = H + H^T +
@@ -181,52 +235,12 @@ DEV bool neo_hookean(float mu, float lam, const float* H, float* P)
 // Returns false when J <= 0 or the state is not finite.
 DEV bool fixed_corotated(float mu, float lam, const float* H, float* P)
 {
-    float A[9];
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            float a = H[3 * i + j] + H[3 * j + i];
-#pragma unroll
-            for (int k = 0; k < 3; k++) a += H[3 * k + i] * H[3 * k + j];
-            A[3 * i + j] = a;
-        }
-    float Q[9] = {1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0.0f, 0.0f, 0.0f, 1.0f};
-    // cyclic Jacobi sweeps (a fixed count: FP32 converges within four)
-#pragma unroll 1
-    for (int sweep = 0; sweep < 4; sweep++) {
-#pragma unroll
-        for (int pq = 0; pq < 3; pq++) {
-            const int p = pq == 2 ? 1 : 0, q = pq == 0 ? 1 : 2;
-            const float apq = A[3 * p + q];
-            if (apq == 0.0f) continue;
-            const float th = (A[3 * q + q] - A[3 * p + p]) / (2.0f * apq);
-            const float t = copysignf(1.0f, th) / (fabsf(th) + sqrtf(th * th + 1.0f));
-            const float c = 1.0f / sqrtf(t * t + 1.0f), sn = t * c;
-#pragma unroll
-            for (int k = 0; k < 3; k++) {
-                const float akp = A[3 * k + p], akq = A[3 * k + q];
-                A[3 * k + p] = c * akp - sn * akq;
-                A[3 * k + q] = sn * akp + c * akq;
-            }
-#pragma unroll
-            for (int k = 0; k < 3; k++) {
-                const float apk = A[3 * p + k], aqk = A[3 * q + k];
-                A[3 * p + k] = c * apk - sn * aqk;
-                A[3 * q + k] = sn * apk + c * aqk;
-            }
-#pragma unroll
-            for (int k = 0; k < 3; k++) {
-                const float qkp = Q[3 * k + p], qkq = Q[3 * k + q];
-                Q[3 * k + p] = c * qkp - sn * qkq;
-                Q[3 * k + q] = sn * qkp + c * qkq;
-            }
-        }
-    }
+    float ev[3], Q[9];
+    eigen_sym(H, ev, Q);
     float sm1[3], sinv[3];
 #pragma unroll
     for (int k = 0; k < 3; k++) {
-        const float e = A[4 * k], r = sqrtf(1.0f + e);
+        const float e = ev[k], r = sqrtf(1.0f + e);
         if (!(1.0f + e > 0.0f)) return false;
         sm1[k] = e / (r + 1.0f);
         sinv[k] = 1.0f / r;
@@ -328,50 +342,11 @@ DEV void add_viscous(float eta, const float* H, const float* Fdot, float* P)
 // G becomes (I + G) M.  Updates G and K; returns whether it yielded.
 DEV bool vm_project(float mu, float sigma_y, float* K, float* G)
 {
-    float A[9];
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            float a = K[3 * i + j] + K[3 * j + i];
-#pragma unroll
-            for (int k = 0; k < 3; k++) a += K[3 * k + i] * K[3 * k + j];
-            A[3 * i + j] = a;
-        }
-    float V[9] = {1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0.0f, 0.0f, 0.0f, 1.0f};
-#pragma unroll 1
-    for (int sweep = 0; sweep < 4; sweep++) {
-#pragma unroll
-        for (int pq = 0; pq < 3; pq++) {
-            const int p = pq == 2 ? 1 : 0, q = pq == 0 ? 1 : 2;
-            const float apq = A[3 * p + q];
-            if (apq == 0.0f) continue;
-            const float th = (A[3 * q + q] - A[3 * p + p]) / (2.0f * apq);
-            const float t = copysignf(1.0f, th) / (fabsf(th) + sqrtf(th * th + 1.0f));
-            const float c = 1.0f / sqrtf(t * t + 1.0f), sn = t * c;
-#pragma unroll
-            for (int k = 0; k < 3; k++) {
-                const float akp = A[3 * k + p], akq = A[3 * k + q];
-                A[3 * k + p] = c * akp - sn * akq;
-                A[3 * k + q] = sn * akp + c * akq;
-            }
-#pragma unroll
-            for (int k = 0; k < 3; k++) {
-                const float apk = A[3 * p + k], aqk = A[3 * q + k];
-                A[3 * p + k] = c * apk - sn * aqk;
-                A[3 * q + k] = sn * apk + c * aqk;
-            }
-#pragma unroll
-            for (int k = 0; k < 3; k++) {
-                const float vkp = V[3 * k + p], vkq = V[3 * k + q];
-                V[3 * k + p] = c * vkp - sn * vkq;
-                V[3 * k + q] = sn * vkp + c * vkq;
-            }
-        }
-    }
+    float ev[3], V[9];
+    eigen_sym(K, ev, V);
     float eps[3];
 #pragma unroll
-    for (int k = 0; k < 3; k++) eps[k] = 0.5f * log1pf(A[4 * k]);
+    for (int k = 0; k < 3; k++) eps[k] = 0.5f * log1pf(ev[k]);
     const float tr = (eps[0] + eps[1] + eps[2]) * (1.0f / 3.0f);
     float dev[3], nd = 0.0f;
 #pragma unroll
