@@ -36,7 +36,7 @@
 #define TL_QBOX 7
 #define TL_QBOXN 343      // nodes of a brick's 7x7x7 box
 #define TL_QWG 512        // threads of a brick workgroup
-#define TL_QNODE 64       // threads of a workgroup of the node kernels
+#define TL_QNODE 256      // threads of a workgroup of the node kernels (8 per node)
 #define TL_QEMPTY 0xFFFFFFFFu
 // LDS places of a wave's 6x6x6 region and of a brick's 7x7x7 box, in 16-byte units: two z
 // planes side by side, and pitches that put the 16 cells of two parity classes (a quarter
@@ -356,70 +356,58 @@ DEV uint32_t* q_part_keys(const SceneK& S, const SceneD& D, int bi)
     return (uint32_t*)(D.p2g + (size_t)D.n_active * S.scap * (TL_QBOXN * 8)) + (size_t)bi * TL_SCAP_MAX;
 }
 
-// The boxes around node g: active bricks (-1: none) and the node's place in their boxes.
-// Per axis a node lies in the box of its own brick, and the lower two of four also in that
-// of the brick below, the last one in that of the brick above.
+// One of the 8 boxes around node g, by the lane's place d in its group of 8 (a lane per box:
+// its loads run side by side, and the code stays short; with a thread per node a scene of a
+// few bricks waited longer for the code than for the data): the active brick (-1: none) and
+// the node's place in its box.  Per axis a node lies in the box of its own brick, and the
+// lower two of four also in that of the brick below, the last one in that of the brick above.
 struct QAround {
-    int bi[8], bn[8];
-    uint4 key[8]; // the boxes' first four side keys
-    DEV void set(const SceneK& S, const SceneD& D, long long g)
+    int bi, bn;
+    uint4 key; // the box's first four side keys
+    DEV void set(const SceneK& S, const SceneD& D, long long g, int d)
     {
         const int nb = (int)(g >> 6), l[3] = {(int)g & 3, ((int)g >> 2) & 3, ((int)g >> 4) & 3};
         const int h[3] = {nb % S.nbx, (nb / S.nbx) % S.nby, nb / S.nbx / S.nby};
         const int n[3] = {S.cbx, S.cby, S.cbz};
+        int b[3], x[3];
+        bool in = true;
 #pragma unroll
-        for (int d = 0; d < 8; d++) {
-            int b[3], x[3];
-            bool in = true;
-#pragma unroll
-            for (int a = 0; a < 3; a++) {
-                const bool other = (d >> a) & 1;
-                b[a] = !other ? h[a] : l[a] == 3 ? h[a] + 1 : h[a] - 1;
-                x[a] = !other ? l[a] + 1 : l[a] == 3 ? 0 : l[a] + 5;
-                in = in && b[a] >= 0 && b[a] < n[a] && x[a] < TL_QBOX;
-            }
-            bn[d] = (x[2] * TL_QBOX + x[1]) * TL_QBOX + x[0];
-            bi[d] = in ? D.bact[((long long)b[2] * S.cby + b[1]) * S.cbx + b[0]] : -1;
+        for (int a = 0; a < 3; a++) {
+            const bool other = (d >> a) & 1;
+            b[a] = !other ? h[a] : l[a] == 3 ? h[a] + 1 : h[a] - 1;
+            x[a] = !other ? l[a] + 1 : l[a] == 3 ? 0 : l[a] + 5;
+            in = in && b[a] >= 0 && b[a] < n[a] && x[a] < TL_QBOX;
         }
-#pragma unroll
-        for (int d = 0; d < 8; d++)
-            key[d] = bi[d] >= 0 ? *(const uint4*)q_part_keys(S, D, bi[d])
-                                : make_uint4(TL_QEMPTY, TL_QEMPTY, TL_QEMPTY, TL_QEMPTY);
+        bn = (x[2] * TL_QBOX + x[1]) * TL_QBOX + x[0];
+        bi = in ? D.bact[((long long)b[2] * S.cby + b[1]) * S.cbx + b[0]] : -1;
+        key = bi >= 0 ? *(const uint4*)q_part_keys(S, D, bi)
+                      : make_uint4(TL_QEMPTY, TL_QEMPTY, TL_QEMPTY, TL_QEMPTY);
     }
-    // adds the boxes' sums of one side key (NV float4 per node) to v
+    // adds the boxes' sums of one side key (NV float4 per node) to v in all 8 lanes (in a
+    // fixed order)
     template <int NV>
     DEV void sum(const SceneK& S, const SceneD& D, uint32_t want, float4 (&v)[NV]) const
     {
-        int k[8];
-        bool more = false;
-#pragma unroll
-        for (int d = 0; d < 8; d++) {
-            k[d] = key[d].x == want ? 0 : key[d].y == want ? 1 : key[d].z == want ? 2 : key[d].w == want ? 3 : -1;
-            if (k[d] >= S.scap) k[d] = -1; // (in the node's slots already)
-            more |= k[d] < 0 && key[d].w != TL_QEMPTY;
-        }
-        if (__any(more)) // (bricks of more than four keys)
-#pragma unroll 1
+        int k = key.x == want ? 0 : key.y == want ? 1 : key.z == want ? 2 : key.w == want ? 3 : -1;
+        if (k < 0 && key.w != TL_QEMPTY) // (a brick of more than four keys)
             for (int j = 4; j < S.scap; j++)
+                if (q_part_keys(S, D, bi)[j] == want) k = j;
+        if (k >= S.scap) k = -1; // (in the node's slots already)
 #pragma unroll
-                for (int d = 0; d < 8; d++)
-                    if (bi[d] >= 0 && q_part_keys(S, D, bi[d])[j] == want) k[d] = j;
-        float4 w[8][NV];
-#pragma unroll
-        for (int d = 0; d < 8; d++)
-#pragma unroll
-            for (int n = 0; n < NV; n++)
-                w[d][n] = k[d] >= 0 ? *((const float4*)q_part(S, D, bi[d], k[d]) + bn[d] * NV + n)
-                                    : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-        for (int d = 0; d < 8; d++)
-#pragma unroll
-            for (int n = 0; n < NV; n++) {
-                v[n].x += w[d][n].x;
-                v[n].y += w[d][n].y;
-                v[n].z += w[d][n].z;
-                v[n].w += w[d][n].w;
-            }
+        for (int n = 0; n < NV; n++) {
+            float4 w = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (k >= 0) w = *((const float4*)q_part(S, D, bi, k) + bn * NV + n);
+            v[n].x += all8(w.x);
+            v[n].y += all8(w.y);
+            v[n].z += all8(w.z);
+            v[n].w += all8(w.w);
+        }
+    }
+    DEV static float all8(float w)
+    {
+        w += lane_xor<1>(w);
+        w += lane_xor<2>(w);
+        return w + lane_xor<4>(w);
     }
 };
 
@@ -629,20 +617,20 @@ __global__ __launch_bounds__(TL_QWG, MAT == 0 ? 6 : 4) void k_q_p2g(SceneK S, Sc
 }
 
 // ---------------------------------------------------------------- node kernels
-// Grid update (bound by its chain of loads: 12 us without the sums, 20 us with them, for 48k
-// nodes): per node, the sums of its slots from the boxes around it (and of keys beyond
+// Grid update (bound by its chain of loads: 12 us with sums made by atomics, 16 us with a lane
+// per box, 20 us with a thread per node, for 48k nodes): per node, the sums of its slots from the boxes around it (and of keys beyond
 // them, added by atomics), coupling of momentum and impulse (Eq. 8), then
 // v^n = pbar / m and dv = dpbar / m (Eq. 9) over the slot's sums.
 __global__ __launch_bounds__(TL_QNODE) void k_q_grid(SceneK S, SceneD D, int par)
 {
-    const int i = blockIdx.x * TL_QNODE + threadIdx.x;
+    const int i = (blockIdx.x * TL_QNODE + threadIdx.x) >> 3, d = threadIdx.x & 7;
     if (i >= D.n_qnodes) return;
     const long long g = D.qnodes[i];
     const uint32_t* tab = q_table(S, D, par);
     const uint32_t key0 = tab[g], key1 = S.scap > 1 ? tab[S.NN + g] : TL_QEMPTY;
     const uint32_t key2 = S.scap > 2 ? tab[2 * S.NN + g] : TL_QEMPTY;
     QAround A;
-    A.set(S, D, g);
+    A.set(S, D, g, d);
     if (key0 == TL_QEMPTY) return;
     const bool one = key1 == TL_QEMPTY, more = key2 != TL_QEMPTY;
     auto at = [&](int s) { return (float4*)(D.qacc + q_at(S, g, s) * 8); };
@@ -656,12 +644,14 @@ __global__ __launch_bounds__(TL_QNODE) void k_q_grid(SceneK S, SceneD D, int par
         A.sum<2>(S, D, s ? key1 : key0, v);
     }
     if (one) {
+        if (d) return;
         const float m = v[0].x, im = m > 0.0f ? 1.0f / m : 0.0f;
         at(0)[0] = make_float4(m, v[0].y * im, v[0].z * im, v[0].w * im);
         at(0)[1] = make_float4(v[1].x * im, v[1].y * im, v[1].z * im, 0.0f);
         return;
     }
     if (!more) {
+        if (d) return;
         const float m0 = u[0].x, m1 = v[0].x;
         float p0[3] = {u[0].y, u[0].z, u[0].w}, p1[3] = {v[0].y, v[0].z, v[0].w};
         float d0[3] = {u[1].x, u[1].y, u[1].z}, d1[3] = {v[1].x, v[1].y, v[1].z};
@@ -693,6 +683,7 @@ __global__ __launch_bounds__(TL_QNODE) void k_q_grid(SceneK S, SceneD D, int par
         dp[c][1] = v[1].y;
         dp[c][2] = v[1].z;
     }
+    if (d) return;
     q_couple(c, m, codes, p);
     q_couple(c, m, codes, dp);
     for (int s = 0; s < c; s++) {
@@ -706,14 +697,14 @@ __global__ __launch_bounds__(TL_QNODE) void k_q_grid(SceneK S, SceneD D, int par
 // (Eq. 8), then v~ = ptbar / m.
 __global__ __launch_bounds__(TL_QNODE) void k_q_remap(SceneK S, SceneD D, int par)
 {
-    const int i = blockIdx.x * TL_QNODE + threadIdx.x;
+    const int i = (blockIdx.x * TL_QNODE + threadIdx.x) >> 3, d = threadIdx.x & 7;
     if (i >= D.n_qnodes) return;
     const long long g = D.qnodes[i];
     const uint32_t* tab = q_table(S, D, par);
     const uint32_t key0 = tab[g], key1 = S.scap > 1 ? tab[S.NN + g] : TL_QEMPTY;
     const uint32_t key2 = S.scap > 2 ? tab[2 * S.NN + g] : TL_QEMPTY;
     QAround A;
-    A.set(S, D, g);
+    A.set(S, D, g, d);
     if (key0 == TL_QEMPTY) return;
     const bool one = key1 == TL_QEMPTY, more = key2 != TL_QEMPTY;
     auto mass = [&](int s) { return D.qacc[q_at(S, g, s) * 8]; };
@@ -726,11 +717,13 @@ __global__ __launch_bounds__(TL_QNODE) void k_q_remap(SceneK S, SceneD D, int pa
         A.sum<1>(S, D, s ? key1 : key0, v);
     }
     if (one) {
+        if (d) return;
         const float m = mass(0), im = m > 0.0f ? 1.0f / m : 0.0f;
         *at(0) = make_float4(v[0].x * im, v[0].y * im, v[0].z * im, 0.0f);
         return;
     }
     if (!more) {
+        if (d) return;
         const float m0 = mass(0), m1 = mass(1);
         float p0[3] = {u.x, u.y, u.z}, p1[3] = {v[0].x, v[0].y, v[0].z};
         q_couple2(m0, m1, !codes_conflict(key0, key1), p0, p1);
@@ -753,6 +746,7 @@ __global__ __launch_bounds__(TL_QNODE) void k_q_remap(SceneK S, SceneD D, int pa
         pt[c][1] = v[0].y;
         pt[c][2] = v[0].z;
     }
+    if (d) return;
     q_couple(c, m, codes, pt);
     for (int s = 0; s < c; s++) {
         const float im = m[s] > 0.0f ? 1.0f / m[s] : 0.0f;
@@ -1042,7 +1036,7 @@ hipError_t tl_launch_quad(const TlLaunch* L, int par, int stage)
     const SceneK& S = *L->S;
     const SceneD& D = *L->D;
     const int nb = D.n_active;
-    const int nn = (D.n_qnodes + TL_QNODE - 1) / TL_QNODE;
+    const int nn = (int)(((long long)D.n_qnodes * 8 + TL_QNODE - 1) / TL_QNODE);
     if (nb == 0) return hipSuccess;
     switch (stage) {
     case 0:
