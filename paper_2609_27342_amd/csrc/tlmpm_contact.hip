@@ -591,7 +591,11 @@ DEV bool pair_impulse(const SceneK& S, const PState& o, const PState& r, float u
 // spring of a pair is kept by both particles (each in its own list, oriented for
 // the pair's lower index): both sides evaluate the pair with the same operands, so
 // the two copies stay equal and no particle reads its partner's list.  A list is
-// only searched by partner, so its order does not matter.
+// only searched by partner, so its order does not matter.  Bound by its chains of loads
+// (about two thirds of the wave cycles wait).  Waves work by themselves and go on past
+// candidates without a possible partner: 127 us a substep for 1.07M candidates of a
+// 14M-particle scene (37 % of them searched), 149 us with two workgroup barriers per
+// chunk; 169 against 193 us for a batch of 64 scenes.
 
 // the first c (<= TL_BCAP) candidate numbers of bucket h in increasing order
 // (sorting network on eight values; unused places hold INT_MAX)
