@@ -798,6 +798,14 @@ __global__ __launch_bounds__(TL_QWG, 6) void k_q_g2p(SceneK S, SceneD D, int par
                     q = (const float4*)(D.qacc + q_at(S, g, s) * 8);
                     a = q[0];
                     b = q[1];
+                } else if (k < S.scap) {
+                    // no slot for a sum that the P2G put into this box (its other keys
+                    // report that where they are added to the slots)
+                    q = (const float4*)q_part(S, D, bi, k) + 2 * bn;
+                    const float4 m = q[0], f = q[1];
+                    if (m.x != 0.0f || m.y != 0.0f || m.z != 0.0f || m.w != 0.0f || f.x != 0.0f || f.y != 0.0f ||
+                        f.z != 0.0f)
+                        atomicOr(D.status, TL_ST_LOOKUP);
                 }
             }
             const int at = q_box_at(bn % TL_QBOX, (bn / TL_QBOX) % TL_QBOX, bn / 49);

@@ -85,3 +85,23 @@ def test_particles_on_half_planes(tl, planes, n_codes):
     s["X"] = X.astype(np.float32)
     print(f"[case] quadratic half planes {planes} codes={n_codes} n={X.shape[0]}", flush=True)
     _check(tl, s, rng.integers(0, n_codes, X.shape[0]), 58)
+
+
+@pytest.mark.parametrize("scap", [1, 2])
+def test_sums_without_a_slot_are_reported(tl, scap):
+    """Bricks of one key each that meet at nodes with room for one key less: besides the full
+    slot list, the sums left without a slot are reported."""
+    s = W.box_scene(n_cells=(12, 4, 4), seed=59, floor_on=0, stencil=1, slot_capacity=scap)
+    brick = np.floor((s["X"][:, 0].astype(np.float64) - s["params"]["origin"][0]) / s["params"]["dx"]).astype(int) // 4
+    code = brick if scap == 1 else brick + (brick == 1) * (s["X"][:, 1] > 0.02)
+    n = code.size
+    dig = np.zeros((n, 4), np.uint8)
+    dig[:, :2] = CODES[code]
+    print(f"[case] quadratic sums without a slot scap={scap} n={n}", flush=True)
+    g = tl.Scene(s)
+    g.write(digits=dig)
+    g.step([])
+    status, text = g.status_detail()
+    assert status == tl.E_SLOT_OVERFLOW
+    bits = int(text.rsplit(" ", 1)[1])
+    assert bits == 2 + 8  # TL_ST_SLOT and TL_ST_LOOKUP
