@@ -123,7 +123,8 @@ struct tlmpm_scene {
     int in_batch = 0; // member of a live batch: single-scene calls are refused
     int fuse_bricks = 0; // one-stream substeps up to this many active bricks (tuning at creation)
     std::vector<int> active_host;
-    size_t stage_bytes = 0; // of the partial arrays, where a state copy is staged
+    char* stage = nullptr;  // where a state copy is staged (memory that holds nothing between substeps)
+    size_t stage_bytes = 0;
     Timing prof;
     GraphCache graphs;
     Fork fork;
@@ -167,6 +168,7 @@ static TlLaunch single_launch(const tlmpm_scene* sc)
     L.D = &sc->D;
     L.any_material = sc->K.material_contact;
     L.general = general_path(sc->K);
+    L.frac = sc->D.T != nullptr;
     L.st = sc->st;
     return L;
 }
@@ -243,6 +245,8 @@ struct Offsets {
         aabb, wpart, Fdot, Gp, wacc, Jmat, Jrig, brig, bmixed, ccode, ckeys, gmeta, gperm, bround, tools, tinfo, ctr, bact, status, dirty, bdirty, pcell, cand_idx, coff, cmask, cstatic, bcand, hbin, hmax, uanc, uanc_x, uref, bor, umm,
         bcount, bids, crec, htab, hnext, ph_n, ph_q, ph_u,
         qcode, qacc, qrs, qnodes, qround, qmap, total;
+    size_t stage_bytes; // from p2g on: the partials and what is free behind them
+    int xcap;           // second boxes there is room for
     uint32_t hmask;
 };
 
@@ -312,7 +316,8 @@ long long count_active(const tlmpm_scene_desc* d)
     return n;
 }
 
-Offsets plan(const tlmpm_scene_desc* d, long long n_active)
+// xcap: second boxes wanted (the offsets depend on it, the total does not)
+Offsets plan(const tlmpm_scene_desc* d, long long n_active, int xcap)
 {
     Dims g = dims_of(d);
     Layout L;
@@ -320,7 +325,6 @@ Offsets plan(const tlmpm_scene_desc* d, long long n_active)
     size_t N = (size_t)std::max<long long>(g.N, 1);
     size_t f = sizeof(float);
     o.X = L.take(3 * N * f);
-    o.T = d->stencil == 0 ? L.take(3 * N * f) : 0;
     o.u = L.take(3 * N * f);
     o.v = L.take(3 * N * f);
     o.H = L.take(9 * N * f);
@@ -333,23 +337,38 @@ Offsets plan(const tlmpm_scene_desc* d, long long n_active)
     o.V0 = d->vol0 ? L.take(N * f) : 0;
     o.cell_start = L.take(((size_t)g.n_bricks * TL_CELLS + 1) * 4);
     o.active = L.take((size_t)g.n_bricks * 4);
-    o.binfo = L.take((size_t)n_active * sizeof(int4));
-    o.ball = L.take((size_t)g.n_bricks * 4);
-    o.bkey = L.take((size_t)g.n_bricks * 4);
     o.cnt0 = L.take((size_t)g.NN);
     o.cnt1 = L.take((size_t)g.NN);
     const size_t scap = slot_cap(d);
     o.sc0 = L.take((size_t)g.NN * scap * 4);
     o.sc1 = L.take((size_t)g.NN * scap * 4);
-    o.tstamp = L.take(2 * 4);
-    o.p2g = L.take((size_t)n_active * scap * TL_BOXN * 8 * f); // 7 components padded to 8
-    o.rs = L.take((size_t)n_active * scap * TL_BOXN * 4 * f);
-    o.p2g_x = L.take((size_t)n_active * scap * TL_BOXN * 8 * f);
-    o.rs_x = L.take((size_t)n_active * scap * TL_BOXN * 4 * f);
-    // these four arrays also stage state copies: at least one 48-byte row per particle (a
-    // few bricks with very many particles per cell would not reach that)
-    const size_t staged = L.take(0) - o.p2g;
-    if (staged < N * 48) L.take(N * 48 - staged);
+    // Partials: a box of every active brick in p2g and rs, and room for as many second boxes
+    // (p2g_x, rs_x).  Only the xcap bricks whose later rounds run in workgroups of their own
+    // have one, and the quadratic stencil, whose boxes take 10976 + 64 of the 12000 bytes, has
+    // none.  Behind them, from the end of that room back, lie the brick tables, and the
+    // positions T in the cells where they fit (up to about 60 particles per cell with 8
+    // slots, fewer than 8 with one slot; P2G forms them from X in other scenes).
+    const size_t box = scap * TL_BOXN * f; // one float of a box
+    o.p2g = L.take((size_t)n_active * box * 8); // 7 components padded to 8
+    o.rs = L.take((size_t)n_active * box * 4);
+    o.p2g_x = L.take((size_t)n_active * box * 8);
+    L.take((size_t)n_active * box * 4);
+    size_t end = L.take(0);
+    const size_t front = d->stencil == 0 ? o.p2g_x : o.p2g + (size_t)n_active * (scap * 343 * 8 * f + TL_SCAP_MAX * 4);
+    auto fits = [&](size_t bytes) { return end - front >= bytes + 15; };
+    auto back = [&](size_t bytes) { // (a grid with far more bricks than active ones: an array of its own)
+        if (!fits(bytes)) return L.take(bytes);
+        end = (end - bytes) & ~size_t(15);
+        return end;
+    };
+    o.tstamp = back(2 * 4);
+    o.binfo = back((size_t)n_active * sizeof(int4));
+    o.ball = back((size_t)g.n_bricks * 4);
+    o.bkey = back((size_t)g.n_bricks * 4);
+    o.xcap = d->stencil == 0 && n_active ? (int)std::min<size_t>(xcap, (end - front) / (12 * box)) : 0;
+    o.rs_x = o.p2g_x + (size_t)o.xcap * box * 8;
+    o.T = d->stencil == 0 && fits(3 * N * f + (size_t)o.xcap * box * 12) ? back(3 * N * f) : 0;
+    o.stage_bytes = end - o.p2g;
     o.xp2g = L.take((size_t)n_active * 4);
     o.xrs = L.take((size_t)n_active * 4);
     o.aabb_x = L.take((size_t)g.n_bricks * 8 * f);
@@ -359,7 +378,7 @@ Offsets plan(const tlmpm_scene_desc* d, long long n_active)
     o.bact = L.take((size_t)g.n_bricks * 4);
     o.hist = L.take((size_t)(TL_MAX_TOOLS + 1) * 4 * N * f);
     o.aabb = L.take((size_t)g.n_bricks * 8 * f);
-    o.wpart = L.take((size_t)g.n_bricks * TL_MAX_TOOLS * 6 * sizeof(double));
+    o.wpart = L.take((size_t)n_active * TL_MAX_TOOLS * 6 * sizeof(double));
     o.Fdot = d->viscosity > 0.0f ? L.take(9 * N * f) : 0;
     o.Gp = d->yield_stress > 0.0f ? L.take(9 * N * f) : 0;
     o.wacc = L.take(TL_MAX_TOOLS * 6 * sizeof(double));
@@ -495,7 +514,7 @@ extern "C" tlmpm_status tlmpm_scene_footprint(const tlmpm_scene_desc* desc, size
     tlmpm_status s = validate(desc);
     if (s) return s;
     if (!device_bytes) return fail(TLMPM_E_INVALID, "null output");
-    *device_bytes = plan(desc, count_active(desc)).total;
+    *device_bytes = plan(desc, count_active(desc), 0).total;
     return TLMPM_OK;
 }
 
@@ -536,7 +555,8 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
             bact[b] = (int)active.size();
             active.push_back((int)b);
         }
-    Offsets o = plan(d, (long long)active.size());
+    const tlmpm_tuning tun = tuning_now();
+    const Offsets o = plan(d, (long long)active.size(), xcap_of((long long)active.size(), tun));
     if (!ws || bytes < o.total) return fail(TLMPM_E_NOMEM, "workspace smaller than tlmpm_scene_footprint()");
 
     tlmpm_scene* sc = new tlmpm_scene();
@@ -544,7 +564,7 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     sc->prof.st = sc->st;
 
     sc->max_cuts = d->max_cuts;
-    sc->fuse_bricks = tuning_now().one_stream_bricks;
+    sc->fuse_bricks = tun.one_stream_bricks;
     sc->n_bricks = (int)g.n_bricks;
     sc->cur = 0;
     sc->rsb = 0;
@@ -601,7 +621,6 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     K.material = d->material;
     K.visc = d->viscosity;
     K.ystress = d->yield_stress;
-    const tlmpm_tuning tun = tuning_now();
     K.pair_blocks = pair_blocks_of(N, tun);
     K.stencil = d->stencil;
     K.pair_skip = (d->material_contact && d->stencil == 0 && tun.pair_skip) ? 1 : 0;
@@ -611,8 +630,7 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     // workgroups on the GPU, so a brick with extra rounds lengthens the whole launch;
     // smaller scenes (the many-scene batches) and larger ones measured slower with the
     // extra launch slots than the rounds cost.
-    const size_t na = active.size();
-    K.xcap = xcap_of((long long)na, tun);
+    K.xcap = o.xcap;
     float vmax0 = d->vol0_uniform;
     if (d->vol0)
         for (long long p = 0; p < N; p++) vmax0 = std::max(vmax0, d->vol0[p]);
@@ -622,7 +640,7 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     SceneD& D = sc->D;
     memset(&D, 0, sizeof(D));
     D.X = (float*)(base + o.X);
-    D.T = d->stencil == 0 ? (float*)(base + o.T) : nullptr;
+    D.T = o.T ? (float*)(base + o.T) : nullptr;
     D.u = (float*)(base + o.u);
     D.v = (float*)(base + o.v);
     D.H = (float*)(base + o.H);
@@ -648,7 +666,11 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     D.rs = (float*)(base + o.rs);
     D.p2g_x = (float*)(base + o.p2g_x);
     D.rs_x = (float*)(base + o.rs_x);
-    sc->stage_bytes = o.xp2g - o.p2g; // (the four partial arrays follow one another)
+    // a state copy is staged in the partials, or, with very many particles per brick, in the
+    // impulse array, which every substep writes before it reads it
+    const size_t jrig_bytes = 3 * (size_t)N * sizeof(float);
+    sc->stage = base + (o.stage_bytes >= jrig_bytes ? o.p2g : o.Jrig);
+    sc->stage_bytes = std::max(o.stage_bytes, jrig_bytes);
     D.xp2g = (int*)(base + o.xp2g);
     D.xrs = (int*)(base + o.xrs);
     D.aabb_x = (float*)(base + o.aabb_x);
@@ -809,7 +831,7 @@ extern "C" tlmpm_status tlmpm_create_scene(const tlmpm_scene_desc* d, void* ws, 
     // contact-history stamp 1 (stored stamps of 0 read as the previous substep's
     // empty history), no F update pending
     if ((e = tl_launch_fill_i32(D.ctr, 1, 1, sc->st)) != hipSuccess) return bail(e, "counters");
-    if (d->stencil == 0 && (e = tl_launch_frac(&K, &D, sc->st)) != hipSuccess) return bail(e, "cell positions");
+    if (D.T && (e = tl_launch_frac(&K, &D, sc->st)) != hipSuccess) return bail(e, "cell positions");
     // cells of bricks without particles (the summaries below cover the others): a zero
     // would read as a cell of code 0 and give the nodes next to it a slot of that code
     if ((e = tl_launch_fill_i32((int*)D.ccode, g.n_bricks * TL_CELLS, (int)TL_CC_EMPTY, sc->st)) != hipSuccess)
@@ -1345,9 +1367,9 @@ static uint64_t code_to_ternary(uint32_t c, int K)
 }
 
 // Copies the wanted fields to the caller's buffers.  They are first brought into the
-// caller's order on the device (k_export), in the partial arrays: with no F update pending
-// they hold nothing that is still needed (the next P2G and G2P write them before they are
-// read).  Where the fields do not fit, a range of particles at a time.
+// caller's order on the device (k_export), in the partial arrays or the impulse array: with
+// no F update pending they hold nothing that is still needed (the next substep writes them
+// before it reads them).  Where the fields do not fit, a range of particles at a time.
 extern "C" tlmpm_status tlmpm_read_state(tlmpm_scene* sc, uint32_t mask, void* const* out)
 {
     if (tlmpm_status r = refuse_batched(sc)) return r;
@@ -1367,7 +1389,7 @@ extern "C" tlmpm_status tlmpm_read_state(tlmpm_scene* sc, uint32_t mask, void* c
         row += bytes[f];
     }
     if (N > 0 && row > 0) {
-        char* stage = (char*)sc->D.p2g;
+        char* stage = sc->stage;
         // each field starts 256-byte aligned
         const long long fit = ((long long)sc->stage_bytes - 8 * 256) / (long long)row;
         if (fit < 1) return fail(TLMPM_E_DEVICE, "no room to stage a state copy");
@@ -1891,6 +1913,7 @@ static tlmpm_status batch_create(tlmpm_scene* const* scenes, int32_t n_scenes, v
     L.Ks = (const SceneK*)(base + P.Ks);
     L.Ds = (const SceneD*)(base + P.Ds);
     L.st = b->st;
+    L.frac = 1;
     std::vector<SceneK> hk(n_scenes);
     std::vector<SceneD> hd(n_scenes);
     std::vector<int2> items[TL_ITEM_KINDS];
@@ -1903,6 +1926,7 @@ static tlmpm_status batch_create(tlmpm_scene* const* scenes, int32_t n_scenes, v
         hd[s].wacc = b->d_wacc + (size_t)s * TL_MAX_TOOLS * 6;
         L.any_material |= sc->K.material_contact;
         L.general |= general_path(sc->K);
+        L.frac &= sc->D.T != nullptr;
         int c[TL_ITEM_KINDS];
         scene_items(sc, c);
         for (int k = 0; k < TL_ITEM_KINDS; k++)

@@ -226,12 +226,15 @@ struct Gather {
         }
     }
     // a split brick's second partial, added to its first
-    DEV void add(const float* __restrict__ xpart, const int* __restrict__ xflag, const Contrib& C, int s)
+    DEV void add(const SceneK& S, const float* __restrict__ xpart, const int* __restrict__ xbox, const Contrib& C,
+                 int s)
     {
 #pragma unroll
         for (int e = 0; e < 2; e++) {
-            if (C.ai[e] < 0 || !xflag[C.ai[e]]) continue;
-            const float4* xp = (const float4*)(xpart + (size_t)(C.rec[e] + (unsigned)(s * TL_BOXN)) * QP);
+            const int x = C.ai[e] < 0 ? 0 : xbox[C.ai[e]];
+            if (!x) continue;
+            const unsigned rec = C.rec[e] + (unsigned)(x - 1 - C.ai[e]) * (unsigned)(S.scap * TL_BOXN);
+            const float4* xp = (const float4*)(xpart + (size_t)(rec + (unsigned)(s * TL_BOXN)) * QP);
 #pragma unroll
             for (int q = 0; q < QP / 4; q++) {
                 const float4 x4 = xp[q];
@@ -383,6 +386,22 @@ DEV void frac_of(const SceneK& S, const float* X, int gxc, int gyc, int gzc, flo
     t[0] = fminf(fmaxf((float)q0, 0.0f), 1.0f);
     t[1] = fminf(fmaxf((float)q1, 0.0f), 1.0f);
     t[2] = fminf(fmaxf((float)q2, 0.0f), 1.0f);
+}
+
+// ... of the lane's particle, as P2G takes it: from the scene's T, or (FRAC false) from X
+// where a scene of the launch has no T.  A kernel of its own: a branch on D.T keeps the
+// scalars of both ways in registers (a 1.3 % slower pass of a 14M-particle scene).
+template <bool FRAC>
+DEV void cell_position(const SceneK& S, const SceneD& D, const Local& loc, const int4 info, const Lane& L, int p,
+                       float t[3])
+{
+    if constexpr (FRAC) {
+        loc.get(D.T, p, t);
+    } else {
+        float X[3];
+        loc.get(D.X, p, X);
+        frac_of(S, X, info.y * TL_B + L.cxl, info.z * TL_B + L.cyl, info.w * TL_B + L.czl, t);
+    }
 }
 
 // The positions inside the reference cells, once per scene: P2G reads them in place of X
@@ -1075,7 +1094,7 @@ DEV int get_rounds(const int* s_rw)
 
 // P2G of a one-code brick.  s_v: the box's remapped velocities (float4 per node); s_part:
 // TL_ONE_PLACES places of 8 floats.
-template <int MAT, bool SPLIT>
+template <int MAT, bool SPLIT, bool FRAC>
 DEV void p2g_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int nb, KA_Args A, bool fp, float* s_v,
                  float* s_part, int* s_rw)
 {
@@ -1093,7 +1112,7 @@ DEV void p2g_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int 
     float t[3] = {0.0f, 0.0f, 0.0f}, H[9];
     uint32_t code = 0;
     auto load_particle = [&]() {
-        loc.get(D.T, p, t);
+        cell_position<FRAC>(S, D, loc, info, L, p, t);
         code = *loc.one(D.code, p);
         loc.get9(D.H, p, H);
     };
@@ -1234,13 +1253,20 @@ DEV void add_places(const NodePlaces& np, int meta, int bn, int u, const float* 
     }
 }
 
+// Box of a workgroup's partials: that of its brick, or (part 1) of the brick's place in xlist
+template <bool SPLIT>
+DEV int box_of(const SceneD& D, int bi, int part)
+{
+    return SPLIT && part ? D.xin[bi] - 1 : bi;
+}
+
 // MAT 0: Neo-Hookean only; MAT 1: the scene's material (Neo-Hookean or
 // fixed-corotated) with Newtonian viscosity.
 // part 0 takes the brick's first same-code round (all rounds unless the brick is
 // split), part 1 the later rounds of a split brick (a brick whose cells hold two
 // codes and need more than one round): the two run as separate workgroups, each
 // with its own box partial, so that such bricks do not lengthen the launch.
-template <int MAT, bool SPLIT>
+template <int MAT, bool SPLIT, bool FRAC>
 DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
 {
     __shared__ BoxTab Tc;
@@ -1261,7 +1287,7 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
     int nbv;
     bool changed;
     if (one_code<true>(S, D, bx, by, bz, nbv, changed)) {
-        p2g_one<MAT, SPLIT>(S, D, bi, info, nbv, A, fp, s_vt, s_part, s_rw);
+        p2g_one<MAT, SPLIT, FRAC>(S, D, bi, info, nbv, A, fp, s_vt, s_part, s_rw);
         return;
     }
     const bool grouped = D.bmixed[brick] != 0; // a cell holds two codes: same-code groups
@@ -1289,7 +1315,7 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
     float t[3] = {0.0f, 0.0f, 0.0f}, H[9];
     uint32_t code = 0;
     auto load_particle = [&]() {
-        loc.get(D.T, p, t);
+        cell_position<FRAC>(S, D, loc, info, L, p, t);
         code = *loc.one(D.code, p);
         loc.get9(D.H, p, H);
     };
@@ -1327,8 +1353,8 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
                 g1.load(D.rs, C, s + 1, s + 1 < cr);
             }
             if (xg_rs) {
-                g0.add(D.rs_x, D.xrs, C, s);
-                if (s + 1 < cr) g1.add(D.rs_x, D.xrs, C, s + 1);
+                g0.add(S, D.rs_x, D.xrs, C, s);
+                if (s + 1 < cr) g1.add(S, D.rs_x, D.xrs, C, s + 1);
             }
             float a0[4], a1[4];
             g0.sum(a0);
@@ -1422,10 +1448,10 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
         np.set(late(tid) >> 2);
         if (bn < TL_BOXN)
             add_places<2, 7>(np, mt, bn, u, s_part, s_cs, s_acc, r == r0, r + 1 == rounds,
-                          (part ? D.p2g_x : D.p2g) + (size_t)bi * (unsigned)(S.scap * TL_BOXN * 8));
+                          (part ? D.p2g_x : D.p2g) + (size_t)box_of<SPLIT>(D, bi, part) * (unsigned)(S.scap * TL_BOXN * 8));
     }
     if (!A.do_p2g) return;
-    if (SPLIT && part == 0 && tid == 0) D.xp2g[bi] = split ? 1 : 0;
+    if (SPLIT && part == 0 && tid == 0) D.xp2g[bi] = split ? D.xin[bi] : 0;
 }
 
 // --------------------------------------------------------------------------- K_B
@@ -1695,8 +1721,8 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
             g1.load(D.p2g, C, s + 1, s + 1 < c);
         }
         if (xsplit) {
-            g0.add(D.p2g_x, D.xp2g, C, s);
-            if (s + 1 < c) g1.add(D.p2g_x, D.xp2g, C, s + 1);
+            g0.add(S, D.p2g_x, D.xp2g, C, s);
+            if (s + 1 < c) g1.add(S, D.p2g_x, D.xp2g, C, s + 1);
         }
         float a0[7], a1[7];
         g0.sum(a0);
@@ -1794,9 +1820,9 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
         np.set(late(tid) >> 2);
         if (bn < TL_BOXN)
             add_places<1, 4>(np, mt, bn, u4, s_part, s_cs, s_acc, r == r0, r + 1 == rounds,
-                          (part ? D.rs_x : D.rs) + (size_t)bi * (unsigned)(S.scap * TL_BOXN * 4));
+                          (part ? D.rs_x : D.rs) + (size_t)box_of<SPLIT>(D, bi, part) * (unsigned)(S.scap * TL_BOXN * 4));
     }
-    if (SPLIT && part == 0 && tid == 0) D.xrs[bi] = split ? 1 : 0;
+    if (SPLIT && part == 0 && tid == 0) D.xrs[bi] = split ? D.xin[bi] : 0;
     put_box(S, D, bi, brick, part, track, ap, bb, s_bb);
 }
 
@@ -1881,8 +1907,9 @@ DEV void cell_summaries(const SceneK& S, const SceneD& D, int bi, int brick)
         if (!m) {
             D.bround[bi] = 0; // no split workgroup for this brick
         } else if (S.xcap > 0 && !D.xin[bi]) { // (codes only gain digits: once mixed, always mixed)
-            D.xin[bi] = 1;
-            D.xlist[atomicAdd(D.ctr + 3, 1)] = bi;
+            const int j = atomicAdd(D.ctr + 3, 1);
+            D.xlist[j] = bi;
+            D.xin[bi] = j + 1;
         }
     }
     if (!m) return;
@@ -2322,7 +2349,7 @@ DEV int split_brick(const SceneK& S, const SceneD& D, int j)
 
 // SPLIT false: one workgroup per brick, every brick keeps all its rounds (scenes with
 // S.xcap = 0, and batches of such scenes); true: the xcap extra workgroups first.
-template <int MAT, bool SPLIT>
+template <int MAT, bool SPLIT, bool FRAC>
 __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(MAT == 0 ? 6 : 4))) void k_p2g(SceneK S,
                                                                                                      SceneD D,
                                                                                                      KA_Args A)
@@ -2330,9 +2357,9 @@ __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(MAT == 0 
     const int b = blockIdx.x, nx = SPLIT ? S.xcap : 0;
     const int bi = SPLIT && b < nx ? split_brick(S, D, b) : b - nx;
     if (SPLIT && bi < 0) return;
-    p2g_body<MAT, SPLIT>(S, D, bi, A, SPLIT && b < nx);
+    p2g_body<MAT, SPLIT, FRAC>(S, D, bi, A, SPLIT && b < nx);
 }
-template <int MAT, bool SPLIT>
+template <int MAT, bool SPLIT, bool FRAC>
 __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(MAT == 0 ? 6 : 4))) void k_p2g_b(
     const SceneK* __restrict__ Ks, const SceneD* __restrict__ Ds, const int2* __restrict__ it,
     const int2* __restrict__ xit, int nx, KA_Args A)
@@ -2343,7 +2370,7 @@ __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(MAT == 0 
     const SceneD& D = Ds[t.x];
     const int bi = SPLIT && b < nx ? split_brick(S, D, t.y) : t.y;
     if (SPLIT && bi < 0) return;
-    p2g_body<MAT, SPLIT>(S, D, bi, A, SPLIT && b < nx);
+    p2g_body<MAT, SPLIT, FRAC>(S, D, bi, A, SPLIT && b < nx);
 }
 template <bool SPLIT>
 __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(6))) void k_g2p(SceneK S, SceneD D, int cur)
@@ -2405,6 +2432,13 @@ static hipError_t tl_run_split(const TlLaunch& L, KP kp, KB kb, KPX kpx, KBX kbx
     return hipGetLastError();
 }
 
+template <int MAT, bool FRAC>
+static hipError_t run_p2g(const TlLaunch& L, KA_Args A)
+{
+    return tl_run_split(L, k_p2g<MAT, false, FRAC>, k_p2g_b<MAT, false, FRAC>, k_p2g<MAT, true, FRAC>,
+                        k_p2g_b<MAT, true, FRAC>, A);
+}
+
 static int blocks_of(long long n, int per) { return (int)((n + per - 1) / per); }
 static int plain_bricks(const TlLaunch& L) { return L.S ? L.D->n_active : 0; }
 static int plain_nodes(const TlLaunch& L) { return L.S ? blocks_of(L.S->NN, 256) : 0; }
@@ -2441,9 +2475,8 @@ hipError_t tl_launch_p2g(const TlLaunch* L, int do_p2g, int tabs_differ, int cur
     A.tabs_differ = tabs_differ;
     A.cur = cur;
     A.rsb = rsb;
-    if (L->general)
-        return tl_run_split(*L, k_p2g<1, false>, k_p2g_b<1, false>, k_p2g<1, true>, k_p2g_b<1, true>, A);
-    return tl_run_split(*L, k_p2g<0, false>, k_p2g_b<0, false>, k_p2g<0, true>, k_p2g_b<0, true>, A);
+    if (L->frac) return L->general ? run_p2g<1, true>(*L, A) : run_p2g<0, true>(*L, A);
+    return L->general ? run_p2g<1, false>(*L, A) : run_p2g<0, false>(*L, A);
 }
 
 hipError_t tl_launch_g2p(const TlLaunch* L, int cur)
