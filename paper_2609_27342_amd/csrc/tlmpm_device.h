@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include "tlmpm_common.h"
+#include "tlmpm_keys.h"
 
 #define DEV __device__ __forceinline__
 
@@ -458,20 +459,10 @@ DEV void slots_body(const SceneK& S, const SceneD& D, int bi, int dst, int src, 
         cc[d] = D.ccode[cell[d]];
         many |= cc[d] == TL_CC_MIXED;
     }
-    // Up to four distinct codes are kept in registers, ascending (~0: none): nearly every
-    // node.  More of them, or a cell whose particles must be looked at, take the list below
-    // (an array indexed at run time lives in memory; with it for every node a scene of 16k
-    // particles took 10.9 us a substep, 6.3 us now).
-    uint32_t a[4] = {~0u, ~0u, ~0u, ~0u};
-    auto add = [&](uint32_t k) { // ~0: nothing
-        const bool have = k == a[0] || k == a[1] || k == a[2] || k == a[3];
-        many |= !have && a[3] != ~0u;
-        k = have ? ~0u : k;
-        a[3] = min(a[3], max(a[2], k));
-        a[2] = min(a[2], max(a[1], k));
-        a[1] = min(a[1], max(a[0], k));
-        a[0] = min(a[0], k);
-    };
+    // Up to four distinct codes are kept in registers (FourKeys): nearly every node.  More of
+    // them, or a cell whose particles must be looked at, take the list below (with it for
+    // every node a scene of 16k particles took 10.9 us a substep, 6.3 us now).
+    FourKeys keys;
     if (!many) {
         uint4 few[8];
 #pragma unroll
@@ -486,18 +477,18 @@ DEV void slots_body(const SceneK& S, const SceneD& D, int bi, int dst, int src, 
         for (int d = 0; d < 8; d++) {
             const uint32_t n = cc[d] < TL_CC_FEW ? 1u : cc[d] != TL_CC_EMPTY ? (cc[d] & 7u) : 0u;
             if (!__any(n > 0u)) continue;
-            add(n > 0u ? few[d].x : ~0u);
+            keys.add(n > 0u ? few[d].x : ~0u);
             if (!__any(n > 1u)) continue;
-            add(n > 1u ? few[d].y : ~0u);
-            add(n > 2u ? few[d].z : ~0u);
-            add(n > 3u ? few[d].w : ~0u);
+            keys.add(n > 1u ? few[d].y : ~0u);
+            keys.add(n > 2u ? few[d].z : ~0u);
+            keys.add(n > 3u ? few[d].w : ~0u);
         }
-        const int c = (a[0] != ~0u) + (a[1] != ~0u) + (a[2] != ~0u) + (a[3] != ~0u);
-        if (!many && c <= S.scap) {
+        const int c = keys.count();
+        if (!keys.more && c <= S.scap) {
             D.cnt[dst][id] = (uint8_t)c;
 #pragma unroll
             for (int s = 0; s < 4; s++)
-                if (s < c) D.scode[dst][s * S.NN + id] = a[s];
+                if (s < c) D.scode[dst][s * S.NN + id] = keys.a[s];
             return;
         }
     }
