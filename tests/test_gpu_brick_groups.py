@@ -91,3 +91,53 @@ def test_groups_of_a_batch(tl):
         for j in range(STEPS):
             assert np.array_equal(ws[j][i][:2], alone[i][1][j]), (i, j)
     assert any(np.any(w) for _, ws1 in alone for w in ws1)  # a blade touched something
+
+
+def _at_the_edge(s, side):
+    """The blade's edge through the middle of a layer of bricks, with particles just ahead of it."""
+    dx = s["params"]["dx"]
+    z = (4 * (side // 2) + 2) * dx
+    tools_at = s["tools_at"]
+
+    def lowered(j):
+        t = tools_at(j)
+        bl = t[0]["blade"]
+        return [W.tool(dict(bl, x_e=np.array([bl["x_e"][0], bl["x_e"][1], z])))] + t[1:]
+
+    s["tools_at"] = lowered
+    X = s["X"].astype(np.float64)
+    at = np.all(np.floor(X[:, [0, 2]] / (4 * dx)) == side // 2, axis=1)
+    rng = np.random.default_rng(44)
+    X[at, 0] = tools_at(0)[0]["blade"]["x_e"][0] + rng.uniform(-0.1, 0.1, at.sum()) * dx
+    X[at, 2] = z - rng.uniform(0.02, 0.1, at.sum()) * dx
+    s["X"] = X.astype(np.float32)
+
+
+@pytest.mark.parametrize("n_bricks,side", [(18431, 28), (18432, 28), (34815, 34), (36001, 34)])
+def test_large_groups_against_oracle(tl, n_bricks, side):
+    """8, 9 and 16 bricks per workgroup (from 9 on the bodies' tests of rigid contact take a
+    second wave; 34815 is the last number below the limit of 16, 36001 is held to it and
+    leaves a remainder): wrench and cutting progress too, so that a brick passed over is seen."""
+    nb = min(n_bricks // 2048, 16)
+    late = np.repeat(np.arange(n_bricks) >= 8 * -(-n_bricks // nb), 2)  # a workgroup's ninth brick on
+    s = _scene(n_bricks, side, 43)
+    _at_the_edge(s, side)
+    n, p = s["X"].shape[0], s["params"]
+    print(f"[case] large brick groups bricks={n_bricks} nb={nb} n={n}", flush=True)
+    g, o = tl.Scene(s), oracle.OracleScene(s)
+    scale = np.zeros(2)  # largest force and torque so far: later impulses come from what earlier ones left
+    for j in range(STEPS):
+        wg = g.step(s["tools_at"](j), wrench=True)
+        st, wo = oracle_substep(o, s["tools_at"](j))
+        assert st == 0
+        for k, q in enumerate((slice(0, 3), slice(3, 6))):
+            scale[k] = max(scale[k], np.abs(wo[:, q]).max())
+            assert np.abs(wg[:, q] - wo[:, q]).max() <= TOL * scale[k], (j, wg, wo)
+    assert g.status() == 0 and scale.min() > 0
+    a, b = g.read(("u", "v", "H", "digits", "D")), o.get()
+    assert np.array_equal(a["digits"], b["digits"])
+    eu, ev, eH = state_errs(a, b, s["X"], p)
+    assert eu < TOL and ev < TOL and eH < TOL, (eu, ev, eH)
+    assert (b["D"] > 0).sum() >= side and np.abs(a["D"] - b["D"]).max() <= TOL * b["D"].max()
+    moved = np.abs(b["v"] - s["v0"] - np.array([0.0, 0.0, -9.81 * p["dt"] * STEPS])).max(axis=1) > 0.01
+    assert nb <= 8 or (moved & late).sum() > 20  # impulses there
