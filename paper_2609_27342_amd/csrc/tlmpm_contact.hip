@@ -149,7 +149,6 @@ DEV void scan_offsets(const SceneD& D)
 DEV void anchor_exact(const SceneK& S, const SceneD& D, int bi, int brick, int beg, int end)
 {
     __shared__ float s_r[4][6];
-    const long long N = S.N;
     float r[6] = {1e30f, 1e30f, 1e30f, -1e30f, -1e30f, -1e30f};
     for (int p = beg + threadIdx.x; p < end; p += blockDim.x)
         for (int a = 0; a < 3; a++) {

@@ -451,19 +451,17 @@ DEV CornerW corner_table(const float t[3], int j)
     return c;
 }
 
-// gen(r, out) produces this lane's contribution to corner r of its cell.  Result:
-// res[Q] = sum over the 8 lanes of the cell group of their values for corner j (the
-// lane's own).  REL: corners in the order of CornerW (x and y bits relative to j);
-// else absolute corner indices.  Stage 1 pairs j with j ^ 4 (lane ^ 16):
-// v_permlane16_swap of (z = 0, z = 1) leaves in the even row (z bit of j clear) its
-// own and its partner's z = 0 values, in the odd row the z = 1 values; stages 2 and
-// 3 pair j ^ 2 and j ^ 1 within the quad, each lane sending the value of the
-// partner's side (REL: its other-side value, no select).  The sum tree is ((j,
-// j^4), (j^2, j^6)), ((j^1, j^5), (j^3, j^7)), own operand first, for every lane
-// order.  Corners are generated in (z = 0, z = 1) pairs, so at most 4 x Q partial
-// sums are live.
-template <int Q, bool REL, class Gen>
-DEV void reduce_scatter8(Gen&& gen, float (&res)[Q], int j)
+// gen(r, out) produces this lane's contribution to corner r of its cell, r in the order of
+// CornerW (x and y bits relative to the lane's own corner j).  Result: res[Q] = sum over the
+// 8 lanes of the cell group of their values for corner j.  Stage 1 pairs j with j ^ 4 (lane
+// ^ 16): v_permlane16_swap of (z = 0, z = 1) leaves in the even row (z bit of j clear) its
+// own and its partner's z = 0 values, in the odd row the z = 1 values; stages 2 and 3 pair
+// j ^ 2 and j ^ 1 within the quad, each lane sending its other-side value (the partner's
+// side: no select).  The sum tree is ((j, j^4), (j^2, j^6)), ((j^1, j^5), (j^3, j^7)), own
+// operand first, for every lane order.  Corners are generated in (z = 0, z = 1) pairs, so at
+// most 4 x Q partial sums are live.
+template <int Q, class Gen>
+DEV void reduce_scatter8(Gen&& gen, float (&res)[Q])
 {
     float c1[4][Q];
 #pragma unroll
@@ -479,30 +477,12 @@ DEV void reduce_scatter8(Gen&& gen, float (&res)[Q], int j)
         }
     }
     float c2[2][Q];
-    const bool b1 = (j >> 1) & 1;
 #pragma unroll
     for (int rr = 0; rr < 2; rr++)
 #pragma unroll
-        for (int q = 0; q < Q; q++) {
-            if constexpr (REL) {
-                c2[rr][q] = c1[rr][q] + lane_xor<2>(c1[rr | 2][q]);
-            } else {
-                const float send = b1 ? c1[rr][q] : c1[rr | 2][q];
-                const float keep = b1 ? c1[rr | 2][q] : c1[rr][q];
-                c2[rr][q] = keep + lane_xor<2>(send);
-            }
-        }
-    const bool b0 = j & 1;
+        for (int q = 0; q < Q; q++) c2[rr][q] = c1[rr][q] + lane_xor<2>(c1[rr | 2][q]);
 #pragma unroll
-    for (int q = 0; q < Q; q++) {
-        if constexpr (REL) {
-            res[q] = c2[0][q] + lane_xor<1>(c2[1][q]);
-        } else {
-            const float send = b0 ? c2[0][q] : c2[1][q];
-            const float keep = b0 ? c2[1][q] : c2[0][q];
-            res[q] = keep + lane_xor<1>(send);
-        }
-    }
+    for (int q = 0; q < Q; q++) res[q] = c2[0][q] + lane_xor<1>(c2[1][q]);
 }
 
 // ------------------------------------------------------- history-based friction
@@ -958,10 +938,10 @@ struct Scatter {
     }
     // The sums over the cell's particles for the lane's corner: impulses first (their
     // butterfly then runs while fewer values are live)
-    DEV void sums(int j, float (&d)[3], float (&q)[4]) const
+    DEV void sums(float (&d)[3], float (&q)[4]) const
     {
-        reduce_scatter8<3, true>([&](int r, float* o) { dp(r, o); }, d, j);
-        reduce_scatter8<4, true>([&](int r, float* o) { mp(r, o); }, q, j);
+        reduce_scatter8<3>([&](int r, float* o) { dp(r, o); }, d);
+        reduce_scatter8<4>([&](int r, float* o) { mp(r, o); }, q);
     }
 };
 
@@ -1152,7 +1132,7 @@ DEV void p2g_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int 
         Scatter C;
         scatter_setup<MAT>(S, D, loc, p, valid, rig, code, H, Lg, Gp, t, L.j, C);
         float dp[3], mp[4];
-        C.sums(L.j, dp, mp);
+        C.sums(dp, mp);
         if (r > 0) lds_barrier(); // the places of the last round have been read
         float4* pl = (float4*)(s_part + tl * 8);
         pl[0] = make_float4(mp[0], mp[1], mp[2], mp[3]);
@@ -1439,7 +1419,7 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
         Scatter W;
         scatter_setup<MAT>(S, D, loc, p, valid, rig, code, H, Lg, Gp, t, L.j, W);
         float dp[3], mp[4];
-        W.sums(L.j, dp, mp);
+        W.sums(dp, mp);
         float4* pl = (float4*)(s_part + tl * 8);
         pl[0] = make_float4(mp[0], mp[1], mp[2], mp[3]);
         pl[1] = make_float4(dp[0], dp[1], dp[2], 0.0f);
@@ -1600,7 +1580,7 @@ DEV void g2p_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int 
         const float mm = valid ? m : 0.0f;
         const CornerW cw = corner_table(t, L.j);
         float res[4];
-        reduce_scatter8<4, true>(
+        reduce_scatter8<4>(
             [&](int q, float* o) {
                 const float wx = cw.wx[q & 1], wy = cw.wy[(q >> 1) & 1], wz = cw.wz[q >> 2];
                 float w = wx * wy * wz * mm;
@@ -1609,7 +1589,7 @@ DEV void g2p_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int 
                 o[2] = w * vn1[1];
                 o[3] = w * vn1[2];
             },
-            res, L.j);
+            res);
         if (r > 0) lds_barrier(); // the places of the last round have been read
         *(float4*)(s_part + tl * 4) = make_float4(res[0], res[1], res[2], res[3]);
         lds_barrier();
@@ -1804,7 +1784,7 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
         const float mm = valid ? m : 0.0f;
         const CornerW cw = corner_table(t, L.j);
         float res[4];
-        reduce_scatter8<4, true>(
+        reduce_scatter8<4>(
             [&](int q, float* o) {
                 const float wx = cw.wx[q & 1], wy = cw.wy[(q >> 1) & 1], wz = cw.wz[q >> 2];
                 float w = wx * wy * wz * mm;
@@ -1813,7 +1793,7 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
                 o[2] = w * vn1[1];
                 o[3] = w * vn1[2];
             },
-            res, L.j);
+            res);
         *(float4*)(s_part + tl * 4) = make_float4(res[0], res[1], res[2], res[3]);
         lds_barrier();
         NodePlaces np;
@@ -2013,7 +1993,6 @@ DEV void labels_brick(const SceneK& S, const SceneD& D, int bi, int brick, int m
         s_nb = nb;
     }
     __syncthreads();
-    const long long N = S.N;
     const int beg = D.cell_start[(long long)brick * TL_CELLS], end = D.cell_start[(long long)(brick + 1) * TL_CELLS];
     bool any = false;
     for (int p = beg + threadIdx.x; p < end; p += blockDim.x) {
@@ -2210,7 +2189,6 @@ DEV void aabb_body(const SceneK& S, const SceneD& D, int bi)
     __shared__ float s_bb[4][13];
     __shared__ float s_a[3];
     const int brick = D.active[bi];
-    const long long N = S.N;
     const int beg = D.cell_start[(long long)brick * TL_CELLS], end = D.cell_start[(long long)(brick + 1) * TL_CELLS];
     // current box (0-5), speed (6), reference box (7-12)
     float bb[13] = {1e30f, 1e30f, 1e30f, -1e30f, -1e30f, -1e30f, 0.0f, 1e30f, 1e30f, 1e30f, -1e30f, -1e30f, -1e30f};
@@ -2443,10 +2421,6 @@ static int blocks_of(long long n, int per) { return (int)((n + per - 1) / per); 
 static int plain_bricks(const TlLaunch& L) { return L.S ? L.D->n_active : 0; }
 static int plain_nodes(const TlLaunch& L) { return L.S ? blocks_of(L.S->NN, 256) : 0; }
 static int plain_parts(const TlLaunch& L) { return L.S ? blocks_of(L.S->N, 256) : 0; }
-static int plain_bflags(const TlLaunch& L)
-{
-    return L.S ? blocks_of((long long)L.S->cbx * L.S->cby * L.S->cbz, 256) : 0;
-}
 
 // the label pass and rigid contact: group_of(n) bricks per workgroup
 template <class KP, class KB>

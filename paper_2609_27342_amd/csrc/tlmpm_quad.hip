@@ -241,7 +241,6 @@ __global__ __launch_bounds__(TL_QWG) void k_q_slots(SceneK S, SceneD D, int par)
     }
     if (tid < TL_SCAP_MAX) s_keys[tid] = TL_QEMPTY;
     __syncthreads();
-    const long long N = S.N;
     const int rounds = q_rounds(D, bi), h = tid >> 6;
     int c[3];
     q_cell(bx, by, bz, tid & 63, c);
