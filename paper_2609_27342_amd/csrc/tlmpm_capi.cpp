@@ -347,7 +347,8 @@ Offsets plan(const tlmpm_scene_desc* d, long long n_active, int xcap)
     // have one, and the quadratic stencil, whose boxes take 10976 + 64 of the 12000 bytes, has
     // none.  Behind them, from the end of that room back, lie the brick tables, and the
     // positions T in the cells where they fit (up to about 60 particles per cell with 8
-    // slots, fewer than 8 with one slot; P2G forms them from X in other scenes).
+    // slots, 45 where bricks are split, fewer than 8 with one slot; P2G forms them from X in
+    // other scenes).
     const size_t box = scap * TL_BOXN * f; // one float of a box
     o.p2g = L.take((size_t)n_active * box * 8); // 7 components padded to 8
     o.rs = L.take((size_t)n_active * box * 4);

@@ -1,15 +1,16 @@
 // tlmpm_common.h -- structures shared by the host runtime and the gfx950 kernels.
 //
 // Layout in HBM (one scene, all carved from the caller's workspace):
-//   particles, sorted by (brick, cell parity class, cell, input order), SoA float:
+//   particles, sorted by (brick, cell parity class, cell, input order), rows of three floats:
 //     X[N][3] reference positions, u[N][3] = x - X, v[N][3], H[3][N][3] = F - I by rows
 //   code[N]      u32: side mask s1 (bits 0-14: digit == 1), s2 (bits 15-29: digit == 2),
 //                bit 30: code_prev[p] holds the code the pending F update must use,
 //                bit 31: material-contact candidate
 //   grid: node ids are brick-major, id = nodebrick * 64 + (lz * 16 + ly * 4 + lx)
 //     slot tables (two buffers): count[node] u8, code[S_CAP][node] u32 (ascending)
-//     P2G partials  [8 contributors][S_CAP][node][8] float  (m, p, dp, pad)
-//     MUSL partials [8 contributors][S_CAP][node][4] float  (m, p~)
+//   partials: every active brick's sums over its 5x5x5 box of nodes
+//     P2G  [active brick][slot][box node][8] float  (m, p, dp, pad)
+//     MUSL [active brick][slot][box node][4] float  (m, p~)
 #pragma once
 #include <stdint.h>
 

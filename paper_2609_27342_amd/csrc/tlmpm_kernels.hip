@@ -27,15 +27,16 @@
 // a box is finalized, by the node's quad, a component per lane.
 //
 // What bounds P2G and G2P: in a large scene vector issue and memory together (14M
-// particles: P2G 78 % of the issue slots at 3.7 TB/s, G2P 64 % at 3.8, where a device copy
+// particles: P2G 78 % of the issue slots at 3.7 TB/s, G2P 60 % at 3.8, where a device copy
 // reaches 5.1), in a small one the chain of dependent phases in a workgroup (brick record,
 // cell index and partial gather, coupling, particle stage, sums); at three workgroups per
 // CU (80 registers, 43 to 53 KB of LDS).  Geometry that depends on the thread alone comes
 // from tables, rows of particles at 32-bit offsets from the brick's first (1250 -> 1050
 // vector instructions per wave of P2G: 183k particles on a cut 23.7 -> 22.9 us, 64 scenes
-// 301 -> 287 us, the plastic P2G 58.9 -> 54.6 us, 14M particles 572 -> 564 us).  The registers
-// hold only because a round recomputes its lane geometry (`late`): hoisted out of the
-// round loop it spills 20 and more words a lane.
+// 301 -> 287 us, 14M particles 572 -> 564 us, the plastic P2G 58.9 -> 54.6 us and 37 since
+// its eigen-decomposition is cheaper).  The registers hold only because a round recomputes
+// its lane geometry (`late`): hoisted out of the round loop it spills 20 and more words a
+// lane.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
