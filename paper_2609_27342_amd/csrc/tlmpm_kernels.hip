@@ -27,8 +27,8 @@
 // a box is finalized, by the node's quad, a component per lane.
 //
 // What bounds P2G and G2P: in a large scene vector issue and memory together (14M
-// particles: P2G 78 % of the issue slots at 3.7 TB/s, G2P 60 % at 3.8, where a device copy
-// reaches 5.1), in a small one the chain of dependent phases in a workgroup (brick record,
+// particles: P2G about 80 % of the issue slots at 3.8 TB/s, G2P 60 % at 3.9, where a device
+// copy reaches 5.1), in a small one the chain of dependent phases in a workgroup (brick record,
 // cell index and partial gather, coupling, particle stage, sums); at three workgroups per
 // CU (80 registers, 43 to 53 KB of LDS).  Geometry that depends on the thread alone comes
 // from tables, rows of particles at 32-bit offsets from the brick's first (1250 -> 1050
