@@ -134,13 +134,13 @@ struct SceneD {
     int* tstamp;   // [2] each slot-table buffer holds the label changes up to this substep stamp
     float* p2g;    // [active brick][scap][125 box nodes][8]: each brick's P2G box sums
     float* rs;     // [active brick][scap][125 box nodes][4]: each brick's re-scatter box sums
-    float* p2g_x;  // the same two for the later same-code rounds of the split bricks: [xcap] boxes
+    float* p2g_x;  // the same two for the later same-code rounds of the bricks in xlist: [xcap] boxes
     float* rs_x;
-    int* xp2g;     // [active brick] 1 + box of p2g_x with this substep's sums of the brick (0: not split)
-    int* xrs;      // [active brick] 1 + box of rs_x (and aabb_x) of its last G2P (0: not split)
+    int* xp2g;     // [active brick] where p2g_x holds this substep's further sums (split_offset; 0: not split)
+    int* xrs;      // [active brick] where rs_x holds those of its last G2P (and aabb_x a box; 0: not split)
     float* aabb_x; // [n_bricks][8] box of a split brick's later rounds
     int* xlist;    // [active brick] active indices of the bricks with a mixed cell (count: ctr[3])
-    int* xin;      // [active brick] 1 + its place in xlist (0: not there)
+    int* xin;      // [active brick] the brick is in xlist
     int* xg;       // [1] the last G2P split the mixed bricks (rs_x, xrs, aabb_x in use)
     int* bact;     // [bricks] active index of a brick, -1 if it holds no particle
     float* hist;   // rigid contact history [TL_MAX_TOOLS+1][4][N]: u_t xyz, stamp

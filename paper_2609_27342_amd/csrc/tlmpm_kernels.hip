@@ -226,16 +226,17 @@ struct Gather {
             }
         }
     }
-    // a split brick's second partial, added to its first
-    DEV void add(const SceneK& S, const float* __restrict__ xpart, const int* __restrict__ xbox, const Contrib& C,
-                 int s)
+    // a split brick's second partial, added to its first (xbox: see split_offset).  Its word
+    // is read where it is used: kept from slot to slot, the words of both contributors cost
+    // G2P of a batch six more spilled registers (256 scenes: 0.85 -> 0.88 ms).
+    DEV void add(const float* __restrict__ xpart, const int* __restrict__ xbox, const Contrib& C, int s)
     {
 #pragma unroll
         for (int e = 0; e < 2; e++) {
-            const int x = C.ai[e] < 0 ? 0 : xbox[C.ai[e]];
+            const int ai = late(C.ai[e]);
+            const unsigned x = ai < 0 ? 0u : (unsigned)xbox[ai];
             if (!x) continue;
-            const unsigned rec = C.rec[e] + (unsigned)(x - 1 - C.ai[e]) * (unsigned)(S.scap * TL_BOXN);
-            const float4* xp = (const float4*)(xpart + (size_t)(rec + (unsigned)(s * TL_BOXN)) * QP);
+            const float4* xp = (const float4*)(xpart + (size_t)(C.rec[e] + x - 1u + (unsigned)(s * TL_BOXN)) * QP);
 #pragma unroll
             for (int q = 0; q < QP / 4; q++) {
                 const float4 x4 = xp[q];
@@ -1234,11 +1235,12 @@ DEV void add_places(const NodePlaces& np, int meta, int bn, int u, const float* 
     }
 }
 
-// Box of a workgroup's partials: that of its brick, or (part 1) of the brick's place in xlist
-template <bool SPLIT>
-DEV int box_of(const SceneD& D, int bi, int part)
+// Word of a split brick in xp2g and xrs, written by its second workgroup: 1 + what the
+// records of its second box, `boxes` further on, are away from those of its first, modulo
+// 2^32.  Never 0: distances are multiples of a box.
+DEV int split_offset(const SceneK& S, int boxes)
 {
-    return SPLIT && part ? D.xin[bi] - 1 : bi;
+    return (int)((unsigned)boxes * (unsigned)(S.scap * TL_BOXN) + 1u);
 }
 
 // MAT 0: Neo-Hookean only; MAT 1: the scene's material (Neo-Hookean or
@@ -1246,9 +1248,10 @@ DEV int box_of(const SceneD& D, int bi, int part)
 // part 0 takes the brick's first same-code round (all rounds unless the brick is
 // split), part 1 the later rounds of a split brick (a brick whose cells hold two
 // codes and need more than one round): the two run as separate workgroups, each
-// with its own box partial, so that such bricks do not lengthen the launch.
+// with its own box partial (box: its index in p2g or p2g_x), so that such bricks do not
+// lengthen the launch.
 template <int MAT, bool SPLIT, bool FRAC>
-DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
+DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part, int box)
 {
     __shared__ BoxTab Tc;
     __shared__ BoxTab Tr;
@@ -1334,8 +1337,8 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
                 g1.load(D.rs, C, s + 1, s + 1 < cr);
             }
             if (xg_rs) {
-                g0.add(S, D.rs_x, D.xrs, C, s);
-                if (s + 1 < cr) g1.add(S, D.rs_x, D.xrs, C, s + 1);
+                g0.add(D.rs_x, D.xrs, C, s);
+                if (s + 1 < cr) g1.add(D.rs_x, D.xrs, C, s + 1);
             }
             float a0[4], a1[4];
             g0.sum(a0);
@@ -1429,10 +1432,10 @@ DEV void p2g_body(const SceneK& S, const SceneD& D, int bi, KA_Args A, int part)
         np.set(late(tid) >> 2);
         if (bn < TL_BOXN)
             add_places<2, 7>(np, mt, bn, u, s_part, s_cs, s_acc, r == r0, r + 1 == rounds,
-                          (part ? D.p2g_x : D.p2g) + (size_t)box_of<SPLIT>(D, bi, part) * (unsigned)(S.scap * TL_BOXN * 8));
+                          (part ? D.p2g_x : D.p2g) + (size_t)box * (unsigned)(S.scap * TL_BOXN * 8));
     }
     if (!A.do_p2g) return;
-    if (SPLIT && part == 0 && tid == 0) D.xp2g[bi] = split ? D.xin[bi] : 0;
+    if (SPLIT && tid == 0 && (part || !split)) D.xp2g[bi] = part ? split_offset(S, box - bi) : 0;
 }
 
 // --------------------------------------------------------------------------- K_B
@@ -1606,7 +1609,7 @@ DEV void g2p_one(const SceneK& S, const SceneD& D, int bi, const int4 info, int 
 }
 
 template <bool SPLIT>
-DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
+DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part, int box)
 {
     __shared__ BoxTab T;
     __shared__ __align__(16) float s_grid[(TL_BOX_SLOTS + 1) * 8]; // per slot (1 - beta) v^n + dv, v^n + dv; a zero
@@ -1702,8 +1705,8 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
             g1.load(D.p2g, C, s + 1, s + 1 < c);
         }
         if (xsplit) {
-            g0.add(S, D.p2g_x, D.xp2g, C, s);
-            if (s + 1 < c) g1.add(S, D.p2g_x, D.xp2g, C, s + 1);
+            g0.add(D.p2g_x, D.xp2g, C, s);
+            if (s + 1 < c) g1.add(D.p2g_x, D.xp2g, C, s + 1);
         }
         float a0[7], a1[7];
         g0.sum(a0);
@@ -1801,9 +1804,9 @@ DEV void g2p_body(const SceneK& S, const SceneD& D, int bi, int cur, int part)
         np.set(late(tid) >> 2);
         if (bn < TL_BOXN)
             add_places<1, 4>(np, mt, bn, u4, s_part, s_cs, s_acc, r == r0, r + 1 == rounds,
-                          (part ? D.rs_x : D.rs) + (size_t)box_of<SPLIT>(D, bi, part) * (unsigned)(S.scap * TL_BOXN * 4));
+                          (part ? D.rs_x : D.rs) + (size_t)box * (unsigned)(S.scap * TL_BOXN * 4));
     }
-    if (SPLIT && part == 0 && tid == 0) D.xrs[bi] = split ? D.xin[bi] : 0;
+    if (SPLIT && tid == 0 && (part || !split)) D.xrs[bi] = part ? split_offset(S, box - bi) : 0;
     put_box(S, D, bi, brick, part, track, ap, bb, s_bb);
 }
 
@@ -1888,9 +1891,8 @@ DEV void cell_summaries(const SceneK& S, const SceneD& D, int bi, int brick)
         if (!m) {
             D.bround[bi] = 0; // no split workgroup for this brick
         } else if (S.xcap > 0 && !D.xin[bi]) { // (codes only gain digits: once mixed, always mixed)
-            const int j = atomicAdd(D.ctr + 3, 1);
-            D.xlist[j] = bi;
-            D.xin[bi] = j + 1;
+            D.xin[bi] = 1;
+            D.xlist[atomicAdd(D.ctr + 3, 1)] = bi;
         }
     }
     if (!m) return;
@@ -2336,7 +2338,7 @@ __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(MAT == 0 
     const int b = blockIdx.x, nx = SPLIT ? S.xcap : 0;
     const int bi = SPLIT && b < nx ? split_brick(S, D, b) : b - nx;
     if (SPLIT && bi < 0) return;
-    p2g_body<MAT, SPLIT, FRAC>(S, D, bi, A, SPLIT && b < nx);
+    p2g_body<MAT, SPLIT, FRAC>(S, D, bi, A, SPLIT && b < nx, SPLIT && b < nx ? b : bi);
 }
 template <int MAT, bool SPLIT, bool FRAC>
 __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(MAT == 0 ? 6 : 4))) void k_p2g_b(
@@ -2349,7 +2351,7 @@ __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(MAT == 0 
     const SceneD& D = Ds[t.x];
     const int bi = SPLIT && b < nx ? split_brick(S, D, t.y) : t.y;
     if (SPLIT && bi < 0) return;
-    p2g_body<MAT, SPLIT, FRAC>(S, D, bi, A, SPLIT && b < nx);
+    p2g_body<MAT, SPLIT, FRAC>(S, D, bi, A, SPLIT && b < nx, SPLIT && b < nx ? t.y : bi);
 }
 template <bool SPLIT>
 __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(6))) void k_g2p(SceneK S, SceneD D, int cur)
@@ -2357,7 +2359,7 @@ __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(6))) void
     const int b = blockIdx.x, nx = SPLIT ? S.xcap : 0;
     const int bi = SPLIT && b < nx ? split_brick(S, D, b) : b - nx;
     if (SPLIT && bi < 0) return;
-    g2p_body<SPLIT>(S, D, bi, cur, SPLIT && b < nx);
+    g2p_body<SPLIT>(S, D, bi, cur, SPLIT && b < nx, SPLIT && b < nx ? b : bi);
 }
 template <bool SPLIT>
 __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(6))) void k_g2p_b(
@@ -2370,7 +2372,7 @@ __global__ __launch_bounds__(TL_WG) __attribute__((amdgpu_waves_per_eu(6))) void
     const SceneD& D = Ds[t.x];
     const int bi = SPLIT && b < nx ? split_brick(S, D, t.y) : t.y;
     if (SPLIT && bi < 0) return;
-    g2p_body<SPLIT>(S, D, bi, cur, SPLIT && b < nx);
+    g2p_body<SPLIT>(S, D, bi, cur, SPLIT && b < nx, SPLIT && b < nx ? t.y : bi);
 }
 
 // ------------------------------------------------------------------- launchers
