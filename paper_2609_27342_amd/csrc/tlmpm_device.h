@@ -407,8 +407,9 @@ DEV int late(int x)
 // ascending order (compact slots, Sec. III-G).  Rebuilt only next to the bricks whose
 // codes changed in this substep's label pass; a destination buffer that is behind the
 // source takes over the nodes next to the bricks changed since it was built.  Bound by the
-// loads of the bricks' stamps: 80 us for the 2.0M nodes of a 14M-particle scene, on its second
-// stream (94 us with a copy of every node each substep).
+// loads of the bricks' stamps: 67 us for the 2.0M nodes of a 14M-particle scene, on its second
+// stream (94 us with a copy of every node each substep; 71 us with nodes of four codes in the
+// long list).
 DEV void slots_body(const SceneK& S, const SceneD& D, int bi, int dst, int src, int force)
 {
     const long long id = (long long)bi * blockDim.x + threadIdx.x;
