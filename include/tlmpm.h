@@ -245,7 +245,8 @@ tlmpm_status tlmpm_contact_stats(tlmpm_scene* scene, double out[8]);
  *   split_lo, split_hi, split_div, split_cap: scenes of split_lo..split_hi active
  *       bricks run the later rounds of bricks with a mixed cell in min(split_cap,
  *       active / split_div) extra workgroups of P2G and G2P (512, 4096, 4, 256;
- *       split_cap 0 turns the split off);
+ *       split_cap 0 turns the split off; with split_div 1 a few less, as many as
+ *       the workspace has room for);
  *   one_stream_bricks: a single scene of at most this many active bricks runs a
  *       substep with a label pass on one stream (label pass and rigid contact in
  *       one launch, slot tables and pair search in one launch), larger ones put
